@@ -30,8 +30,8 @@
 
 #include "lattice.h"
 #include "common.hpp"
+#include "launch.hpp"
 #include "stage_scalar.hpp"
-#include "stage_rows.hpp"
 #include "stage_u1.hpp"
 #include "stage_su2.hpp"
 #include "stage_gauss.hpp"
@@ -69,21 +69,6 @@ void su2_geometry(lat_ctx *c);
 size_t u1_partial_capacity(int N);
 void u1_geometry(lat_ctx *c);
 lat_status batch_step(lat_ctx *c, int64_t nsteps);
-
-struct TileCfg {
-    int tx, ty;
-};
-constexpr TileCfg kTiles[] = {{64, 4}, {64, 8}, {32, 8}, {16, 16}, {8, 8}};
-constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-
-enum Variant : int {
-    kKickOnly = 0,     // no drift, kick, momenta in place (VV first point, LF sync)
-    kKickOnlyRed = 1,  // same + reductions (self-consistent first point)
-    kDriftKick = 2,    // drift on load, kick (VV inner and last points)
-    kDriftKickRed = 3, // same + reductions (self-consistent)
-    kKickDrift = 4,    // kick, drift at end (leapfrog)
-    kEnergy = 5        // kick on a copy + reductions, writes nothing
-};
 
 }  // namespace
 
@@ -419,130 +404,6 @@ void geometry_from_env(lat_ctx *c)
 // ---------------------------------------------------------------------------
 // kernel dispatch
 // ---------------------------------------------------------------------------
-template <typename T, int NF, int TX, int TY>
-hipError_t launch_variant(int variant, const ScalarArgs<T> &a, int nb, hipStream_t s)
-{
-    const dim3 grid(nb), block(TX * TY);
-    switch (variant) {
-    case kKickOnly:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, false, false, true>), grid, block, 0, s, a);
-        break;
-    case kKickOnlyRed:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, true, false, true>), grid, block, 0, s, a);
-        break;
-    case kDriftKick:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, true, false, false, true, true>), grid, block, 0, s, a);
-        break;
-    case kDriftKickRed:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, true, false, true, true, true>), grid, block, 0, s, a);
-        break;
-    case kKickDrift:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, true, false, true, true>), grid, block, 0, s, a);
-        break;
-    case kEnergy:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, true, false, false>), grid, block, 0, s, a);
-        break;
-    default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-template <typename T, int NF, int XS, int TY, int PF = 1, int VW = 1, int LP = 0>
-hipError_t launch_rows_variant(int variant, const ScalarArgs<T> &a, int nb, hipStream_t s)
-{
-    const dim3 grid(nb), block(64 * TY);
-    switch (variant) {
-    case kKickOnly:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, false, false, true, PF, VW, LP>), grid, block, 0, s, a);
-        break;
-    case kKickOnlyRed:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, true, false, true, PF, VW, LP>), grid, block, 0, s, a);
-        break;
-    case kDriftKick:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, true, false, false, true, true, PF, VW, LP>), grid, block, 0, s, a);
-        break;
-    case kDriftKickRed:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, true, false, true, true, true, PF, VW, LP>), grid, block, 0, s, a);
-        break;
-    case kKickDrift:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, true, false, true, true, PF, VW, LP>), grid, block, 0, s, a);
-        break;
-    case kEnergy:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, true, false, false, PF, VW, LP>), grid, block, 0, s, a);
-        break;
-    default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-// pf: prefetch depth in planes (2 is instantiated for N = 256 with 4-row
-// blocks only; 8-row float64 blocks would spill at that depth).
-// vw > 1: 16-byte accesses (two float64 or four float32 sites per lane and
-// access), instantiated where the row holds a whole number of them per lane:
-// N = 128, 256 in float64, N = 256 in float32.
-// lp: store policy of the row kernel (RowPolicy in stage_rows.hpp; 1 streams
-// the first part of the march past the caches), instantiated for the N = 256
-// defaults (float64 4-row blocks two planes ahead, float32 4-row blocks four
-// planes ahead with 16-byte accesses); elsewhere policy 0.
-template <typename T, int NF>
-hipError_t launch_rows(int N, int ty, int pf, int vw, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s,
-                       int lp = 0)
-{
-    const int xs = N / 64;
-    constexpr int V = 16 / (int)sizeof(T);
-    if constexpr (sizeof(T) == 8) {
-        if (lp == 1 && vw == 1 && pf == 2 && xs == 4 && ty == 4)
-            return launch_rows_variant<T, NF, 4, 4, 2, 1, 1>(variant, a, nb, s);
-    } else {
-        if (lp == 1 && vw > 1 && pf == 4 && xs == 4 && ty == 4)
-            return launch_rows_variant<T, NF, 4, 4, 4, V, 1>(variant, a, nb, s);
-    }
-    if (vw > 1 && xs % V == 0) {
-        if (pf == 2 && xs == 4 && ty == 4) return launch_rows_variant<T, NF, 4, 4, 2, V>(variant, a, nb, s);
-        if constexpr (V == 4) {
-            if (pf == 2 && xs == 4 && ty == 8) return launch_rows_variant<T, NF, 4, 8, 2, V>(variant, a, nb, s);
-            if (pf == 3 && xs == 4 && ty == 4) return launch_rows_variant<T, NF, 4, 4, 3, V>(variant, a, nb, s);
-            if (pf == 4 && xs == 4 && ty == 4) return launch_rows_variant<T, NF, 4, 4, 4, V>(variant, a, nb, s);
-        }
-        if (xs == 4) return ty == 4 ? launch_rows_variant<T, NF, 4, 4, 1, V>(variant, a, nb, s)
-                                    : launch_rows_variant<T, NF, 4, 8, 1, V>(variant, a, nb, s);
-        if constexpr (V == 2) {
-            if (xs == 2) return ty == 4 ? launch_rows_variant<T, NF, 2, 4, 1, V>(variant, a, nb, s)
-                                        : launch_rows_variant<T, NF, 2, 8, 1, V>(variant, a, nb, s);
-        }
-        return hipErrorInvalidValue;
-    }
-    if (pf == 2 && xs == 4 && ty == 4) return launch_rows_variant<T, NF, 4, 4, 2>(variant, a, nb, s);
-    if constexpr (sizeof(T) == 8) {
-        if (pf == 3 && xs == 4 && ty == 4) return launch_rows_variant<T, NF, 4, 4, 3>(variant, a, nb, s);
-    }
-    if (ty == 4) {
-        if (xs == 1) return launch_rows_variant<T, NF, 1, 4>(variant, a, nb, s);
-        if (xs == 2) return launch_rows_variant<T, NF, 2, 4>(variant, a, nb, s);
-        if (xs == 4) return launch_rows_variant<T, NF, 4, 4>(variant, a, nb, s);
-    } else {
-        if (xs == 1) return launch_rows_variant<T, NF, 1, 8>(variant, a, nb, s);
-        if (xs == 2) return launch_rows_variant<T, NF, 2, 8>(variant, a, nb, s);
-        if (xs == 4) return launch_rows_variant<T, NF, 4, 8>(variant, a, nb, s);
-    }
-    return hipErrorInvalidValue;
-}
-
-template <typename T, int NF>
-hipError_t launch_tile(int tile, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s)
-{
-    switch (tile) {
-    case 0: return launch_variant<T, NF, 64, 4>(variant, a, nb, s);
-    case 1: return launch_variant<T, NF, 64, 8>(variant, a, nb, s);
-    case 2: return launch_variant<T, NF, 32, 8>(variant, a, nb, s);
-    case 3: return launch_variant<T, NF, 16, 16>(variant, a, nb, s);
-    case 4: return launch_variant<T, NF, 8, 8>(variant, a, nb, s);
-    }
-    return hipErrorInvalidValue;
-}
-
 // Which arrays a variant reads with a halo (must not be written in place) and writes.
 struct VariantIO {
     bool wphi, wpi, pi_halo;
@@ -1097,35 +958,6 @@ lat_status step_lf_self(lat_ctx *c, int64_t ns, int dir)
 // block and its advanced planes the LDS a block may use.  Default S = 4,
 // ZS = 1, YB = 4 (at 32^3: 256 blocks of 12 x 32 threads); LATTICE_SLAB=
 // "S,ZS[,YB]" overrides, "0" turns it off.
-template <typename T, int NF, int S, int ZS>
-void slab_kernel_of(const void **fn, size_t *lds, int N, int yb)
-{
-    *fn = (const void *)lf_slab<T, NF, S, ZS>;
-    *lds = slab_lds<T, NF, S, ZS>(N, yb);
-}
-
-template <typename T, int NF, int S>
-bool slab_pick_zs(int zs, const void **fn, size_t *lds, int N, int yb)
-{
-    switch (zs) {
-    case 1: slab_kernel_of<T, NF, S, 1>(fn, lds, N, yb); return true;
-    case 2: slab_kernel_of<T, NF, S, 2>(fn, lds, N, yb); return true;
-    default: return false;
-    }
-}
-
-template <typename T, int NF>
-bool slab_pick(int S, int zs, const void **fn, size_t *lds, int N, int yb)
-{
-    switch (S) {
-    case 2: return slab_pick_zs<T, NF, 2>(zs, fn, lds, N, yb);
-    case 3: return slab_pick_zs<T, NF, 3>(zs, fn, lds, N, yb);
-    case 4: return slab_pick_zs<T, NF, 4>(zs, fn, lds, N, yb);
-    case 5: return slab_pick_zs<T, NF, 5>(zs, fn, lds, N, yb);
-    default: return false;
-    }
-}
-
 bool slab_kernel(const lat_ctx *c, int S, int zs, int yb, const void **fn, size_t *lds)
 {
     if (c->f32)

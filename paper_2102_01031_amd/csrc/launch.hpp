@@ -1,0 +1,40 @@
+// launch.hpp -- kernel launchers of the real scalar passes, each compiled in a
+// translation unit of its own (tile_kernels.hip, rows_kernels_f64.hip,
+// rows_kernels_f32.hip, slab_kernels.hip), so that the instantiations build in
+// parallel.
+#pragma once
+#include "common.hpp"
+#include "stage_scalar.hpp"
+
+namespace lat {
+
+struct TileCfg {
+    int tx, ty;
+};
+constexpr TileCfg kTiles[] = {{64, 4}, {64, 8}, {32, 8}, {16, 16}, {8, 8}};
+constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+
+enum Variant : int {
+    kKickOnly = 0,     // no drift, kick, momenta in place (VV first point, LF sync)
+    kKickOnlyRed = 1,  // same + reductions (self-consistent first point)
+    kDriftKick = 2,    // drift on load, kick (VV inner and last points)
+    kDriftKickRed = 3, // same + reductions (self-consistent)
+    kKickDrift = 4,    // kick, drift at end (leapfrog)
+    kEnergy = 5        // kick on a copy + reductions, writes nothing
+};
+
+// one pass of the tiled kernel (any N) with tile shape kTiles[tile]
+template <typename T, int NF>
+hipError_t launch_tile(int tile, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s);
+
+// one pass of the whole-row kernel (N = 64, 128, 256); see rows_launch.hpp
+template <typename T, int NF>
+hipError_t launch_rows(int N, int ty, int pf, int vw, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s,
+                       int lp = 0);
+
+// the lf_slab instance for S steps per launch and ZS planes per block, and its
+// dynamic LDS for yb rows per block; false if that shape is not compiled
+template <typename T, int NF>
+bool slab_pick(int S, int zs, const void **fn, size_t *lds, int N, int yb);
+
+}  // namespace lat

@@ -293,7 +293,7 @@ __global__ void __launch_bounds__(NT) self_finish(const double *partials, int nb
 }
 
 // copy of a record (one thread)
-__global__ void record_copy(const ScaleRecord *src, ScaleRecord *dst)
+static __global__ void record_copy(const ScaleRecord *src, ScaleRecord *dst)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
 }
@@ -542,7 +542,7 @@ __global__ void __launch_bounds__(TX *TY) scalar_stage(const ScalarArgs<T> g)
 
 // Kick coefficients of the first pass of a self-consistent call from the
 // current scale factor (no drift precedes it).
-__global__ void self_prologue(PassCoef *c0, const ScaleRecord *S, double alpha)
+static __global__ void self_prologue(PassCoef *c0, const ScaleRecord *S, double alpha)
 {
     if (threadIdx.x == 0) {
         const double a = S->a;
