@@ -140,6 +140,8 @@ struct lat_ctx {
     int rows_lp = 0;          // whole-row kernel store policy (see launch_rows)
     int rows_split = 6;       // store policy 1: eighths of the march with non-temporal stores
     int rows_zpair = 0;       // whole-row kernel: odd z chunks march the other way
+    bool plane = false;       // plane-run kernel (stage_plane.hpp): tiles_x runs of tiles_y sites per plane
+    PlaneCfg plane_cfg{};
     int zc = 0;
     int tiles_x = 0, tiles_y = 0, chunks_z = 0, nblocks = 0;
     // launch statistics and optional event timing
@@ -272,10 +274,16 @@ int auto_chunk(int N, long xy_blocks, long target)
     return (int)z;
 }
 
+// threads per block of the stage passes
+int stage_threads(const lat_ctx *c)
+{
+    return c->rows ? 64 * c->rows_ty : (c->plane ? c->plane_cfg.nt : kTiles[c->tile].tx * kTiles[c->tile].ty);
+}
+
 void set_geometry(lat_ctx *c, int tile, int zc)
 {
     const int N = c->N;
-    c->rows = false;
+    c->rows = c->plane = false;
     c->tile = tile;
     c->tiles_x = (N + kTiles[tile].tx - 1) / kTiles[tile].tx;
     c->tiles_y = (N + kTiles[tile].ty - 1) / kTiles[tile].ty;
@@ -298,6 +306,64 @@ void set_rows_geometry(lat_ctx *c, int ty, int zc)
     c->zc = zc;
     c->chunks_z = (N + zc - 1) / zc;
     c->nblocks = c->tiles_y * c->chunks_z;
+}
+
+// Plane-run kernel: the plane cut into `runs` equal runs of at most nt xs sites.
+void set_plane_geometry(lat_ctx *c, const PlaneCfg &cfg, int runs, int zc)
+{
+    const int N = c->N, NN = N * N;
+    c->rows = false;
+    c->plane = true;
+    c->plane_cfg = cfg;
+    runs = std::max(runs, (NN + cfg.nt * cfg.xs - 1) / (cfg.nt * cfg.xs));
+    c->tiles_y = (NN + runs - 1) / runs;
+    c->tiles_x = (NN + c->tiles_y - 1) / c->tiles_y;
+    c->zc = std::min(std::max(zc, 1), N);
+    c->chunks_z = (N + c->zc - 1) / c->zc;
+    c->nblocks = c->tiles_x * c->chunks_z;
+}
+
+// The plane-run kernel runs every N up to 1024 without a whole-row kernel of its
+// own (N = 64, 128, 256).  Shape: 512 threads (256 up to N = 64, where a plane is
+// at most eight wavefronts of sites); four sites per thread where the registers
+// allow it without spilling (float32, and one float64 field beyond N = 256, where
+// the longer run halves the share of halo sites: 349 against 373 us at 384^3),
+// else two (two float64 fields at four sites spill 312 bytes per lane: 958
+// against 519 us at 320^3).  Runs and z chunks: of all cuts of the lattice, the
+// one with the least rounds * (planes + 3 of a block's start-up) * (run + N of
+// its halo), where `slots` blocks run at once (one block of 512 threads per CU;
+// two of one float64 field with two sites per thread), plus a term per block for
+// the sums every block adds up in its prologue.  A grid just above a multiple of
+// `slots` costs a whole round: 200^3, two float64 fields, 161 us in 560 blocks,
+// 128.5 in 252.  LATTICE_TILE="plane[,zc[,runs]]" overrides the cut.
+bool plane_geometry(lat_ctx *c, const char *spec)
+{
+    const int N = c->N, NN = N * N;
+    if (N > 1024) return false;
+    PlaneCfg cfg{512, 2, N > 512 ? 4 : (N > 256 ? 2 : 1), 1};
+    if (N <= 64) cfg.nt = 256;
+    else if (c->f32 || (c->nf == 1 && N > 256)) cfg.xs = 4;
+    int zc = 0, runs = 0;
+    if (spec) std::sscanf(spec, ",%d,%d", &zc, &runs);
+    const int rmin = (NN + cfg.nt * cfg.xs - 1) / (cfg.nt * cfg.xs);
+    if (zc <= 0) {
+        const int slots = (!c->f32 && c->nf == 1 && cfg.nt == 512 && cfg.xs == 2) ? 512 : 256;
+        double best = 0.0;
+        for (int z = 1; z <= N; ++z) {
+            const int chunks = (N + z - 1) / z;
+            for (int r : {rmin, std::max(rmin, slots / chunks)}) {
+                const long nb = (long)r * chunks, rounds = (nb + slots - 1) / slots;
+                const double cost = (double)rounds * (z + 3) * ((NN + r - 1) / r + N) + 30.0 * nb;
+                if (best == 0.0 || cost < best) {
+                    best = cost;
+                    zc = z;
+                    runs = r;
+                }
+            }
+        }
+    }
+    set_plane_geometry(c, cfg, std::min(runs, NN), zc);
+    return true;
 }
 
 // Energy pass geometry of the whole-row kernel.  Read-only, the pass needs
@@ -379,6 +445,7 @@ void geometry_from_env(lat_ctx *c)
         set_rows_geometry(c, ty, z);
         return;
     }
+    if (s && std::strncmp(s, "plane", 5) == 0 && plane_geometry(c, s + 5)) return;
     int tile = pick_tile(c->N), zc = 0;
     if (s) {
         int tx = 0, ty = 0, z = 0;
@@ -398,6 +465,7 @@ void geometry_from_env(lat_ctx *c)
         set_rows_geometry(c, (c->f32 && c->N != 256) ? 8 : 4, 0);
         return;
     }
+    if (plane_geometry(c, nullptr)) return;
     set_geometry(c, tile, zc);
 }
 
@@ -639,12 +707,15 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
     if (c->rows)
         e = c->nf == 1 ? launch_rows<T, 1>(c->N, ty, pf, c->rows_vw, variant, a, nb, stream, lp)
                        : launch_rows<T, 2>(c->N, ty, pf, c->rows_vw, variant, a, nb, stream, lp);
+    else if (c->plane)
+        e = c->nf == 1 ? launch_plane<T, 1>(c->plane_cfg, variant, a, nb, stream)
+                       : launch_plane<T, 2>(c->plane_cfg, variant, a, nb, stream);
     else
         e = c->nf == 1 ? launch_tile<T, 1>(c->tile, variant, a, c->nblocks, stream)
                        : launch_tile<T, 2>(c->tile, variant, a, c->nblocks, stream);
     if (e != hipSuccess) return fail(c, LAT_EHIP, std::string("stage launch: ") + hipGetErrorString(e));
     if (lk && lk->defer && lk->store_to) {
-        const int NT = c->rows ? 64 * ty : kTiles[c->tile].tx * kTiles[c->tile].ty;
+        const int NT = c->rows ? 64 * ty : stage_threads(c);
         e = launch_sums_finish(NT, c->nf, lk->partials, c->rows ? nb : c->nblocks, lk->store_to, stream);
         if (e != hipSuccess) return fail(c, LAT_EHIP, std::string("sums launch: ") + hipGetErrorString(e));
     }
@@ -695,7 +766,7 @@ lat_status finish_chain(lat_ctx *c, int64_t M, int mode, hipStream_t st)
     double *buf[2] = {c->partials, c->partials + (size_t)c->nblocks * 8};
     const ScaleRecord *in = M == 0 ? c->sc : c->sc + 1 + ((M - 1) & 1);
     const double iv = 1.0 / (double)c->vol, idx2 = 1.0 / (c->p.dx * c->p.dx);
-    const int NT = c->rows ? 64 * c->rows_ty : kTiles[c->tile].tx * kTiles[c->tile].ty;
+    const int NT = stage_threads(c);
     const double *P = buf[M & 1];
     PassCoef *Nx = c->coef + M + 1;
     if (NT == 64) {
@@ -1792,19 +1863,18 @@ lat_status lattice_energy_noalloc(const lat_params *p, const lat_fields *f, doub
         A.inv_vol = 1.0 / (double)g.vol;
         return A;
     };
-    if (g.f32) {
-        const ScalarArgs<float> A = args((float *)nullptr);
-        e = g.rows ? (g.nf == 1 ? launch_rows<float, 1>(g.N, g.rows_ty, g.rows_pf, g.rows_vw, kEnergy, A, g.nblocks, st)
-                                : launch_rows<float, 2>(g.N, g.rows_ty, g.rows_pf, g.rows_vw, kEnergy, A, g.nblocks, st))
-                   : (g.nf == 1 ? launch_tile<float, 1>(g.tile, kEnergy, A, g.nblocks, st)
-                                : launch_tile<float, 2>(g.tile, kEnergy, A, g.nblocks, st));
-    } else {
-        const ScalarArgs<double> A = args((double *)nullptr);
-        e = g.rows ? (g.nf == 1 ? launch_rows<double, 1>(g.N, g.rows_ty, g.rows_pf, g.rows_vw, kEnergy, A, g.nblocks, st)
-                                : launch_rows<double, 2>(g.N, g.rows_ty, g.rows_pf, g.rows_vw, kEnergy, A, g.nblocks, st))
-                   : (g.nf == 1 ? launch_tile<double, 1>(g.tile, kEnergy, A, g.nblocks, st)
-                                : launch_tile<double, 2>(g.tile, kEnergy, A, g.nblocks, st));
-    }
+    auto pass = [&](auto *tag, auto nfc) {
+        using T = std::remove_pointer_t<decltype(tag)>;
+        constexpr int NF = decltype(nfc)::value;
+        const ScalarArgs<T> A = args(tag);
+        if (g.rows) return launch_rows<T, NF>(g.N, g.rows_ty, g.rows_pf, g.rows_vw, kEnergy, A, g.nblocks, st);
+        if (g.plane) return launch_plane<T, NF>(g.plane_cfg, kEnergy, A, g.nblocks, st);
+        return launch_tile<T, NF>(g.tile, kEnergy, A, g.nblocks, st);
+    };
+    const std::integral_constant<int, 1> one{};
+    const std::integral_constant<int, 2> two{};
+    if (g.f32) e = g.nf == 1 ? pass((float *)nullptr, one) : pass((float *)nullptr, two);
+    else e = g.nf == 1 ? pass((double *)nullptr, one) : pass((double *)nullptr, two);
     if (e != hipSuccess) return fail(nullptr, LAT_EHIP, std::string("energy pass: ") + hipGetErrorString(e));
     hipLaunchKernelGGL(na_finish, dim3(1), dim3(64), 0, st, rec, out, g.nf, 1.0 / (double)g.vol,
                        1.0 / (p->dx * p->dx), a);
@@ -2080,9 +2150,9 @@ lat_status lattice_stats(lat_ctx *c, int reset, lat_stats *out)
         out->kernel_ms[i] = c->kernel_ms[i];
     }
     out->blocks = c->nblocks;
-    out->threads = c->rows ? 64 * c->rows_ty : kTiles[c->tile].tx * kTiles[c->tile].ty;
-    out->tile_x = c->rows ? c->N : kTiles[c->tile].tx;
-    out->tile_y = c->rows ? c->rows_ty : kTiles[c->tile].ty;
+    out->threads = stage_threads(c);
+    out->tile_x = c->rows ? c->N : (c->plane ? c->tiles_y : kTiles[c->tile].tx);
+    out->tile_y = c->rows ? c->rows_ty : (c->plane ? 1 : kTiles[c->tile].ty);
     out->z_chunk = c->zc;
     if (reset) {
         std::memset(c->launches, 0, sizeof(c->launches));

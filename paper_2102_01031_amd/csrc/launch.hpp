@@ -1,6 +1,6 @@
 // launch.hpp -- kernel launchers of the real scalar passes, each compiled in a
-// translation unit of its own (tile_kernels.hip, rows_kernels_f64.hip,
-// rows_kernels_f32.hip, slab_kernels.hip), so that the instantiations build in
+// translation unit of its own (tile_kernels.hip, rows_kernels_*.hip,
+// plane_kernels_*.hip, slab_kernels.hip), so that the instantiations build in
 // parallel.
 #pragma once
 #include "common.hpp"
@@ -31,6 +31,15 @@ hipError_t launch_tile(int tile, int variant, const ScalarArgs<T> &a, int nb, hi
 template <typename T, int NF>
 hipError_t launch_rows(int N, int ty, int pf, int vw, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s,
                        int lp = 0);
+
+// Launch shape of the plane-run kernel (stage_plane.hpp): threads per block,
+// sites and halo sites per thread, prefetch depth.
+struct PlaneCfg {
+    int nt, xs, hpt, pf;
+};
+// one pass of the plane-run kernel (any N with 2 N <= hpt nt)
+template <typename T, int NF>
+hipError_t launch_plane(const PlaneCfg &c, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s);
 
 // the lf_slab instance for S steps per launch and ZS planes per block, and its
 // dynamic LDS for yb rows per block; false if that shape is not compiled

@@ -433,44 +433,7 @@ __global__ void __launch_bounds__(64 * TY) scalar_rows(const ScalarArgs<T> g)
         }
     }
 
-    if constexpr (RED) {
-        double tot[NQ];
-        block_sums<NT, NQ>(acc, lds_red, tot);
-        if (g.defer) {
-            if (tid == 0) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) g.partials[(size_t)lid * NQ + k] = tot[k];
-            }
-            return;
-        }
-        if (tid == 0) {
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) store_agent(&g.partials[(size_t)lid * NQ + k], tot[k]);
-            last_flag = ticket_arrive(g.ticket, gridDim.x) ? 1 : 0;
-        }
-        __syncthreads();
-        if (last_flag) {
-            const int nb = gridDim.x;
-            double part[NQ];
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) part[k] = 0.0;
-            for (int i = tid; i < nb; i += NT) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) part[k] += load_agent(&g.partials[(size_t)i * NQ + k]);
-            }
-            double fin[NQ];
-            block_sums<NT, NQ>(part, lds_red, fin);
-            if (tid == 0) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) g.sc->sums[k] = fin[k];
-                if (g.last_mode == kLastSelf)
-                    self_update<NF>(C, fin, g.sc, g.coef_next, g.alpha, g.kappa2, g.inv_vol, g.inv_dx2);
-                else if (g.last_mode == kLastSelfLF)
-                    self_update_lf<NF>(C, fin, g.sc, g.coef_next, g.alpha, g.kappa2, g.inv_vol, g.inv_dx2);
-                __hip_atomic_store(g.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
+    if constexpr (RED) reduce_tail<NT, NF>(g, C, acc, lds_red, &last_flag, lid);
 }
 
 }  // namespace lat

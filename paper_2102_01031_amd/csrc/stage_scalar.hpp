@@ -298,6 +298,53 @@ static __global__ void record_copy(const ScaleRecord *src, ScaleRecord *dst)
     if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
 }
 
+// The end of a reducing pass: the block's sums to its partials, and, unless the
+// pass defers them, the last block's sum of all partials in block order with
+// the scale-factor update of g.last_mode.
+template <int NT, int NF, typename T>
+__device__ inline void reduce_tail(const ScalarArgs<T> &g, const PassCoef &C, double (&acc)[3 * NF], double *lds_red,
+                                   int *last_flag, int lid)
+{
+    constexpr int NQ = 3 * NF;
+    const int tid = threadIdx.x;
+    double tot[NQ];
+    block_sums<NT, NQ>(acc, lds_red, tot);
+    if (g.defer) {
+        if (tid == 0) {
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) g.partials[(size_t)lid * NQ + k] = tot[k];
+        }
+        return;
+    }
+    if (tid == 0) {
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) store_agent(&g.partials[(size_t)lid * NQ + k], tot[k]);
+        *last_flag = ticket_arrive(g.ticket, gridDim.x) ? 1 : 0;
+    }
+    __syncthreads();
+    if (*last_flag) {
+        const int nb = gridDim.x;
+        double part[NQ];
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) part[k] = 0.0;
+        for (int i = tid; i < nb; i += NT) {
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) part[k] += load_agent(&g.partials[(size_t)i * NQ + k]);
+        }
+        double fin[NQ];
+        block_sums<NT, NQ>(part, lds_red, fin);
+        if (tid == 0) {
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) g.sc->sums[k] = fin[k];
+            if (g.last_mode == kLastSelf)
+                self_update<NF>(C, fin, g.sc, g.coef_next, g.alpha, g.kappa2, g.inv_vol, g.inv_dx2);
+            else if (g.last_mode == kLastSelfLF)
+                self_update_lf<NF>(C, fin, g.sc, g.coef_next, g.alpha, g.kappa2, g.inv_vol, g.inv_dx2);
+            __hip_atomic_store(g.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 template <typename T, int NF, int TX, int TY, bool DLOAD, bool DEND, bool RED, bool WPHI, bool WPI>
 __global__ void __launch_bounds__(TX *TY) scalar_stage(const ScalarArgs<T> g)
 {
@@ -500,44 +547,7 @@ __global__ void __launch_bounds__(TX *TY) scalar_stage(const ScalarArgs<T> g)
         if (z + 1 < z1) plane(z + 1, ownB_f, ownB_p, haloB_f, haloB_p, ownA_f, ownA_p, haloA_f, haloA_p);
     }
 
-    if constexpr (RED) {
-        double tot[NQ];
-        block_sums<NT, NQ>(acc, lds_red, tot);
-        if (g.defer) {
-            if (tid == 0) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) g.partials[(size_t)lid * NQ + k] = tot[k];
-            }
-            return;
-        }
-        if (tid == 0) {
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) store_agent(&g.partials[(size_t)lid * NQ + k], tot[k]);
-            last_flag = ticket_arrive(g.ticket, gridDim.x) ? 1 : 0;
-        }
-        __syncthreads();
-        if (last_flag) {
-            const int nb = gridDim.x;
-            double part[NQ];
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) part[k] = 0.0;
-            for (int i = tid; i < nb; i += NT) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) part[k] += load_agent(&g.partials[(size_t)i * NQ + k]);
-            }
-            double fin[NQ];
-            block_sums<NT, NQ>(part, lds_red, fin);
-            if (tid == 0) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) g.sc->sums[k] = fin[k];
-                if (g.last_mode == kLastSelf)
-                    self_update<NF>(C, fin, g.sc, g.coef_next, g.alpha, g.kappa2, g.inv_vol, g.inv_dx2);
-                else if (g.last_mode == kLastSelfLF)
-                    self_update_lf<NF>(C, fin, g.sc, g.coef_next, g.alpha, g.kappa2, g.inv_vol, g.inv_dx2);
-                __hip_atomic_store(g.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
+    if constexpr (RED) reduce_tail<NT, NF>(g, C, acc, lds_red, &last_flag, lid);
 }
 
 // Kick coefficients of the first pass of a self-consistent call from the
