@@ -393,8 +393,9 @@ typedef struct lat_grad_out {
 lat_status lattice_grad(lat_ctx *ctx, const lat_grad_spec *spec, lat_grad_out *out);
 
 /* Launch statistics of the stencil kernels, per kernel kind:
- *   0 kick only, 1 kick only + reductions, 2 drift on load + kick,
- *   3 drift on load + kick + reductions, 4 kick + drift at end (leapfrog),
+ *   0 kick only, 1 kick only + reductions, 2 drift only (the end of a
+ *   self-consistent leapfrog call), 3 drift on load + kick + reductions,
+ *   4 kick + drift at end (leapfrog; velocity-Verlet without self-consistent expansion),
  *   5 energy (read only), 6 U(1) or SU(2) leapfrog (and their energy passes), 7 adjoint reverse pass.
  * kernel_ms is accumulated from HIP events recorded on the context stream around
  * each launch while profiling is on (lattice_profile); it stays 0 otherwise. */

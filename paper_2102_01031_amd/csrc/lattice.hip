@@ -3,10 +3,11 @@
 // The runtime turns a call lattice_step(n) into a schedule of stencil passes
 // (one pass per kick point) and launches them on the context stream:
 //   leapfrog   pass k: kick (half after a sync, else full) then local drift
-//   VV2 / VV4  kick points p = 0..M of the sub-step sequence (M = n or 3n);
-//              pass p: drift that ends at p (on load), kick h_{p-1}/2, sample
-//              energies, kick h_p/2.  The two half kicks that meet at an inner
-//              point share one force evaluation.
+//   VV family  kick points p = 0..M of the sub-step sequence (M sub-steps);
+//              self-consistent: pass p: drift that ends at p (on load), kick
+//              h_{p-1}/2, sample energies, kick h_p/2; known background: the same
+//              kicks, then the drift that leaves p at the pass's end.  The two half
+//              kicks that meet at an inner point share one force evaluation.
 // For a fixed or absent background every coefficient is known beforehand and
 // uploaded as a table; for self-consistent expansion the pass that samples the
 // energies at point p also advances (a, b) and writes the next pass's drift and
@@ -472,7 +473,11 @@ void geometry_from_env(lat_ctx *c)
 // ---------------------------------------------------------------------------
 // kernel dispatch
 // ---------------------------------------------------------------------------
-// Which arrays a variant reads with a halo (must not be written in place) and writes.
+// the launch-statistics kind a variant counts under
+int variant_kind(int v) { return v == kKickCopy ? kKickOnly : (v == kKickCopyRed ? kKickOnlyRed : v); }
+
+// Which arrays a variant writes, and whether pi goes to the other buffer
+// (read with a halo, or carried over) instead of in place.
 struct VariantIO {
     bool wphi, wpi, pi_halo;
 };
@@ -481,9 +486,10 @@ VariantIO variant_io(int v)
     switch (v) {
     case kKickOnly:
     case kKickOnlyRed: return {false, true, false};
-    case kDriftKick:
-    case kDriftKickRed: return {true, true, true};
-    case kKickDrift: return {true, true, false};
+    case kDriftKickRed:
+    case kKickCopyRed: return {true, true, true};
+    case kKickDrift:
+    case kKickCopy: return {true, true, false};
     default: return {false, false, false};
     }
 }
@@ -720,10 +726,10 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
         if (e != hipSuccess) return fail(c, LAT_EHIP, std::string("sums launch: ") + hipGetErrorString(e));
     }
     if (c->profiling) {
-        lat_status st = timing_end(c, ev0, ev1, variant);
+        lat_status st = timing_end(c, ev0, ev1, variant_kind(variant));
         if (st != LAT_OK) return st;
     }
-    c->launches[variant] += 1;
+    c->launches[variant_kind(variant)] += 1;
     for (int f = 0; f < c->nf; ++f) {
         if (io.wphi) c->cur_phi[f] ^= 1;
         if (io.wpi && io.pi_halo) c->cur_pi[f] ^= 1;
@@ -938,43 +944,96 @@ lat_status upload_coef(lat_ctx *c, size_t n)
 // copy shadow buffers back so the caller's arrays hold the state
 lat_status settle(lat_ctx *c)
 {
-    const size_t bytes = c->vol * c->esize;
+    CopySet cs{};
+    auto back = [&](void *const (&buf)[2], int &cur) {
+        if (!cur) return;
+        cs.src[cs.n] = (const unsigned *)buf[1];
+        cs.dst[cs.n] = (unsigned *)buf[0];
+        ++cs.n;
+        cur = 0;
+    };
     for (int f = 0; f < c->nf; ++f) {
-        if (c->cur_phi[f]) {
-            HIPCHK(c, hipMemcpyAsync(c->phi[f][0], c->phi[f][1], bytes, hipMemcpyDeviceToDevice, c->stream));
-            c->cur_phi[f] = 0;
-        }
-        if (c->cur_pi[f]) {
-            HIPCHK(c, hipMemcpyAsync(c->pi[f][0], c->pi[f][1], bytes, hipMemcpyDeviceToDevice, c->stream));
-            c->cur_pi[f] = 0;
-        }
+        back(c->phi[f], c->cur_phi[f]);
+        back(c->pi[f], c->cur_pi[f]);
     }
-    for (int i = 0; i < 3; ++i) {
-        if (c->cur_A[i]) {
-            HIPCHK(c, hipMemcpyAsync(c->A[i][0], c->A[i][1], bytes, hipMemcpyDeviceToDevice, c->stream));
-            c->cur_A[i] = 0;
-        }
-    }
+    for (int i = 0; i < 3; ++i) back(c->A[i], c->cur_A[i]);
     if (c->cur_su2) {
-        for (int k = 0; k < 4; ++k)
-            HIPCHK(c, hipMemcpyAsync(c->dbl[k][0], c->dbl[k][1], bytes, hipMemcpyDeviceToDevice, c->stream));
-        for (int k = 0; k < 12; ++k)
-            HIPCHK(c, hipMemcpyAsync(c->lnk[k][0], c->lnk[k][1], bytes, hipMemcpyDeviceToDevice, c->stream));
+        int one;
+        for (int k = 0; k < 4; ++k) back(c->dbl[k], one = 1);
+        for (int k = 0; k < 12; ++k) back(c->lnk[k], one = 1);
         c->cur_su2 = 0;
     }
+    if (cs.n == 0) return LAT_OK;
+    // one launch for all of them: each copy of its own costs a launch gap, more
+    // than the copy itself on small lattices (two arrays of 32^3: 6 us)
+    const size_t words = c->vol * c->esize / 4;
+    const unsigned nb = (unsigned)std::min<size_t>((words / 4 + 255) / 256 + 1, 2048);
+    hipLaunchKernelGGL(copy_arrays, dim3(nb, cs.n), dim3(256), 0, c->stream, cs, words);
+    HIPCHK(c, hipGetLastError());
     return LAT_OK;
 }
 
 // ---------------------------------------------------------------------------
 // scalar schedules
 // ---------------------------------------------------------------------------
+// the drift that closes a self-consistent leapfrog call, on the current buffers
+template <typename T>
+lat_status run_drift(lat_ctx *c, int pass_index, hipStream_t st, const PassLink &lk)
+{
+    ScalarArgs<T> a{};
+    for (int f = 0; f < c->nf; ++f) {
+        a.phi_in[f] = a.phi_out[f] = (T *)c->phi[f][c->cur_phi[f]];
+        a.pi_in[f] = (const T *)c->pi[f][c->cur_pi[f]];
+    }
+    a.N = c->N;
+    a.inv_dx2 = 1.0 / (c->p.dx * c->p.dx);
+    a.coef = c->coef + pass_index;
+    a.alpha = c->p.alpha;
+    a.kappa2 = c->p.kappa2;
+    a.inv_vol = 1.0 / (double)c->vol;
+    a.fin = lk.fin;
+    a.fin_nb = c->nblocks;
+    a.fin_mode = lk.fin_mode;
+    a.fin_coef = lk.fin_coef;
+    a.fin_in = lk.fin_in;
+    a.fin_out = lk.fin_out;
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    if (c->profiling) {
+        lat_status s = timing_begin(c, &ev0, &ev1);
+        if (s != LAT_OK) return s;
+    }
+    // threads as the stage passes', so the sums are added in their order
+    const int NT = stage_threads(c);
+    const dim3 grid((unsigned)std::min<size_t>((c->vol + NT - 1) / NT, 1024)), blk(NT);
+    auto go = [&](auto nt) {
+        constexpr int K = decltype(nt)::value;
+        if (c->nf == 1) hipLaunchKernelGGL((scalar_drift<T, 1, K>), grid, blk, 0, st, a, c->vol);
+        else hipLaunchKernelGGL((scalar_drift<T, 2, K>), grid, blk, 0, st, a, c->vol);
+        return hipGetLastError();
+    };
+    if (NT == 64) HIPCHK(c, go(std::integral_constant<int, 64>{}));
+    else if (NT == 256) HIPCHK(c, go(std::integral_constant<int, 256>{}));
+    else if (NT == 512) HIPCHK(c, go(std::integral_constant<int, 512>{}));
+    else return fail(c, LAT_EHIP, "unexpected block size for the drift");
+    if (c->profiling) {
+        lat_status s = timing_end(c, ev0, ev1, 2);
+        if (s != LAT_OK) return s;
+    }
+    c->launches[2] += 1;
+    return LAT_OK;
+}
+
 // Leapfrog with self-consistent expansion (reading A3): the drift after each
 // kick needs b after that kick, which needs the kicked momenta's volume sum, so
 // the drift moves into the next pass (drift on load) and the call ends with a
 // drift-only pass.  Pass k < ns kicks pi by c1 (h/2 for the first kick from
 // synchronised momenta, else h) and reduces the kicked momenta squared, E_G and
-// E_V; its last block kicks b and drifts a (self_update_lf) and writes the next
-// pass's drift and kick factors.  Pass ns drifts phi only.
+// E_V; the next pass kicks b and drifts a (self_update_lf) in its prologue.  The
+// last launch drifts phi in place (scalar_drift).  The ns - 1 drift-and-kick
+// passes write to the other buffers; where their number is odd, the first pass
+// writes its state there too, so that the call ends in the caller's arrays
+// (one more array of traffic per field than the plain first pass, against four
+// to copy phi and pi back).
 lat_status step_lf_self(lat_ctx *c, int64_t ns, int dir)
 {
     const double h = dir * c->p.dt;
@@ -1003,16 +1062,19 @@ lat_status step_lf_self(lat_ctx *c, int64_t ns, int dir)
     s = launch_passes(c, dir * ns, ns + 1, [&](hipStream_t st) {
         hipLaunchKernelGGL(self_prologue, dim3(1), dim3(64), 0, st, c->coef, c->sc, al);
         HIPCHK(c, hipGetLastError());
-        for (int64_t k = 0; k <= ns; ++k) {
-            const int v = k == ns ? kDriftKick : (k == 0 ? kKickOnlyRed : kDriftKickRed);
-            // the drift-only pass finalises the last kick's sums and reduces nothing
-            const PassLink lk = pass_link(c, k, kLastSelfLF, k < ns);
-            lat_status r = run_pass(c, v, (int)k, k == ns ? kLastStore : kLastSelfLF, st, &lk);
+        for (int64_t k = 0; k < ns; ++k) {
+            const int v = k > 0 ? kDriftKickRed : (ns % 2 == 0 ? kKickCopyRed : kKickOnlyRed);
+            const PassLink lk = pass_link(c, k, kLastSelfLF, true);
+            lat_status r = run_pass(c, v, (int)k, kLastSelfLF, st, &lk);
             if (r != LAT_OK) return r;
         }
-        // the record the drift-only pass wrote is the context's
-        hipLaunchKernelGGL(record_copy, dim3(1), dim3(64), 0, st, (const ScaleRecord *)(c->sc + 1 + ((ns - 1) & 1)),
-                           c->sc);
+        // the drift finalises the last kick's sums; its record is the context's
+        // (written there directly unless the other blocks still read it, ns = 1)
+        PassLink lk = pass_link(c, ns, kLastSelfLF, false);
+        if (ns > 1) lk.fin_out = c->sc;
+        lat_status r = c->f32 ? run_drift<float>(c, (int)ns, st, lk) : run_drift<double>(c, (int)ns, st, lk);
+        if (r != LAT_OK || ns > 1) return r;
+        hipLaunchKernelGGL(record_copy, dim3(1), dim3(64), 0, st, (const ScaleRecord *)lk.fin_out, c->sc);
         HIPCHK(c, hipGetLastError());
         return LAT_OK;
     });
@@ -1204,6 +1266,15 @@ std::vector<double> vv_weights(int integrator)
     }
 }
 
+// Velocity-Verlet calls.  Self-consistent expansion: pass p drifts on load to
+// kick point p, kicks and reduces (the drift needs the sums before it); phi and
+// pi go to the other buffers.  On a known background (fixed or none): pass p < M
+// kicks at point p and drifts at its end, so pi needs no neighbours and stays in
+// place, and a closing pass kicks.  The M passes that write to the other buffer
+// end in the caller's arrays if M is even; if M is odd the first (self) or the
+// closing (known background) pass carries the state across: one more array of
+// traffic per field, against copying phi (and, self, pi) back after the call
+// (256^3, two float64 fields, VV4, five steps: 230 us of 3.4 ms).
 lat_status step_vv(lat_ctx *c, int64_t ns, int dir)
 {
     const double h = dir * c->p.dt;
@@ -1241,7 +1312,7 @@ lat_status step_vv(lat_ctx *c, int64_t ns, int dir)
             const double a = scale_at(c, P.t);
             P.ka1 = std::pow(a, 1.0 + al);
             P.ka3 = std::pow(a, 3.0 + al);
-            P.dload = p > 0 ? hp * std::pow(scale_at(c, ts(p - 1) + 0.5 * hp), al - 3.0) : 0.0;
+            P.dend = p < M ? hn * std::pow(scale_at(c, ts(p) + 0.5 * hn), al - 3.0) : 0.0;
         }
     }
     if ((s = upload_coef(c, (size_t)M + 2)) != LAT_OK) return s;
@@ -1252,7 +1323,9 @@ lat_status step_vv(lat_ctx *c, int64_t ns, int dir)
             HIPCHK(c, hipGetLastError());
         }
         for (int64_t p = 0; p <= M; ++p) {
-            const int v = p == 0 ? (self ? kKickOnlyRed : kKickOnly) : (self ? kDriftKickRed : kDriftKick);
+            const bool odd = M % 2 != 0;
+            const int v = self ? (p > 0 ? kDriftKickRed : (odd ? kKickCopyRed : kKickOnlyRed))
+                               : (p < M ? kKickDrift : (odd ? kKickCopy : kKickOnly));
             const PassLink lk = self ? pass_link(c, p, kLastSelf, true) : PassLink{};
             lat_status r = run_pass(c, v, (int)p, mode, st, self ? &lk : nullptr);
             if (r != LAT_OK) return r;

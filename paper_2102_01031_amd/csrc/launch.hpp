@@ -17,10 +17,11 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 enum Variant : int {
     kKickOnly = 0,     // no drift, kick, momenta in place (VV first point, LF sync)
     kKickOnlyRed = 1,  // same + reductions (self-consistent first point)
-    kDriftKick = 2,    // drift on load, kick (VV inner and last points)
-    kDriftKickRed = 3, // same + reductions (self-consistent)
-    kKickDrift = 4,    // kick, drift at end (leapfrog)
-    kEnergy = 5        // kick on a copy + reductions, writes nothing
+    kDriftKickRed = 3, // drift on load, kick + reductions (self-consistent)
+    kKickDrift = 4,    // kick, drift at end (leapfrog; VV sub-steps on a known background)
+    kEnergy = 5,       // kick on a copy + reductions, writes nothing
+    kKickCopy = 6,     // kick only, phi carried to the other buffer (see step_vv)
+    kKickCopyRed = 7   // kick only + reductions, phi and pi written to the other buffers
 };
 
 // one pass of the tiled kernel (any N) with tile shape kTiles[tile]

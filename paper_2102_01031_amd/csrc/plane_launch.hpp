@@ -26,9 +26,10 @@ hipError_t launch_plane_variant(int variant, const ScalarArgs<T> &a, int nb, hip
     switch (variant) {
     case kKickOnly: return launch_plane_one<T, NF, NT, XS, HPT, false, false, false, false, true, PF>(a, nb, s);
     case kKickOnlyRed: return launch_plane_one<T, NF, NT, XS, HPT, false, false, true, false, true, PF>(a, nb, s);
-    case kDriftKick: return launch_plane_one<T, NF, NT, XS, HPT, true, false, false, true, true, PF>(a, nb, s);
     case kDriftKickRed: return launch_plane_one<T, NF, NT, XS, HPT, true, false, true, true, true, PF>(a, nb, s);
     case kKickDrift: return launch_plane_one<T, NF, NT, XS, HPT, false, true, false, true, true, PF>(a, nb, s);
+    case kKickCopy: return launch_plane_one<T, NF, NT, XS, HPT, false, false, false, true, true, PF>(a, nb, s);
+    case kKickCopyRed: return launch_plane_one<T, NF, NT, XS, HPT, false, false, true, true, true, PF>(a, nb, s);
     case kEnergy: return launch_plane_one<T, NF, NT, XS, HPT, false, false, true, false, false, PF>(a, nb, s);
     }
     return hipErrorInvalidValue;

@@ -17,14 +17,17 @@ hipError_t launch_rows_variant(int variant, const ScalarArgs<T> &a, int nb, hipS
     case kKickOnlyRed:
         hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, true, false, true, PF, VW, LP>), grid, block, 0, s, a);
         break;
-    case kDriftKick:
-        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, true, false, false, true, true, PF, VW, LP>), grid, block, 0, s, a);
-        break;
     case kDriftKickRed:
         hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, true, false, true, true, true, PF, VW, LP>), grid, block, 0, s, a);
         break;
     case kKickDrift:
         hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, true, false, true, true, PF, VW, LP>), grid, block, 0, s, a);
+        break;
+    case kKickCopy:
+        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, false, true, true, PF, VW, LP>), grid, block, 0, s, a);
+        break;
+    case kKickCopyRed:
+        hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, true, true, true, PF, VW, LP>), grid, block, 0, s, a);
         break;
     case kEnergy:
         hipLaunchKernelGGL((scalar_rows<T, NF, XS, TY, false, false, true, false, false, PF, VW, LP>), grid, block, 0, s, a);

@@ -292,6 +292,45 @@ __global__ void __launch_bounds__(NT) self_finish(const double *partials, int nb
     }
 }
 
+// The drift alone, in place: phi += dload pi with the coefficient the prologue
+// forms from the sums of the pass before (three arrays of traffic per field, no
+// neighbours; a stencil pass with zero kicks moves four).
+template <typename T, int NF, int NT>
+__global__ void __launch_bounds__(NT) scalar_drift(const ScalarArgs<T> g, size_t vol)
+{
+    __shared__ double lds_red[(NT / 64) * 3 * NF];
+    __shared__ double lds_coef[4];
+    PassCoef C = *g.coef;
+    finalise_prologue<NT, NF>(g, lds_red, lds_coef, C);
+    const T dl = (T)C.dload;
+    for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < vol; i += (size_t)gridDim.x * NT) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) g.phi_out[f][i] = g.phi_in[f][i] + dl * g.pi_in[f][i];
+    }
+}
+
+// Arrays copied back to the caller's buffers in one launch (settle).
+struct CopySet {
+    static constexpr int kMax = 16;
+    const unsigned *src[kMax];
+    unsigned *dst[kMax];
+    int n;
+};
+static __global__ void __launch_bounds__(256) copy_arrays(const CopySet s, size_t words)
+{
+    const unsigned *a = s.src[blockIdx.y];
+    unsigned *b = s.dst[blockIdx.y];
+    // 16-byte pieces where both pointers allow them, else 4-byte words
+    if ((((uintptr_t)a | (uintptr_t)b) & 15u) == 0) {
+        const size_t quads = words / 4;
+        for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < quads; i += (size_t)gridDim.x * 256)
+            ((uint4 *)b)[i] = ((const uint4 *)a)[i];
+        if (blockIdx.x == 0 && threadIdx.x < words % 4) b[4 * quads + threadIdx.x] = a[4 * quads + threadIdx.x];
+    } else {
+        for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) b[i] = a[i];
+    }
+}
+
 // copy of a record (one thread)
 static __global__ void record_copy(const ScaleRecord *src, ScaleRecord *dst)
 {

@@ -14,14 +14,17 @@ hipError_t launch_variant(int variant, const ScalarArgs<T> &a, int nb, hipStream
     case kKickOnlyRed:
         hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, true, false, true>), grid, block, 0, s, a);
         break;
-    case kDriftKick:
-        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, true, false, false, true, true>), grid, block, 0, s, a);
-        break;
     case kDriftKickRed:
         hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, true, false, true, true, true>), grid, block, 0, s, a);
         break;
     case kKickDrift:
         hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, true, false, true, true>), grid, block, 0, s, a);
+        break;
+    case kKickCopy:
+        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, false, true, true>), grid, block, 0, s, a);
+        break;
+    case kKickCopyRed:
+        hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, true, true, true>), grid, block, 0, s, a);
         break;
     case kEnergy:
         hipLaunchKernelGGL((scalar_stage<T, NF, TX, TY, false, false, true, false, false>), grid, block, 0, s, a);

@@ -27,7 +27,8 @@ ROOT = os.path.dirname(HERE)
 VARIANTS = {
     ("false", "false", "false", "false", "true"): "kick",
     ("false", "false", "true", "false", "true"): "kick_red",
-    ("true", "false", "false", "true", "true"): "drift_kick",
+    ("false", "false", "false", "true", "true"): "kick",
+    ("false", "false", "true", "true", "true"): "kick_red",
     ("true", "false", "true", "true", "true"): "drift_kick_red",
     ("false", "true", "false", "true", "true"): "kick_drift",
     ("false", "false", "true", "false", "false"): "energy",
