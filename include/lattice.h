@@ -232,8 +232,9 @@ lat_status lattice_energy_batch(lat_ctx *ctx, int32_t r, lat_energies *out);
  * of |f~(n)|^2 of the unnormalised forward DFT, count[b] = number of modes,
  * delta[b] = k_b^3/(2 pi^2) (dx/N)^3 sum[b]/(4 pi b^2) with k_b = b k_IR,
  * k_IR = 2 pi/(N dx) (delta[0] = 0), so that sum_{b>=1} (k_IR/k_b) delta[b]
- * = <f^2> - <f>^2 (eq. discretePSII).  Float64 transform (hipFFT) whatever
- * the field precision; bin sums are accumulated in an order that may vary at
+ * = <f^2> - <f>^2 (eq. discretePSII).  Float64 transform whatever the field
+ * precision (the library's own line transforms for N up to 512 without a prime
+ * factor above 7, hipFFT otherwise); bin sums are accumulated in an order that may vary at
  * the last bit.  The transform buffers (about 2 N^3 doubles) are allocated on
  * the first call.  Synchronizes the context stream.  Errors: LAT_EINVAL for a
  * batch context, a field or array out of range, or nbins outside [1, 448]. */
@@ -268,8 +269,8 @@ lat_status lattice_gauss_init(lat_ctx *ctx, double *mean_charge);
  * fstar2 = (f_star/omega_star)^2 of the model's units, and a, a' those of the
  * current time (self-consistent, fixed or a = 1).  The shell average divides by
  * 4 pi b^2 as in eq. discretePS; count[b] gives the number of modes for a
- * per-mode mean.  n[0] = 0.  Host arrays of nbins.  Float64 transforms of
- * phi_s and pi_s (hipFFT); a second half-spectrum buffer is allocated on the
+ * per-mode mean.  n[0] = 0.  Host arrays of nbins.  Float64 transforms as
+ * lattice_spectrum's; a second half-spectrum buffer is allocated on the
  * first call.  Synchronizes the context stream.  Errors: LAT_EINVAL for a batch
  * context, field outside [0, nfields), nbins outside [1, 448] or fstar2 <= 0;
  * LAT_EUNSUPPORTED for the U(1) model; LAT_ESTATE for leapfrog momenta at the

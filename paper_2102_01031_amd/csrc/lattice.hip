@@ -40,6 +40,7 @@
 #include "stage_batch.hpp"
 #include "stage_slab.hpp"
 #include "spectrum.hpp"
+#include "fft_launch.hpp"
 #include "stage_adjoint_self.hpp"
 
 using namespace lat;
@@ -209,7 +210,11 @@ struct lat_ctx {
     double *fft_in = nullptr;
     double2 *fft_out = nullptr;
     double2 *fft_out2 = nullptr;          // second half spectrum (occupation number: momenta)
-    double *spec_part = nullptr;        // per-block sums and counts, then the per-bin totals
+    double *spec_part = nullptr;        // per-block sums and counts
+    double *spec_host = nullptr;        // pinned: the per-bin totals
+    int spec_own = -1;                  // 1: the line transforms of fft.hpp serve N, 0: hipFFT, -1: not set up
+    FftPlan spec_plan{};
+    double2 *spec_tw = nullptr, *spec_g[2] = {};
     std::string err;
 };
 
@@ -1481,6 +1486,10 @@ void free_ctx(lat_ctx *c)
     if (c->fft_out) (void)hipFree(c->fft_out);
     if (c->fft_out2) (void)hipFree(c->fft_out2);
     if (c->spec_part) (void)hipFree(c->spec_part);
+    if (c->spec_host) (void)hipHostFree(c->spec_host);
+    if (c->spec_tw) (void)hipFree(c->spec_tw);
+    for (auto q : c->spec_g)
+        if (q) (void)hipFree(q);
     for (void *q : c->pi_scratch)
         if (q) (void)hipFree(q);
     for (lat_ctx *sub : c->subs) free_ctx(sub);
@@ -1961,6 +1970,53 @@ lat_status lattice_energy_noalloc(const lat_params *p, const lat_fields *f, doub
 // device, normalisation on the host.
 constexpr int kSpecBlocks = 1024;
 
+// Partial and pinned result buffers of the shell sums, on first use.
+static lat_status ensure_spec_sums(lat_ctx *c)
+{
+    if (!c->spec_part &&
+        hipMalloc(&c->spec_part, (size_t)4 * (kSpecBlocks + 1) * kSpecMaxBins * sizeof(double)) != hipSuccess) {
+        c->spec_part = nullptr;
+        return fail(c, LAT_ENOMEM, "spectrum buffers");
+    }
+    if (!c->spec_host && hipHostMalloc((void **)&c->spec_host, (3 * (size_t)kSpecMaxBins + 2) * sizeof(double),
+                                       hipHostMallocDefault) != hipSuccess) {
+        c->spec_host = nullptr;
+        return fail(c, LAT_ENOMEM, "spectrum buffers");
+    }
+    return LAT_OK;
+}
+
+// The spectrum passes' plan, roots and nq half-spectrum buffers, on first use;
+// spec_own = 0 where N needs the library transform.
+static lat_status ensure_spec(lat_ctx *c, int nq)
+{
+    lat_status st = ensure_spec_sums(c);
+    if (st != LAT_OK) return st;
+    if (c->spec_own < 0) {
+        if (!fft_radices(c->N, &c->spec_plan)) {
+            c->spec_own = 0;
+            return LAT_OK;
+        }
+        std::vector<double2> tw((size_t)c->N);
+        fft_roots(c->N, tw.data());
+        if (hipMalloc(&c->spec_tw, tw.size() * sizeof(double2)) != hipSuccess) {
+            c->spec_tw = nullptr;
+            return fail(c, LAT_ENOMEM, "spectrum buffers");
+        }
+        HIPCHK(c, hipMemcpy(c->spec_tw, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice));
+        c->spec_plan.tw = c->spec_tw;
+        c->spec_own = 1;
+    }
+    if (c->spec_own == 0) return LAT_OK;
+    for (int q = 0; q < nq; ++q)
+        if (!c->spec_g[q] &&
+            hipMalloc(&c->spec_g[q], (size_t)c->N * c->N * c->spec_plan.HP * sizeof(double2)) != hipSuccess) {
+            c->spec_g[q] = nullptr;
+            return fail(c, LAT_ENOMEM, "spectrum buffers");
+        }
+    return LAT_OK;
+}
+
 // Transform buffers and plans on first use (kept until lattice_destroy).
 static lat_status ensure_fft(lat_ctx *c, bool inverse)
 {
@@ -2093,27 +2149,28 @@ lat_status lattice_spectrum(lat_ctx *c, int32_t field, int32_t which, int32_t nb
         return fail(c, LAT_EINVAL, "field or array out of range");
     if (nbins < 1 || nbins > kSpecMaxBins) return fail(c, LAT_EINVAL, "nbins out of range");
     const int N = c->N;
-    const size_t V = c->vol, H = (size_t)N * N * (N / 2 + 1);
-    lat_status st = ensure_fft(c, false);
-    if (st != LAT_OK) return st;
     const void *src = which == 0 ? c->phi[field][c->cur_phi[field]] : c->pi[field][c->cur_pi[field]];
     if (c->su2) src = which == 0 ? c->dbl[field][c->cur_su2] : c->dpi[field];
-    st = forward_transform(c, src, c->fft_out);
+    lat_status st = ensure_spec(c, 1);
     if (st != LAT_OK) return st;
-    const int nb = (int)std::min<size_t>(kSpecBlocks, (H + kSpecThreads - 1) / kSpecThreads);
-    double *ps = c->spec_part, *pc = ps + (size_t)kSpecBlocks * kSpecMaxBins;
-    double *tot = pc + (size_t)kSpecBlocks * kSpecMaxBins;
-    hipLaunchKernelGGL(spectrum_bin, dim3(nb), dim3(kSpecThreads), 0, c->stream, c->fft_out, N, nbins, ps, pc);
-    HIPCHK(c, hipGetLastError());
-    hipLaunchKernelGGL(spectrum_reduce, dim3((nbins + 63) / 64), dim3(64), 0, c->stream, ps, pc, nb, nbins, tot,
-                       tot + kSpecMaxBins);
-    HIPCHK(c, hipGetLastError());
-    std::vector<double> host(2 * (size_t)kSpecMaxBins);
-    HIPCHK(c, hipMemcpyAsync(host.data(), tot, host.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    double *host = c->spec_host;
+    if (c->spec_own) {
+        HIPCHK(c, fft_spectra(c->spec_plan, c->f32, src, nullptr, 0.0, 0.0, 1, c->spec_g[0], nullptr, nbins,
+                              c->spec_part, host, c->stream));
+    } else {
+        const size_t H = (size_t)N * N * (N / 2 + 1);
+        if ((st = ensure_fft(c, false)) != LAT_OK) return st;
+        if ((st = forward_transform(c, src, c->fft_out)) != LAT_OK) return st;
+        const int nb = (int)std::min<size_t>(kSpecBlocks, (H + kSpecThreads - 1) / kSpecThreads);
+        hipLaunchKernelGGL(spectrum_bin, dim3(nb), dim3(kSpecThreads), 0, c->stream, c->fft_out, N, nbins,
+                           c->spec_part);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, sum_rows(c->spec_part, nb, 2 * nbins, host, c->stream));
+    }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (int b = 0; b < nbins; ++b) {
         sum[b] = host[b];
-        count[b] = (int64_t)std::llround(host[kSpecMaxBins + b]);
+        count[b] = (int64_t)std::llround(host[nbins + b]);
         delta[b] = b == 0 ? 0.0 : shell_weight(N, c->p.dx, b) * sum[b];
     }
     return LAT_OK;
@@ -2134,13 +2191,9 @@ lat_status lattice_occupation(lat_ctx *c, int32_t field, int32_t nbins, double f
     if (c->p.integrator == LAT_LF && c->lf_stag != 0)
         return fail(c, LAT_ESTATE, "momenta are at the half step: call lattice_sync first");
     const int N = c->N;
-    const size_t V = c->vol, H = (size_t)N * N * (N / 2 + 1);
-    lat_status st = ensure_fft(c, false);
+    const size_t V = c->vol;
+    lat_status st = ensure_spec(c, 2);
     if (st != LAT_OK) return st;
-    if (!c->fft_out2 && hipMalloc(&c->fft_out2, H * sizeof(double2)) != hipSuccess) {
-        c->fft_out2 = nullptr;
-        return fail(c, LAT_ENOMEM, "spectrum buffers");
-    }
     // scale factor and its derivative at the current time
     double a = 1.0, b = 0.0;
     if (c->p.expansion == LAT_EXP_FIXED) fixed_ab(c->p, c->t, &a, &b);
@@ -2150,20 +2203,29 @@ lat_status lattice_occupation(lat_ctx *c, int32_t field, int32_t nbins, double f
         a = c->sc_host->a;
         b = c->sc_host->b;
     }
-    st = forward_transform(c, c->phi[field][c->cur_phi[field]], c->fft_out);
-    if (st != LAT_OK) return st;
-    st = forward_transform(c, c->pi[field][c->cur_pi[field]], c->fft_out2);
-    if (st != LAT_OK) return st;
-    const size_t S = (size_t)kSpecBlocks * kSpecMaxBins;
-    double *part = c->spec_part, *tot = part + 3 * S;
-    double *sq_part = tot + 3 * kSpecMaxBins, *sq_tot = sq_part + 2 * kSpecBlocks;
-    const int nb = (int)std::min<size_t>(kSpecBlocks, (H + kSpecThreads - 1) / kSpecThreads);
-    hipLaunchKernelGGL(occupation_bin, dim3(nb), dim3(kSpecThreads), 0, c->stream, c->fft_out, c->fft_out2, N, nbins,
-                       std::pow(a, c->p.alpha - 3.0), b / a, part, S);
-    HIPCHK(c, hipGetLastError());
-    hipLaunchKernelGGL(spectrum_reduce_q, dim3((nbins + 63) / 64, 3), dim3(64), 0, c->stream, part, S, nb, nbins, 3,
-                       tot, kSpecMaxBins);
-    HIPCHK(c, hipGetLastError());
+    // shell sums of phi and of phi' + (a'/a) phi, the mode counts, then <phi^2>, <chi^2>
+    const void *phi = c->phi[field][c->cur_phi[field]], *pi_s = c->pi[field][c->cur_pi[field]];
+    const double cp = std::pow(a, c->p.alpha - 3.0), hub = b / a;
+    double *host = c->spec_host, *sq_host = host + 3 * (size_t)nbins;
+    if (c->spec_own) {
+        HIPCHK(c, fft_spectra(c->spec_plan, c->f32, phi, pi_s, hub, cp, 2, c->spec_g[0], c->spec_g[1], nbins,
+                              c->spec_part, host, c->stream));
+    } else {
+        const size_t H = (size_t)N * N * (N / 2 + 1);
+        if ((st = ensure_fft(c, false)) != LAT_OK) return st;
+        if (!c->fft_out2 && hipMalloc(&c->fft_out2, H * sizeof(double2)) != hipSuccess) {
+            c->fft_out2 = nullptr;
+            return fail(c, LAT_ENOMEM, "spectrum buffers");
+        }
+        if ((st = forward_transform(c, phi, c->fft_out)) != LAT_OK) return st;
+        if ((st = forward_transform(c, pi_s, c->fft_out2)) != LAT_OK) return st;
+        const int nb = (int)std::min<size_t>(kSpecBlocks, (H + kSpecThreads - 1) / kSpecThreads);
+        hipLaunchKernelGGL(occupation_bin, dim3(nb), dim3(kSpecThreads), 0, c->stream, c->fft_out, c->fft_out2, N,
+                           nbins, cp, hub, c->spec_part);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, sum_rows(c->spec_part, nb, 3 * nbins, host, c->stream));
+    }
+    double *sq_part = c->spec_part + (size_t)3 * kSpecBlocks * kSpecMaxBins;
     const int nq = (int)std::min<size_t>(kSpecBlocks, (V + kSpecThreads - 1) / kSpecThreads);
     const void *f0 = c->phi[0][c->cur_phi[0]], *f1 = c->nf > 1 ? c->phi[1][c->cur_phi[1]] : nullptr;
     if (c->f32)
@@ -2173,15 +2235,10 @@ lat_status lattice_occupation(lat_ctx *c, int32_t field, int32_t nbins, double f
         hipLaunchKernelGGL(sumsq_blocks<double>, dim3(nq), dim3(kSpecThreads), 0, c->stream, (const double *)f0,
                            (const double *)f1, V, sq_part);
     HIPCHK(c, hipGetLastError());
-    hipLaunchKernelGGL(sumsq_reduce, dim3(1), dim3(64), 0, c->stream, sq_part, nq, sq_tot);
-    HIPCHK(c, hipGetLastError());
-    std::vector<double> host(3 * (size_t)kSpecMaxBins + 2);
-    HIPCHK(c, hipMemcpyAsync(host.data(), tot, 3 * kSpecMaxBins * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(host.data() + 3 * kSpecMaxBins, sq_tot, 2 * sizeof(double), hipMemcpyDeviceToHost,
-                             c->stream));
+    HIPCHK(c, sum_rows(sq_part, nq, 2, sq_host, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     // <d^2V/dphi_s^2>: lambda/4 phi^4 -> 3 lambda phi^2; q/2 phi^2 chi^2 -> q chi^2 (phi), q phi^2 (chi)
-    const double p2 = host[3 * kSpecMaxBins] / (double)V, c2 = host[3 * kSpecMaxBins + 1] / (double)V;
+    const double p2 = sq_host[0] / (double)V, c2 = sq_host[1] / (double)V;
     double vpp = 0.0;
     if (field == 0) {
         vpp = 3.0 * c->p.lambda * p2;
@@ -2193,14 +2250,14 @@ lat_status lattice_occupation(lat_ctx *c, int32_t field, int32_t nbins, double f
     const double L = N * c->p.dx, N6 = (double)V * (double)V;
     const double pref = a * a * L * L * L / (2.0 * N6) * fstar2, wx = std::pow(a, 2.0 * (1.0 - c->p.alpha));
     for (int bin = 0; bin < nbins; ++bin) {
-        count[bin] = (int64_t)std::llround(host[2 * kSpecMaxBins + bin]);
+        count[bin] = (int64_t)std::llround(host[2 * nbins + bin]);
         if (bin == 0) {
             n[bin] = 0.0;
             continue;
         }
         const double kb = bin * (2.0 * pi / L);
         const double om = std::sqrt(kb * kb + a * a * vpp);
-        n[bin] = pref * (om * host[bin] + wx * host[kSpecMaxBins + bin] / om) / (4.0 * pi * (double)bin * bin);
+        n[bin] = pref * (om * host[bin] + wx * host[nbins + bin] / om) / (4.0 * pi * (double)bin * bin);
     }
     return LAT_OK;
 }

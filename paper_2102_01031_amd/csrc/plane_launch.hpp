@@ -12,8 +12,9 @@ hipError_t launch_plane_one(const ScalarArgs<T> &a, int nb, hipStream_t s)
 {
     const size_t lds = (size_t)2 * NF * (a.tiles_y + 2 * a.N) * sizeof(T);
     const auto fn = scalar_plane<T, NF, NT, XS, HPT, DLOAD, DEND, RED, WPHI, WPI, PF>;
-    if (lds > 48 * 1024) {   // beyond what a launch gets by default (with the static part)
-        const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (lds > 48 * 1024) {   // beyond what a launch gets by default (with the static part); a constant, so
+                             // that calls of several threads agree
+        const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(fn, dim3(nb), dim3(NT), lds, s, a);

@@ -7,7 +7,9 @@
 // kx in (0, N/2) stand for themselves and their mirror images (-nx, -ny, -nz),
 // which have the same |F| and |n|, so they count twice.  Bin b holds the modes
 // with b <= |n| < b + 1.  Per block: sums of |F|^2 and mode counts per bin in
-// LDS; a second kernel adds the block partials in block order.
+// LDS, left as one row of block values per bin (part[row gridDim.x + block]) that
+// sum_rows adds up, one block per row.  These kernels and the library transform
+// serve the sizes that fft.hpp does not (N above 512 or with a prime factor above 7).
 #pragma once
 #include "common.hpp"
 
@@ -17,8 +19,7 @@ constexpr int kSpecThreads = 256;
 constexpr int kSpecMaxBins = 448;   // >= floor(sqrt(3) 512/2) + 1
 
 __global__ void __launch_bounds__(kSpecThreads) spectrum_bin(const double2 *__restrict__ F, int N, int nbins,
-                                                             double *__restrict__ part_sum,
-                                                             double *__restrict__ part_cnt)
+                                                             double *__restrict__ part)
 {
     __shared__ double s_sum[kSpecMaxBins], s_cnt[kSpecMaxBins];
     for (int b = threadIdx.x; b < nbins; b += kSpecThreads) s_sum[b] = s_cnt[b] = 0.0;
@@ -43,23 +44,9 @@ __global__ void __launch_bounds__(kSpecThreads) spectrum_bin(const double2 *__re
     }
     __syncthreads();
     for (int b = threadIdx.x; b < nbins; b += kSpecThreads) {
-        part_sum[(size_t)blockIdx.x * nbins + b] = s_sum[b];
-        part_cnt[(size_t)blockIdx.x * nbins + b] = s_cnt[b];
+        part[(size_t)b * gridDim.x + blockIdx.x] = s_sum[b];
+        part[(size_t)(nbins + b) * gridDim.x + blockIdx.x] = s_cnt[b];
     }
-}
-
-__global__ void spectrum_reduce(const double *__restrict__ part_sum, const double *__restrict__ part_cnt, int nblocks,
-                                int nbins, double *__restrict__ sum, double *__restrict__ cnt)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nbins) return;
-    double s = 0.0, c = 0.0;
-    for (int k = 0; k < nblocks; ++k) {
-        s += part_sum[(size_t)k * nbins + b];
-        c += part_cnt[(size_t)k * nbins + b];
-    }
-    sum[b] = s;
-    cnt[b] = c;
 }
 
 // Seed of an adjoint from O = Delta(b) of one field (eq. discretePS).  With
@@ -130,11 +117,10 @@ __global__ void __launch_bounds__(kSpecThreads) spectrum_shell_seed(double2 *__r
 // real field: from the half spectra F of phi and P of pi, per bin the sums of
 // |F|^2, of |cp P + hub F|^2 (the transform of phi' + (a'/a) phi with
 // phi' = cp pi, cp = a^{alpha-3}, hub = a'/a) and the mode count, mirror modes
-// counted as in spectrum_bin.  Per-block LDS sums, then one row per block.
+// counted as in spectrum_bin.  Per-block LDS sums, then rows as there.
 __global__ void __launch_bounds__(kSpecThreads) occupation_bin(const double2 *__restrict__ F,
                                                                const double2 *__restrict__ P, int N, int nbins,
-                                                               double cp, double hub, double *__restrict__ part,
-                                                               size_t stride)
+                                                               double cp, double hub, double *__restrict__ part)
 {
     __shared__ double s_f[kSpecMaxBins], s_x[kSpecMaxBins], s_c[kSpecMaxBins];
     for (int b = threadIdx.x; b < nbins; b += kSpecThreads) s_f[b] = s_x[b] = s_c[b] = 0.0;
@@ -161,27 +147,14 @@ __global__ void __launch_bounds__(kSpecThreads) occupation_bin(const double2 *__
     }
     __syncthreads();
     for (int b = threadIdx.x; b < nbins; b += kSpecThreads) {
-        part[(size_t)blockIdx.x * nbins + b] = s_f[b];
-        part[stride + (size_t)blockIdx.x * nbins + b] = s_x[b];
-        part[2 * stride + (size_t)blockIdx.x * nbins + b] = s_c[b];
+        part[(size_t)b * gridDim.x + blockIdx.x] = s_f[b];
+        part[(size_t)(nbins + b) * gridDim.x + blockIdx.x] = s_x[b];
+        part[(size_t)(2 * nbins + b) * gridDim.x + blockIdx.x] = s_c[b];
     }
 }
 
-// nq quantities of per-block rows (quantity q at part + q stride) added in
-// block order: tot[q * tot_stride + b]
-__global__ void spectrum_reduce_q(const double *__restrict__ part, size_t stride, int nblocks, int nbins, int nq,
-                                  double *__restrict__ tot, int tot_stride)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    const int q = blockIdx.y;
-    if (b >= nbins || q >= nq) return;
-    double s = 0.0;
-    for (int k = 0; k < nblocks; ++k) s += part[q * stride + (size_t)k * nbins + b];
-    tot[(size_t)q * tot_stride + b] = s;
-}
-
 // Sums of squares of up to two real arrays of n values (f1 may be null): per
-// block part[2 block + s]; fixed grid, so the result does not vary run to run.
+// block part[s gridDim.x + block]; fixed grid, so the result does not vary run to run.
 template <typename T>
 __global__ void __launch_bounds__(kSpecThreads) sumsq_blocks(const T *__restrict__ f0, const T *__restrict__ f1,
                                                              size_t n, double *__restrict__ part)
@@ -206,17 +179,8 @@ __global__ void __launch_bounds__(kSpecThreads) sumsq_blocks(const T *__restrict
     if (threadIdx.x < 2) {
         double s = 0.0;
         for (int k = 0; k < kSpecThreads / 64; ++k) s += lds[threadIdx.x][k];
-        part[2 * blockIdx.x + threadIdx.x] = s;
+        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = s;
     }
-}
-
-__global__ void sumsq_reduce(const double *__restrict__ part, int nblocks, double *__restrict__ tot)
-{
-    const int s = threadIdx.x;
-    if (s >= 2) return;
-    double acc = 0.0;
-    for (int k = 0; k < nblocks; ++k) acc += part[2 * k + s];
-    tot[s] = acc;
 }
 
 // widen a float32 field into the float64 transform input
