@@ -106,9 +106,8 @@ struct lat_ctx {
     // per-site records of the doublet and links while lattice_step runs (ping-pong)
     double4 *su2_aos[2] = {};
     int su2_aos_on = 0;
-    bool u1_rows = false;   // whole-row U(1) leapfrog kernel
-    int u1_ty = 4, u1_zc = 8;
-    int u1_ezc = 1;         // z planes per block of the U(1) energy pass
+    int u1_ty = 0, u1_zc = 1; // U(1) row-sharing kernel (u1_span): rows and planes per block; u1_ty 0: u1_stage
+    int u1_ezc = 1;         // z planes per block of u1_stage's energy pass
     // scratch
     double *partials = nullptr;
     size_t partial_cap = 0;
@@ -598,55 +597,9 @@ hipError_t launch_sums_finish(int NT, int nf, const double *partials, int nb, Sc
     return hipErrorInvalidValue;
 }
 
-// The deferred block partials of a gauge summing pass (the U(1) and SU(2)
-// energy and kick-and-sums passes: 8 sums, then 3 maxima per block), combined
-// by one block of NT threads, NT the pass's block size: the order and the
-// arithmetic of the pass's own last-block reduction.
-static_assert(kU1Sums == 8 && kU1Maxes == 3 && kSU2Sums == 8 && kSU2Maxes == 3, "gauge sum layout");
-template <int NT>
-__global__ void __launch_bounds__(NT) gauge_sums_finish(const double *partials, int nb, ScaleRecord *S)
-{
-    constexpr int NS = 8, NQ = 11;
-    __shared__ double lds_red[(NT / 64) * NQ];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    double part[NQ];
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) part[k] = 0.0;
-    for (int i = tid; i < nb; i += NT) {
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            const double v = partials[(size_t)i * NQ + k];
-            part[k] = k < NS ? part[k] + v : fmax(part[k], v);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-        const double r = k < NS ? wave_sum(part[k]) : wave_max(part[k]);
-        if (lane == 0) lds_red[w * NQ + k] = r;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        for (int k = 0; k < NQ; ++k) {
-            double r = 0.0;
-            for (int i = 0; i < NT / 64; ++i) r = k < NS ? r + lds_red[i * NQ + k] : fmax(r, lds_red[i * NQ + k]);
-            if (k < NS) S->sums[k] = r;
-            else S->maxes[k - NS] = r;
-        }
-    }
-}
-
-hipError_t launch_gauge_sums_finish(int NT, const double *partials, int nb, ScaleRecord *S, hipStream_t st)
-{
-    if (NT == 256) hipLaunchKernelGGL(gauge_sums_finish<256>, dim3(1), dim3(256), 0, st, partials, nb, S);
-    else if (NT == 512) hipLaunchKernelGGL(gauge_sums_finish<512>, dim3(1), dim3(512), 0, st, partials, nb, S);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-// Summing passes of the gauge models leave their block partials to
-// gauge_sums_finish (no ticket release in their blocks); LATTICE_ENERGY_DEFER=0
-// keeps the ticketed last block (the same results, bit for bit).
-static bool gauge_defer_on()
+// The adjoint passes leave dO/dq in per-block slots (no ticket release in their
+// blocks); LATTICE_ENERGY_DEFER=0 keeps the ticketed last block.
+static bool adjoint_defer_on()
 {
     const char *e = std::getenv("LATTICE_ENERGY_DEFER");
     return e ? std::atoi(e) != 0 : true;
@@ -1594,10 +1547,13 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
         free_ctx(c);
         return st;
     };
+    const bool gauge_self = p->expansion == LAT_EXP_SELF;
     for (int i = 0; i < c->nf; ++i) {
         c->phi[i][0] = f->phi[i];
         c->pi[i][0] = f->pi[i];
-        if (hipMalloc(&c->phi[i][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
+        // (the gauge models' self-consistent steps drift in place and need no shadows)
+        if (!(c->u1 && gauge_self) && hipMalloc(&c->phi[i][1], bytes) != hipSuccess)
+            return bail(LAT_ENOMEM, "shadow allocation failed");
         // U(1) momenta are read at their own site only and updated in place
         if (!c->u1 && hipMalloc(&c->pi[i][1], bytes) != hipSuccess)
             return bail(LAT_ENOMEM, "shadow allocation failed");
@@ -1606,18 +1562,18 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
         for (int i = 0; i < 3; ++i) {
             c->A[i][0] = f->A[i];
             c->piA[i] = f->piA[i];
-            if (hipMalloc(&c->A[i][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
+            if (!gauge_self && hipMalloc(&c->A[i][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
         }
     }
     if (c->su2) {
         for (int k = 0; k < 4; ++k) {
             c->dbl[k][0] = f->doublet[k];
             c->dpi[k] = f->pi_doublet[k];
-            if (hipMalloc(&c->dbl[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
+            if (!gauge_self && hipMalloc(&c->dbl[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
         }
         for (int k = 0; k < 12; ++k) {
             c->lnk[k][0] = f->U[k];
-            if (hipMalloc(&c->lnk[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
+            if (!gauge_self && hipMalloc(&c->lnk[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
         }
         for (int k = 0; k < 9; ++k) c->efl[k] = f->E[k];
         su2_geometry(c);
@@ -1629,8 +1585,8 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
     c->partial_cap = (size_t)std::max(c->nblocks > 1 ? c->nblocks : 1, c->en_nblocks) * kMaxQ + 64;
     if (c->su2) c->partial_cap = su2_partial_capacity(c->N) + 64;
     if (c->u1) {
-        c->partial_cap = u1_partial_capacity(c->N) + 64;
         u1_geometry(c);
+        c->partial_cap = u1_partial_capacity(c->N) + 64;
     }
     if (hipMalloc(&c->partials, c->partial_cap * sizeof(double)) != hipSuccess) return bail(LAT_ENOMEM, "scratch allocation failed");
     if (hipMalloc(&c->ticket, 64) != hipSuccess) return bail(LAT_ENOMEM, "scratch allocation failed");
@@ -2304,8 +2260,9 @@ constexpr int kU1TX = 64, kU1TY = 4;
 
 size_t u1_partial_capacity(int N)
 {
+    // one block per plane and four rows or fewer sites of the span kernel's shapes
     const size_t tiles = (size_t)((N + kU1TX - 1) / kU1TX) * ((N + kU1TY - 1) / kU1TY) * (size_t)N;
-    return tiles * (kU1Sums + kU1Maxes);
+    return std::max(tiles, (size_t)N * N) * (kU1Sums + kU1Maxes);
 }
 
 U1Args u1_args(lat_ctx *c, double ck, double hd, bool write_fields)
@@ -2336,8 +2293,6 @@ U1Args u1_args(lat_ctx *c, double ck, double hd, bool write_fields)
     a.hdA = hd;
     a.dw = nullptr;
     a.partials = c->partials;
-    a.ticket = c->ticket;
-    a.sc = c->sc;
     return a;
 }
 
@@ -2355,115 +2310,142 @@ U1Args u1_args_bg(lat_ctx *c, double ck, double h, double ak, double am, bool wr
     return a;
 }
 
-// weights from the device record (self-consistent expansion)
-U1Args u1_args_dev(lat_ctx *c, bool write_fields)
+// weights from the device record (self-consistent expansion); the drift in place
+U1Args u1_args_dev(lat_ctx *c)
 {
-    U1Args a = u1_args(c, 0.0, 0.0, write_fields);
+    U1Args a = u1_args(c, 0.0, 0.0, false);
+    for (int i = 0; i < 2; ++i) a.phi_out[i] = (double *)c->phi[i][0];
+    for (int i = 0; i < 3; ++i) a.A_out[i] = (double *)c->A[i][0];
     a.dw = c->sc->w;
     return a;
 }
 
-U1SelfConst u1_self_const(const lat_ctx *c)
+// U(1) launch geometry.  u1_span where a block's rows fit: 17 TY + 24 doubles of LDS
+// per x position, at most 512 sites per block.  Of all row counts and z chunks the one
+// with the least rounds * (planes + 2 of a block's start-up) * (threads resident per
+// CU, a halo row counted as 0.6 of a row for its loads and half of its sines, and not
+// below 512: fewer wait for latency all the same).  96^3: 30.4 us per pass in five
+// rows by eight planes, 32.2 in four by ten, 37.0 in two by ten.  u1_stage otherwise.
+// LATTICE_U1_TILE="tile" selects u1_stage, "TY,zc" the span kernel's shape.
+constexpr size_t kU1MaxLds = 156 * 1024;
+bool u1_shape_ok(int N, int ty)
 {
-    return U1SelfConst{c->p.alpha, c->p.kappa2, 1.0 / (double)c->vol};
+    return ty >= 1 && ty <= N && ty * N <= kU1SpanThreads && u1_span_lds(N, ty) * sizeof(double) <= kU1MaxLds;
 }
 
-// whole-row leapfrog pass: N = 64 XS, rows per block TY in {4, 8} (N = 64)
-// or {2, 4} (N = 128), 64 XS TY threads (one site each per plane)
-bool u1_rows_shape_ok(int N, int ty)
+void u1_geometry(lat_ctx *c)
 {
-    return (N == 64 && (ty == 4 || ty == 8)) || (N == 128 && (ty == 2 || ty == 4));
+    const int N = c->N;
+    c->u1_ty = 0;
+    double best = 0.0;
+    for (int ty = 1; ty <= N && ty * N <= kU1SpanThreads; ++ty) {
+        if (!u1_shape_ok(N, ty)) continue;
+        const int nt = (ty * N + 63) / 64 * 64, tiles = (N + ty - 1) / ty;
+        const long per_cu = std::max<long>(1, std::min<long>(160 * 1024 / (u1_span_lds(N, ty) * sizeof(double) + 1024),
+                                                             kU1SpanThreads / nt));
+        for (int z = 1; z <= N; ++z) {
+            const long nb = (long)tiles * ((N + z - 1) / z), rounds = (nb + 256 * per_cu - 1) / (256 * per_cu);
+            const long resident = std::min<long>(per_cu, (nb + 255) / 256);
+            const double cost = (double)rounds * (z + 2) * std::max(512.0, resident * nt * (1.0 + 0.6 / ty));
+            if (c->u1_ty == 0 || cost < best) {
+                best = cost;
+                c->u1_ty = ty;
+                c->u1_zc = z;
+            }
+        }
+    }
+    // u1_stage's energy pass: columns of z planes, about 256 blocks in all
+    const long tpp = (long)((N + kU1TX - 1) / kU1TX) * ((N + kU1TY - 1) / kU1TY);
+    c->u1_ezc = (int)std::min<long>(N, std::max<long>(1, ((long)N * tpp + 255) / 256));
+    if (const char *ez = std::getenv("LATTICE_U1_ENERGY_ZC")) {
+        const int v = std::atoi(ez);
+        if (v >= 1 && v <= N) c->u1_ezc = v;
+    }
+    if (const char *env = std::getenv("LATTICE_U1_TILE")) {
+        int ty = 0, zc = 0;
+        if (std::strcmp(env, "tile") == 0) {
+            c->u1_ty = 0;
+        } else if (std::sscanf(env, "%d,%d", &ty, &zc) == 2 && u1_shape_ok(N, ty) && zc >= 1 && zc <= N) {
+            c->u1_ty = ty;
+            c->u1_zc = zc;
+        }
+    }
+}
+
+int u1_span_blocks(const lat_ctx *c)
+{
+    return ((c->N + c->u1_ty - 1) / c->u1_ty) * ((c->N + c->u1_zc - 1) / c->u1_zc);
 }
 
 template <int MODE>
-hipError_t launch_u1_rows(const lat_ctx *c, const U1Args &a)
+hipError_t launch_u1_span(const lat_ctx *c, const U1Args &a, int nb)
 {
-    const int nb = (c->N / c->u1_ty) * ((c->N + c->u1_zc - 1) / c->u1_zc);
-    const dim3 nt(c->N * c->u1_ty);
-    if (c->N == 64 && c->u1_ty == 4) hipLaunchKernelGGL((u1_rows<1, 4, MODE>), dim3(nb), nt, 0, c->stream, a);
-    else if (c->N == 64) hipLaunchKernelGGL((u1_rows<1, 8, MODE>), dim3(nb), nt, 0, c->stream, a);
-    else if (c->u1_ty == 2) hipLaunchKernelGGL((u1_rows<2, 2, MODE>), dim3(nb), nt, 0, c->stream, a);
-    else hipLaunchKernelGGL((u1_rows<2, 4, MODE>), dim3(nb), nt, 0, c->stream, a);
-    return hipGetLastError();
+    const int N = c->N, ty = c->u1_ty, nt = (ty * N + 63) / 64 * 64;
+    if (!u1_shape_ok(N, ty) || 2 * N > 2 * nt || a.zc < 1) return hipErrorInvalidValue;
+    const size_t lds = u1_span_lds(N, ty) * sizeof(double);
+    auto go = [&](auto fn) {
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kU1MaxLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(fn, dim3(nb), dim3(nt), lds, c->stream, a, ty);
+        return hipGetLastError();
+    };
+    return 2 * N <= nt ? go(u1_span<1, MODE>) : go(u1_span<2, MODE>);
 }
 
-// U(1) launch geometry: whole-row kernel for N = 64, 128 unless LATTICE_U1_TILE
-// says "tile"; "TY,zc" overrides the row kernel's rows per block and z chunk.
-void u1_geometry(lat_ctx *c)
+// The one-block kernel after a summing pass of nb blocks: its sums into the record,
+// the scale-factor update, and with `host` the record into c->sc_host.
+lat_status gauge_finish_launch(lat_ctx *c, int nb, const GaugeUpdate &u, bool host)
 {
-    c->u1_rows = c->N == 64 || c->N == 128;
-    c->u1_ty = 4;
-    c->u1_zc = c->N == 128 ? 16 : 4;
-    // the energy pass gives each block a column of z planes, about 256 blocks in
-    // all: every block's ticket release writes back its XCD's L2, and these
-    // releases queue per XCD (at 128^3: 337 us per pass in 8192 one-plane
-    // blocks, 140 us at 8 planes, 114 us at 32 planes, 256 blocks).
-    // LATTICE_U1_ENERGY_ZC overrides the planes per block.
-    const long tpp = (long)((c->N + kU1TX - 1) / kU1TX) * ((c->N + kU1TY - 1) / kU1TY);
-    c->u1_ezc = (int)std::min<long>(c->N, std::max<long>(1, ((long)c->N * tpp + 255) / 256));
-    if (const char *ez = std::getenv("LATTICE_U1_ENERGY_ZC")) {
-        const int v = std::atoi(ez);
-        if (v >= 1 && v <= c->N) c->u1_ezc = v;
-    }
-    const char *env = std::getenv("LATTICE_U1_TILE");
-    if (!env) return;
-    if (std::strcmp(env, "tile") == 0) {
-        c->u1_rows = false;
-        return;
-    }
-    int ty = 0, zc = 0;
-    if (c->u1_rows && std::sscanf(env, "%d,%d", &ty, &zc) == 2 && u1_rows_shape_ok(c->N, ty) && zc >= 1 &&
-        zc <= c->N) {
-        c->u1_ty = ty;
-        c->u1_zc = zc;
-    }
+    const U1SelfConst k{c->p.alpha, c->p.kappa2, 1.0 / (double)c->vol};
+    hipLaunchKernelGGL(gauge_finish, dim3(1), dim3(kGaugeFinishThreads), 0, c->stream, (const double *)c->partials, nb,
+                       c->sc, u, k, host ? c->sc_host : nullptr);
+    HIPCHK(c, hipGetLastError());
+    return LAT_OK;
 }
 
-lat_status u1_launch(lat_ctx *c, int mode, const U1Args &a)
+lat_status u1_launch(lat_ctx *c, int mode, const U1Args &a, const GaugeUpdate &u = GaugeUpdate{}, bool host = false)
 {
-    const int nb = a.tiles_x * a.tiles_y * c->N;
     const int kind = 6;
+    const bool span = c->u1_ty > 0;
+    int nb = span ? u1_span_blocks(c) : a.tiles_x * a.tiles_y * c->N;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (c->profiling) {
         lat_status st = timing_begin(c, &ev0, &ev1);
         if (st != LAT_OK) return st;
     }
+    const dim3 tb(kU1TX * kU1TY);
     switch (mode) {
     case kU1Step:
-        if (c->u1_rows) {
-            HIPCHK(c, launch_u1_rows<kU1Step>(c, a));
-            break;
-        }
-        hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Step>), dim3(nb), dim3(kU1TX * kU1TY), 0, c->stream, a);
+        if (span) HIPCHK(c, launch_u1_span<kU1Step>(c, a, nb));
+        else hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Step>), dim3(nb), tb, 0, c->stream, a);
         break;
     case kU1Kick:
-        if (c->u1_rows) {
-            HIPCHK(c, launch_u1_rows<kU1Kick>(c, a));
-            break;
-        }
-        hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Kick>), dim3(nb), dim3(kU1TX * kU1TY), 0, c->stream, a);
+        if (span) HIPCHK(c, launch_u1_span<kU1Kick>(c, a, nb));
+        else hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Kick>), dim3(nb), tb, 0, c->stream, a);
         break;
     case kU1Drift:
-        hipLaunchKernelGGL(u1_drift, dim3((unsigned)((c->vol + 255) / 256)), dim3(256), 0, c->stream, a,
-                           (unsigned)c->vol);
+        hipLaunchKernelGGL(u1_drift, dim3((unsigned)((c->vol + 255) / 256)), dim3(256), 0, c->stream, a, c->vol);
         break;
-    default: {   // the summing passes: energy, kick and sums (row kernel only)
+    default: {   // the summing passes
         U1Args e = a;
-        e.defer = gauge_defer_on() ? 1 : 0;
-        int fnt, fnb;
-        if (c->u1_rows) {
-            HIPCHK(c, mode == kU1KickSums ? launch_u1_rows<kU1KickSums>(c, e) : launch_u1_rows<kU1Energy>(c, e));
-            fnt = c->N * c->u1_ty;
-            fnb = (c->N / c->u1_ty) * ((c->N + c->u1_zc - 1) / c->u1_zc);
+        if (span) {
+            HIPCHK(c, mode == kU1KickSums ? launch_u1_span<kU1KickSums>(c, e, nb) : launch_u1_span<kU1Energy>(c, e, nb));
         } else {
-            if (mode == kU1KickSums) return fail(c, LAT_EINVAL, "U(1) kick-and-sums pass needs the row kernel");
+            // kick and sums: the energy pass forms the sums of the kicked state
+            // without writing it, then a pass applies both kicks
             e.zc = c->u1_ezc;
-            fnb = a.tiles_x * a.tiles_y * ((c->N + e.zc - 1) / e.zc);
-            fnt = kU1TX * kU1TY;
-            hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Energy>), dim3(fnb), dim3(fnt), 0, c->stream, e);
+            nb = a.tiles_x * a.tiles_y * ((c->N + e.zc - 1) / e.zc);
+            hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Energy>), dim3(nb), tb, 0, c->stream, e);
+            if (mode == kU1KickSums) {
+                HIPCHK(c, hipGetLastError());
+                e.phi_out[0] = nullptr;   // momenta only
+                hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Kick>), dim3(a.tiles_x * a.tiles_y * c->N), tb, 0,
+                                   c->stream, e);
+            }
         }
         HIPCHK(c, hipGetLastError());
-        if (e.defer) HIPCHK(c, launch_gauge_sums_finish(fnt, e.partials, fnb, e.sc, c->stream));
+        lat_status st = gauge_finish_launch(c, nb, u, host);
+        if (st != LAT_OK) return st;
         break;
     }
     }
@@ -2489,69 +2471,24 @@ lat_status u1_flip(lat_ctx *c)
         HIPCHK(c, hipGetLastError());                                               \
     } while (0)
 
-// LATTICE_U1_FUSE=0 turns off the shortcuts of the self-consistent gauge steps
-// (the U(1) kick pass that also forms the sums and the U(1) drift-only pass,
-// bit for bit the same results; the SU(2) drift-only pass, the same to rounding).
-static bool u1_fuse_on()
-{
-    const char *e = std::getenv("LATTICE_U1_FUSE");
-    return e ? std::atoi(e) != 0 : true;
-}
+// Self-consistent expansion of the gauge models (readings A3 and R1): two passes per
+// sub-step and one block between them.  A kick-and-sums pass (the two half kicks that
+// meet at a kick point use the same fields and the same a: one force evaluation, the
+// sums taken between them; leapfrog: one full kick, the momentum sums taken before
+// and after it), gauge_finish (b, a and the next weights from the sums), and the
+// drift, in place.
+lat_status gauge_kick_sums(lat_ctx *c, const GaugeUpdate &u);   // with the record's weights
+lat_status gauge_drift(lat_ctx *c);
 
-// The drift with the record's weights (its kick weight is zero): u1_drift in
-// place of a step pass.
-lat_status u1_drift_pass(lat_ctx *c)
-{
-    const bool drift = u1_fuse_on() && c->vol <= 0xffffffffu;   // 32-bit site index
-    return u1_launch(c, drift ? kU1Drift : kU1Step, u1_args_dev(c, true));
-}
-
-// The kick with the record's weights followed by the volume sums of the kicked
-// state (the b kick's "after" sums): one row-kernel pass where the row kernel
-// runs, which forms the sums an energy pass with zero kick weight would, bit for
-// bit.
-lat_status u1_kick_sums(lat_ctx *c)
-{
-    if (c->u1_rows && u1_fuse_on()) return u1_launch(c, kU1KickSums, u1_args_dev(c, false));
-    lat_status s = u1_launch(c, kU1Kick, u1_args_dev(c, false));
-    if (s != LAT_OK) return s;
-    return u1_launch(c, kU1Energy, u1_args(c, 0.0, 0.0, false));
-}
-
-// Leapfrog steps of the self-consistent gauge models after a call's first take
-// the sums before the kick from the neighbouring passes (u1_self_drift_w) in
-// place of an energy pass of their own; LATTICE_SELF_CARRY=0 measures them on
-// every step (the same values).
-static bool self_carry()
-{
-    const char *e = std::getenv("LATTICE_SELF_CARRY");
-    return e ? std::atoi(e) != 0 : true;
-}
-
-// Self-consistent expansion (readings A3 and R1 for the U(1) model): the kicks,
-// energy sums and drifts as separate passes, the scale factor, b and the pass
-// weights updated on the device between them (stage_u1.hpp, U1SelfConst).
-lat_status u1_step_self_lf(lat_ctx *c, int64_t ns, int dir)
+lat_status gauge_step_self_lf(lat_ctx *c, int64_t ns, int dir)
 {
     const double h = dir * c->p.dt;
-    const U1SelfConst kc = u1_self_const(c);
     int stag = c->lf_stag;
-    lat_status s;
-    const bool carry_on = self_carry();
+    U1K(u1_self_kick_w, c->sc, stag == 0 ? 0.5 * h : h, 0.0, c->p.alpha);
     for (int64_t k = 0; k < ns; ++k) {
-        const double w = stag == 0 ? 0.5 * h : h;
-        // sums of the state before the kick: measured on a call's first step,
-        // carried from the passes around it on the later ones
-        const int carry = stag != 0 && k > 0 && carry_on;
-        if (stag != 0 && !carry) {
-            if ((s = u1_launch(c, kU1Energy, u1_args(c, 0.0, 0.0, false))) != LAT_OK) return s;
-            U1K(u1_self_stash, c->sc);
-        }
-        U1K(u1_self_kick_w, c->sc, w, c->p.alpha);
-        if ((s = u1_kick_sums(c)) != LAT_OK) return s;
-        U1K(u1_self_drift_w, c->sc, h, stag == 0 ? 0.0 : 0.5 * h, stag == 0 ? w : 0.5 * h, kc, carry);
-        if ((s = u1_drift_pass(c)) != LAT_OK) return s;
-        u1_flip(c);
+        lat_status s = gauge_kick_sums(c, GaugeUpdate{1, stag == 0 ? 0.0 : 0.5 * h, 0.5 * h, 0.0, h, h, 0.0});
+        if (s != LAT_OK) return s;
+        if ((s = gauge_drift(c)) != LAT_OK) return s;
         stag = dir;
     }
     c->lf_stag = dir;
@@ -2559,9 +2496,76 @@ lat_status u1_step_self_lf(lat_ctx *c, int64_t ns, int dir)
     return LAT_OK;
 }
 
+lat_status gauge_step_self_vv(lat_ctx *c, int64_t ns, int dir)
+{
+    const double h = dir * c->p.dt;
+    const std::vector<double> w = vv_weights(c->p.integrator);
+    const int64_t J = (int64_t)w.size(), M = J * ns;
+    auto half = [&](int64_t p) { return p < 0 || p >= M ? 0.0 : 0.5 * (w[(size_t)(p % J)] * h); };
+    U1K(u1_self_kick_w, c->sc, 0.0, half(0), c->p.alpha);
+    for (int64_t p = 0; p <= M; ++p) {
+        lat_status s = gauge_kick_sums(c, GaugeUpdate{1, 0.0, half(p - 1), half(p), 2.0 * half(p), half(p), half(p + 1)});
+        if (s != LAT_OK) return s;
+        if (p < M && (s = gauge_drift(c)) != LAT_OK) return s;
+    }
+    c->t += (double)ns * h;
+    return LAT_OK;
+}
+
+// the sync's half kick of the momenta and b (its sums those before the kick)
+lat_status gauge_sync_self(lat_ctx *c)
+{
+    const double w = 0.5 * c->lf_stag * c->p.dt;
+    U1K(u1_self_kick_w, c->sc, w, 0.0, c->p.alpha);
+    return gauge_kick_sums(c, GaugeUpdate{1, w, 0.0, 0.0, 0.0, 0.0, 0.0});
+}
+
+// Energies of the gauge models' record after an energy pass: shared tail of
+// u1_energy and su2_energy (ck: the on-the-fly kick that pass took).
+void gauge_energies(const lat_ctx *c, double ck, lat_energies *out, double *EKg, double *EGg)
+{
+    const double V = (double)c->vol, al = c->p.alpha;
+    const double *S = c->sc_host->sums, *M = c->sc_host->maxes;
+    double a = 1.0, b = 0.0;
+    if (c->p.expansion == LAT_EXP_FIXED) fixed_ab(c->p, c->t, &a, &b);
+    if (c->p.expansion == LAT_EXP_SELF) {
+        a = c->sc_host->a;
+        b = c->sc_host->b;
+    }
+    const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2;
+    if (c->p.expansion == LAT_EXP_SELF && ck != 0.0) {
+        // a staggered b is half-kicked on the fly with the sums of the stored
+        // half-step momenta (reading A3)
+        const double Ka = std::pow(a, 2.0 * al + 1.0) / 3.0 * c->p.kappa2 *
+                          ((al - 2.0) * S[8] / V / a6 + al * S[1] / V / a2 +
+                           (al - 1.0) * (S[9] / V / a4 + S[4] / V / a4) + (al + 1.0) * S[2] / V);
+        b += ck * Ka;
+    }
+    out->t = c->t;
+    out->a = a;
+    out->b = b;
+    out->EK[0] = S[0] / V / a6;
+    out->EG[0] = S[1] / V / a2;
+    out->EV[0] = S[2] / V;
+    *EKg = S[3] / V / a4;
+    *EGg = S[4] / V / a4;
+    out->rho = out->EK[0] + out->EG[0] + out->EV[0] + *EKg + *EGg;
+    out->hubble_lhs = b * b;
+    out->hubble_rhs = std::pow(a, 2.0 * al + 2.0) * c->p.kappa2 * out->rho / 3.0;
+    const double den = out->hubble_lhs + out->hubble_rhs;
+    out->hubble_res = den != 0.0 ? (out->hubble_lhs - out->hubble_rhs) / den : 0.0;
+    out->gauss_mean = S[5] / V;
+    out->gauss_sum_mean = S[6] / V;
+    out->gauss_abs_mean = S[7] / V;
+    out->gauss_max = M[0];
+    out->gauss_div_max = M[1];
+    out->gauss_charge_max = M[2];
+    out->step = c->step;
+}
+
 lat_status u1_step_lf(lat_ctx *c, int64_t ns, int dir)
 {
-    if (c->p.expansion == LAT_EXP_SELF) return u1_step_self_lf(c, ns, dir);
+    if (c->p.expansion == LAT_EXP_SELF) return gauge_step_self_lf(c, ns, dir);
     const double h = dir * c->p.dt;
     const double t0 = c->t;
     int stag = c->lf_stag;
@@ -2582,14 +2586,8 @@ lat_status u1_step_lf(lat_ctx *c, int64_t ns, int dir)
 
 lat_status u1_sync(lat_ctx *c)
 {
+    if (c->p.expansion == LAT_EXP_SELF) return gauge_sync_self(c);
     const double w = 0.5 * c->lf_stag * c->p.dt;
-    if (c->p.expansion == LAT_EXP_SELF) {
-        lat_status s = u1_launch(c, kU1Energy, u1_args(c, 0.0, 0.0, false));
-        if (s != LAT_OK) return s;
-        U1K(u1_self_b_kick, c->sc, w, u1_self_const(c));
-        U1K(u1_self_kick_w, c->sc, w, c->p.alpha);
-        return u1_launch(c, kU1Kick, u1_args_dev(c, false));
-    }
     const double a = scale_at(c, c->t);
     return u1_launch(c, kU1Kick, u1_args_bg(c, w, 0.0, a, a, false));
 }
@@ -2597,55 +2595,18 @@ lat_status u1_sync(lat_ctx *c)
 lat_status u1_energy(lat_ctx *c, lat_energies *out)
 {
     const double ck = c->lf_stag != 0 ? 0.5 * c->lf_stag * c->p.dt : 0.0;
-    const double V = (double)c->vol, al = c->p.alpha;
-    double a = 1.0, b = 0.0;
-    lat_status s;
-    if (c->p.expansion == LAT_EXP_FIXED) fixed_ab(c->p, c->t, &a, &b);
+    U1Args a;
     if (c->p.expansion == LAT_EXP_SELF) {
-        // a and b of the record; a staggered b is half-kicked on the fly with
-        // the sums of the stored half-step momenta (reading A3)
-        if (ck != 0.0 && (s = u1_launch(c, kU1Energy, u1_args(c, 0.0, 0.0, false))) != LAT_OK) return s;
-        HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        a = c->sc_host->a;
-        b = c->sc_host->b;
-        if (ck != 0.0) {
-            const double *S = c->sc_host->sums;
-            const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2;
-            const double Ka = std::pow(a, 2.0 * al + 1.0) / 3.0 * c->p.kappa2 *
-                              ((al - 2.0) * S[0] / V / a6 + al * S[1] / V / a2 +
-                               (al - 1.0) * (S[3] / V / a4 + S[4] / V / a4) + (al + 1.0) * S[2] / V);
-            b += ck * Ka;
-        }
+        U1K(u1_self_kick_w, c->sc, ck, 0.0, c->p.alpha);   // at the record's a
+        a = u1_args_dev(c);
+    } else {
+        const double ak = scale_at(c, c->t);
+        a = u1_args_bg(c, ck, 0.0, ak, ak, false);
     }
-    s = u1_launch(c, kU1Energy, u1_args_bg(c, ck, 0.0, a, a, false));
+    lat_status s = u1_launch(c, kU1Energy, a, GaugeUpdate{}, true);
     if (s != LAT_OK) return s;
-    HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const double *S = c->sc_host->sums, *M = c->sc_host->maxes;
-    const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2;
-    out->t = c->t;
-    out->a = a;
-    out->b = b;
-    out->EK[0] = S[0] / V / a6;
-    out->EG[0] = S[1] / V / a2;
-    out->EV[0] = S[2] / V;
-    out->EK_A = S[3] / V / a4;
-    out->EG_A = S[4] / V / a4;
-    out->rho = out->EK[0] + out->EG[0] + out->EV[0] + out->EK_A + out->EG_A;
-    out->hubble_lhs = b * b;
-    out->hubble_rhs = std::pow(a, 2.0 * al + 2.0) * c->p.kappa2 * out->rho / 3.0;
-    {
-        const double den = out->hubble_lhs + out->hubble_rhs;
-        out->hubble_res = den != 0.0 ? (out->hubble_lhs - out->hubble_rhs) / den : 0.0;
-    }
-    out->gauss_mean = S[5] / V;
-    out->gauss_sum_mean = S[6] / V;
-    out->gauss_abs_mean = S[7] / V;
-    out->gauss_max = M[0];
-    out->gauss_div_max = M[1];
-    out->gauss_charge_max = M[2];
-    out->step = c->step;
+    gauge_energies(c, ck, out, &out->EK_A, &out->EG_A);
     return LAT_OK;
 }
 
@@ -2728,8 +2689,6 @@ SU2Args su2_args(lat_ctx *c, double ck, double hd, bool write_fields)
     a.hdU = hd;
     a.dw = nullptr;
     a.partials = c->partials;
-    a.ticket = c->ticket;
-    a.sc = c->sc;
     return a;
 }
 
@@ -2753,14 +2712,17 @@ SU2Args su2_args_bg(lat_ctx *c, double ck, double h, double ak, double am, bool 
 }
 
 // weights from the device record (self-consistent expansion)
-SU2Args su2_args_dev(lat_ctx *c, bool write_fields)
+SU2Args su2_args_dev(lat_ctx *c)
 {
-    SU2Args a = su2_args(c, 0.0, 0.0, write_fields);
+    SU2Args a = su2_args(c, 0.0, 0.0, false);
+    for (int k = 0; k < 4; ++k) a.phi_out[k] = (double *)c->dbl[k][0];   // the drift in place
+    for (int k = 0; k < 12; ++k) a.U_out[k] = (double *)c->lnk[k][0];
     a.dw = c->sc->w;
     return a;
 }
 
-lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args)
+lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args, const GaugeUpdate &u = GaugeUpdate{},
+                      bool host = false)
 {
     // the energy pass keeps the plane-wide order with its z columns: in the
     // band order's one-plane blocks its last block would sum 16x more block
@@ -2770,7 +2732,6 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args)
     if (sums) {
         a.band = 0;
         a.zc = su2_zc(c->N, false);
-        a.defer = gauge_defer_on() ? 1 : 0;
         // LATTICE_SU2_ENERGY_ZC: z planes per block of the summing passes alone
         if (const char *ez = std::getenv("LATTICE_SU2_ENERGY_ZC")) {
             const int v = std::atoi(ez);
@@ -2801,8 +2762,6 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args)
     case kSU2Kick: hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2Kick, false>), grid, blk, 0, c->stream, a); break;
     case kSU2KickSums:
         hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2KickSums, false>), grid, blk, 0, c->stream, a);
-        HIPCHK(c, hipGetLastError());
-        if (a.defer) HIPCHK(c, launch_gauge_sums_finish(kSU2TX * kSU2TY, a.partials, nb, a.sc, c->stream));
         break;
     case kSU2StepAoS:
         if (nt) hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2StepAoS, true>), grid, blk, 0, c->stream, a);
@@ -2810,11 +2769,13 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args)
         break;
     default:
         hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2Energy, false>), grid, blk, 0, c->stream, a);
-        HIPCHK(c, hipGetLastError());
-        if (a.defer) HIPCHK(c, launch_gauge_sums_finish(kSU2TX * kSU2TY, a.partials, nb, a.sc, c->stream));
         break;
     }
     HIPCHK(c, hipGetLastError());
+    if (sums) {
+        lat_status st = gauge_finish_launch(c, nb, u, host);
+        if (st != LAT_OK) return st;
+    }
     if (c->profiling) {
         lat_status st = timing_end(c, ev0, ev1, kind);
         if (st != LAT_OK) return st;
@@ -2882,61 +2843,19 @@ static bool su2_alternate()
     return e ? std::atoi(e) != 0 : true;
 }
 
-// Self-consistent expansion (readings A3 and R1 for the SU(2) model), as the
-// U(1) model's: the kicks, energy sums and drifts as separate passes on the
-// plain arrays, the scale factor, b and the pass weights updated on the device
-// between them with the U(1) model's one-thread kernels (the SU(2) energy pass
-// leaves its sums in the same slots: doublet kinetic, gradient, potential,
-// electric, magnetic).
-// The drift with the record's weights (its kick weight is zero): su2_drift in
-// place of a step pass (the same values to rounding); LATTICE_U1_FUSE=0 runs
-// the step pass, as for the U(1) model.
-lat_status su2_drift_pass(lat_ctx *c)
+lat_status gauge_kick_sums(lat_ctx *c, const GaugeUpdate &u)
 {
-    const bool drift = u1_fuse_on() && c->vol <= 0xffffffffu;
-    return su2_launch(c, drift ? kSU2Drift : kSU2Step, su2_args_dev(c, true));
+    return c->su2 ? su2_launch(c, kSU2KickSums, su2_args_dev(c), u) : u1_launch(c, kU1KickSums, u1_args_dev(c), u);
 }
 
-// The kick with the record's weights followed by the volume sums of the kicked
-// state: one pass in the energy pass's launch shape (kSU2KickSums) forming the
-// sums that pass would; LATTICE_U1_FUSE=0 runs the two passes.
-lat_status su2_kick_sums(lat_ctx *c)
+lat_status gauge_drift(lat_ctx *c)
 {
-    if (u1_fuse_on()) return su2_launch(c, kSU2KickSums, su2_args_dev(c, false));
-    lat_status s = su2_launch(c, kSU2Kick, su2_args_dev(c, false));
-    if (s != LAT_OK) return s;
-    return su2_launch(c, kSU2Energy, su2_args(c, 0.0, 0.0, false));
-}
-
-lat_status su2_step_self_lf(lat_ctx *c, int64_t ns, int dir)
-{
-    const double h = dir * c->p.dt;
-    const U1SelfConst kc = u1_self_const(c);
-    int stag = c->lf_stag;
-    lat_status s;
-    const bool carry_on = self_carry();
-    for (int64_t k = 0; k < ns; ++k) {
-        const double w = stag == 0 ? 0.5 * h : h;
-        const int carry = stag != 0 && k > 0 && carry_on;   // as in u1_step_self_lf
-        if (stag != 0 && !carry) {
-            if ((s = su2_launch(c, kSU2Energy, su2_args(c, 0.0, 0.0, false))) != LAT_OK) return s;
-            U1K(u1_self_stash, c->sc);
-        }
-        U1K(u1_self_kick_w, c->sc, w, c->p.alpha);
-        if ((s = su2_kick_sums(c)) != LAT_OK) return s;
-        U1K(u1_self_drift_w, c->sc, h, stag == 0 ? 0.0 : 0.5 * h, stag == 0 ? w : 0.5 * h, kc, carry);
-        if ((s = su2_drift_pass(c)) != LAT_OK) return s;
-        c->cur_su2 ^= 1;
-        stag = dir;
-    }
-    c->lf_stag = dir;
-    c->t += (double)ns * h;
-    return LAT_OK;
+    return c->su2 ? su2_launch(c, kSU2Drift, su2_args_dev(c)) : u1_launch(c, kU1Drift, u1_args_dev(c));
 }
 
 lat_status su2_step_lf(lat_ctx *c, int64_t ns, int dir)
 {
-    if (c->p.expansion == LAT_EXP_SELF) return su2_step_self_lf(c, ns, dir);
+    if (c->p.expansion == LAT_EXP_SELF) return gauge_step_self_lf(c, ns, dir);
     const double h = dir * c->p.dt;
     const double t0 = c->t;
     const bool fixed = c->p.expansion == LAT_EXP_FIXED;
@@ -2980,14 +2899,8 @@ lat_status su2_step_lf(lat_ctx *c, int64_t ns, int dir)
 
 lat_status su2_sync(lat_ctx *c)
 {
+    if (c->p.expansion == LAT_EXP_SELF) return gauge_sync_self(c);
     const double w = 0.5 * c->lf_stag * c->p.dt;
-    if (c->p.expansion == LAT_EXP_SELF) {
-        lat_status s = su2_launch(c, kSU2Energy, su2_args(c, 0.0, 0.0, false));
-        if (s != LAT_OK) return s;
-        U1K(u1_self_b_kick, c->sc, w, u1_self_const(c));
-        U1K(u1_self_kick_w, c->sc, w, c->p.alpha);
-        return su2_launch(c, kSU2Kick, su2_args_dev(c, false));
-    }
     const double a = scale_at(c, c->t);
     return su2_launch(c, kSU2Kick, su2_args_bg(c, w, 0.0, a, a, false));
 }
@@ -2995,55 +2908,18 @@ lat_status su2_sync(lat_ctx *c)
 lat_status su2_energy(lat_ctx *c, lat_energies *out)
 {
     const double ck = c->lf_stag != 0 ? 0.5 * c->lf_stag * c->p.dt : 0.0;
-    const double V = (double)c->vol, al = c->p.alpha;
-    double a = 1.0, b = 0.0;
-    lat_status s;
-    if (c->p.expansion == LAT_EXP_FIXED) fixed_ab(c->p, c->t, &a, &b);
+    SU2Args a;
     if (c->p.expansion == LAT_EXP_SELF) {
-        // a and b of the record; a staggered b is half-kicked on the fly with
-        // the sums of the stored half-step momenta (reading A3)
-        if (ck != 0.0 && (s = su2_launch(c, kSU2Energy, su2_args(c, 0.0, 0.0, false))) != LAT_OK) return s;
-        HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        a = c->sc_host->a;
-        b = c->sc_host->b;
-        if (ck != 0.0) {
-            const double *S = c->sc_host->sums;
-            const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2;
-            const double Ka = std::pow(a, 2.0 * al + 1.0) / 3.0 * c->p.kappa2 *
-                              ((al - 2.0) * S[0] / V / a6 + al * S[1] / V / a2 +
-                               (al - 1.0) * (S[3] / V / a4 + S[4] / V / a4) + (al + 1.0) * S[2] / V);
-            b += ck * Ka;
-        }
+        U1K(u1_self_kick_w, c->sc, ck, 0.0, c->p.alpha);   // at the record's a
+        a = su2_args_dev(c);
+    } else {
+        const double ak = scale_at(c, c->t);
+        a = su2_args_bg(c, ck, 0.0, ak, ak, false);
     }
-    s = su2_launch(c, kSU2Energy, su2_args_bg(c, ck, 0.0, a, a, false));
+    lat_status s = su2_launch(c, kSU2Energy, a, GaugeUpdate{}, true);
     if (s != LAT_OK) return s;
-    HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const double *S = c->sc_host->sums, *M = c->sc_host->maxes;
-    const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2;
-    out->t = c->t;
-    out->a = a;
-    out->b = b;
-    out->EK[0] = S[0] / V / a6;
-    out->EG[0] = S[1] / V / a2;
-    out->EV[0] = S[2] / V;
-    out->EK_B = S[3] / V / a4;
-    out->EG_B = S[4] / V / a4;
-    out->rho = out->EK[0] + out->EG[0] + out->EV[0] + out->EK_B + out->EG_B;
-    out->hubble_lhs = b * b;
-    out->hubble_rhs = std::pow(a, 2.0 * al + 2.0) * c->p.kappa2 * out->rho / 3.0;
-    {
-        const double den = out->hubble_lhs + out->hubble_rhs;
-        out->hubble_res = den != 0.0 ? (out->hubble_lhs - out->hubble_rhs) / den : 0.0;
-    }
-    out->gauss_mean = S[5] / V;
-    out->gauss_sum_mean = S[6] / V;
-    out->gauss_abs_mean = S[7] / V;
-    out->gauss_max = M[0];
-    out->gauss_div_max = M[1];
-    out->gauss_charge_max = M[2];
-    out->step = c->step;
+    gauge_energies(c, ck, out, &out->EK_B, &out->EG_B);
     return LAT_OK;
 }
 
@@ -3052,61 +2928,9 @@ lat_status su2_energy(lat_ctx *c, lat_energies *out)
 // pass per sub-step whose kick merges the half kicks that meet at its point,
 // (h_{p-1} + h_p)/2, and a closing kick-only pass of h_{M-1}/2; momenta end
 // at integer time.
-// U(1) velocity-Verlet family with self-consistent expansion (reading R1 for
-// each second-order map of the composition): kick(hs/2) at a_n, b half kick with
-// E_n, a drift, field drift at the mean a, kick(hs/2) at a_{n+1}, energies,
-// b half kick; every piece its own pass.
-lat_status u1_step_self_vv(lat_ctx *c, int64_t ns, int dir)
-{
-    const double h = dir * c->p.dt;
-    const std::vector<double> w = vv_weights(c->p.integrator);
-    const U1SelfConst kc = u1_self_const(c);
-    lat_status s;
-    if ((s = u1_launch(c, kU1Energy, u1_args(c, 0.0, 0.0, false))) != LAT_OK) return s;   // E_n
-    for (int64_t k = 0; k < ns; ++k)
-        for (double wp : w) {
-            const double hs = wp * h;
-            U1K(u1_self_kick_w, c->sc, 0.5 * hs, c->p.alpha);
-            if ((s = u1_launch(c, kU1Kick, u1_args_dev(c, false))) != LAT_OK) return s;
-            U1K(u1_self_drift_w, c->sc, hs, 0.0, 0.5 * hs, kc, 0);
-            if ((s = u1_drift_pass(c)) != LAT_OK) return s;
-            u1_flip(c);
-            U1K(u1_self_kick_w, c->sc, 0.5 * hs, c->p.alpha);
-            if ((s = u1_kick_sums(c)) != LAT_OK) return s;
-            U1K(u1_self_b_kick, c->sc, 0.5 * hs, kc);
-        }
-    c->t += (double)ns * h;
-    return LAT_OK;
-}
-
-// SU(2) velocity-Verlet family with self-consistent expansion: as the U(1) model's.
-lat_status su2_step_self_vv(lat_ctx *c, int64_t ns, int dir)
-{
-    const double h = dir * c->p.dt;
-    const std::vector<double> w = vv_weights(c->p.integrator);
-    const U1SelfConst kc = u1_self_const(c);
-    lat_status s;
-    if ((s = su2_launch(c, kSU2Energy, su2_args(c, 0.0, 0.0, false))) != LAT_OK) return s;   // E_n
-    for (int64_t k = 0; k < ns; ++k)
-        for (double wp : w) {
-            const double hs = wp * h;
-            U1K(u1_self_kick_w, c->sc, 0.5 * hs, c->p.alpha);
-            if ((s = su2_launch(c, kSU2Kick, su2_args_dev(c, false))) != LAT_OK) return s;
-            U1K(u1_self_drift_w, c->sc, hs, 0.0, 0.5 * hs, kc, 0);
-            if ((s = su2_drift_pass(c)) != LAT_OK) return s;
-            c->cur_su2 ^= 1;
-            U1K(u1_self_kick_w, c->sc, 0.5 * hs, c->p.alpha);
-            if ((s = su2_kick_sums(c)) != LAT_OK) return s;
-            U1K(u1_self_b_kick, c->sc, 0.5 * hs, kc);
-        }
-    c->t += (double)ns * h;
-    return LAT_OK;
-}
-
 lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir)
 {
-    if (c->u1 && c->p.expansion == LAT_EXP_SELF) return u1_step_self_vv(c, ns, dir);
-    if (c->su2 && c->p.expansion == LAT_EXP_SELF) return su2_step_self_vv(c, ns, dir);
+    if (c->p.expansion == LAT_EXP_SELF) return gauge_step_self_vv(c, ns, dir);
     const double h = dir * c->p.dt;
     const std::vector<double> w = vv_weights(c->p.integrator);
     const int64_t J = (int64_t)w.size(), M = J * ns;
@@ -3151,11 +2975,16 @@ lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir)
     }
     const double tend = t_start + (double)ns * h;
     const double ae = scale_at(c, tend);
-    lat_status s = c->su2 ? su2_launch(c, kSU2Kick, fixed ? su2_args_bg(c, 0.5 * prev, 0.0, ae, ae, false)
-                                                          : su2_args(c, 0.5 * prev, 0.0, false))
-                          : u1_launch(c, kU1Kick, fixed ? u1_args_bg(c, 0.5 * prev, 0.0, ae, ae, false)
-                                                        : u1_args(c, 0.5 * prev, 0.0, false));
+    // after an odd number of out-of-place passes the closing kick carries the
+    // positions back to the caller's arrays
+    const bool carry = c->su2 ? c->cur_su2 != 0 : c->cur_phi[0] != 0;
+    lat_status s = c->su2 ? su2_launch(c, kSU2Kick, su2_args_bg(c, 0.5 * prev, 0.0, ae, ae, carry))
+                          : u1_launch(c, kU1Kick, u1_args_bg(c, 0.5 * prev, 0.0, ae, ae, carry));
     if (s != LAT_OK) return s;
+    if (carry) {
+        if (c->su2) c->cur_su2 ^= 1;
+        else u1_flip(c);
+    }
     c->t = tend;
     return LAT_OK;
 }
@@ -3499,7 +3328,7 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
         // (c->adj_partials, free once the seed has finished), summed after the
         // sweep, so no pass ends with ticket releases; LATTICE_ENERGY_DEFER=0
         // keeps the per-pass ticketed sums (the same value to rounding)
-        double *slots = gauge_defer_on() ? c->adj_partials : nullptr;
+        double *slots = adjoint_defer_on() ? c->adj_partials : nullptr;
         if (slots) {
             hipLaunchKernelGGL(zero_doubles, dim3((nb + 255) / 256), dim3(256), 0, c->stream, slots, nb);
             HIPCHK(c, hipGetLastError());

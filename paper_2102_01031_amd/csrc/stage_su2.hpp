@@ -22,6 +22,7 @@
 // doublet and links are written out of place (the stencil reads the old values).
 #pragma once
 #include "common.hpp"
+#include "stage_u1.hpp"
 
 namespace lat {
 
@@ -49,19 +50,18 @@ struct SU2Args {
     // la3 = a^{3+alpha}, the staple force with lam1 = a^{alpha-1}; hdU is the
     // link drift weight (time times a^{alpha-1}).  All 1 (hdU = hd) at a = 1.
     double la1, la3, lam1, hdU;
-    // if not null: {ck, la1, la3, lam1, hd, hdU} from device memory (written by
+    // if not null: {ck, la1, la3, lam1, hd, hdU, ck2} from device memory (written by
     // the self-consistent scale-factor update)
     const double *dw;
     double *partials;
-    unsigned *ticket;
-    ScaleRecord *sc;
-    int defer;   // summing passes: leave the block partials, take no ticket
+    double ck2;  // a second kick weight, applied after the first (and after the sums of kSU2KickSums)
 };
 
-// kSU2Drift: the drift alone (su2_drift), for a step pass whose kick weight is zero.
-// kSU2KickSums: the kick-only pass that also leaves the volume sums [0, 5) of
-// the kicked state, as an energy pass with zero kick weight after it would (in
-// that pass's launch shape; Gauss terms not measured: the rest stays zero).
+// kSU2Drift: the drift alone (su2_drift).
+// kSU2KickSums: kicks by ck, forms the volume sums [0, 5) of that state and the momentum
+// sums [8, 10) before the kick, then kicks by ck2 (in the energy pass's launch shape;
+// Gauss terms not measured: the rest stays zero).  kSU2Kick with output arrays also
+// carries the doublet and the links over to them.
 enum SU2Mode : int { kSU2Step = 0, kSU2Kick = 1, kSU2Energy = 2, kSU2StepAoS = 3, kSU2Drift = 4, kSU2KickSums = 5 };
 
 // one 32-byte record through a 32-bit byte offset (valid while 32 N^3 < 2^32)
@@ -102,7 +102,7 @@ __device__ __forceinline__ void st4_s(double4 *base, unsigned i, double4 v)
         st4(base, i, v);
     }
 }
-constexpr int kSU2Sums = 8, kSU2Maxes = 3;
+constexpr int kSU2Sums = kU1Sums, kSU2Maxes = kU1Maxes;   // the U(1) passes' slots
 
 // unit quaternion q = (w, v) for the matrix w I - i v.sigma
 struct Q4 {
@@ -149,13 +149,13 @@ __device__ __forceinline__ void isospin(double a, double b, double c, double d, 
 // predecessors.
 // the pass weights of SU2Args, from device memory if SU2Args::dw is set
 struct SU2W {
-    double ck, la1, la3, lm1, hd, hdU;
+    double ck, la1, la3, lm1, hd, hdU, ck2;
 };
 
 __device__ inline SU2W su2_weights(const SU2Args &g)
 {
-    if (g.dw) return SU2W{g.dw[0], g.dw[1], g.dw[2], g.dw[3], g.dw[4], g.dw[5]};
-    return SU2W{g.ck, g.la1, g.la3, g.lam1, g.hd, g.hdU};
+    if (g.dw) return SU2W{g.dw[0], g.dw[1], g.dw[2], g.dw[3], g.dw[4], g.dw[5], g.dw[6]};
+    return SU2W{g.ck, g.la1, g.la3, g.lam1, g.hd, g.hdU, g.ck2};
 }
 
 template <int MODE, int NQ, bool NT>
@@ -251,17 +251,21 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
     for (int k = 0; k < 9; ++k) ev[k] = ld_s<NT>((const double *)g.E[k], n);
 
     if (MODE == kSU2Energy) {
-        double kin = 0.0, ke = 0.0;
+        double kin = 0.0, ke = 0.0, kin0 = 0.0, ke0 = 0.0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const double s = pv[k] + wt.ck * F[k];
             kin += s * s;
+            kin0 += pv[k] * pv[k];
         }
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
             const double s = ev[k] + wt.ck * FE[k];
             ke += s * s;
+            ke0 += ev[k] * ev[k];
         }
+        acc[8] += 0.5 * kin0;
+        acc[9] += 0.5 * ke0;
         acc[0] += 0.5 * kin;
         acc[1] += grad2 * inv_dx2 * 0.5;
         const double u = m2 - g.v * g.v;
@@ -312,29 +316,35 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
         acc[5] += Gn;
         acc[6] += sqrt(S2);
         acc[7] += Dn + Cn;
-        acc[8] = fmax(acc[8], Gn);
-        acc[9] = fmax(acc[9], Dn);
-        acc[10] = fmax(acc[10], Cn);
+        acc[10] = fmax(acc[10], Gn);
+        acc[11] = fmax(acc[11], Dn);
+        acc[12] = fmax(acc[12], Cn);
     } else {
         double pn[4], en[9];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             pn[k] = pv[k] + wt.ck * F[k];
-            st_s<NT>(g.pi[k], n, pn[k]);
+            st_s<NT>(g.pi[k], n, MODE == kSU2KickSums ? pn[k] + wt.ck2 * F[k] : pn[k]);
         }
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
             en[k] = ev[k] + wt.ck * FE[k];
-            st_s<NT>(g.E[k], n, en[k]);
+            st_s<NT>(g.E[k], n, MODE == kSU2KickSums ? en[k] + wt.ck2 * FE[k] : en[k]);
         }
         if constexpr (MODE == kSU2KickSums) {
-            // the terms the energy mode forms after this kick, where the stored
-            // momenta are pn, en and p + 0 F = p
-            double kin = 0.0, ke = 0.0;
+            double kin = 0.0, ke = 0.0, kin0 = 0.0, ke0 = 0.0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) kin += pn[k] * pn[k];
+            for (int k = 0; k < 4; ++k) {
+                kin += pn[k] * pn[k];
+                kin0 += pv[k] * pv[k];
+            }
 #pragma unroll
-            for (int k = 0; k < 9; ++k) ke += en[k] * en[k];
+            for (int k = 0; k < 9; ++k) {
+                ke += en[k] * en[k];
+                ke0 += ev[k] * ev[k];
+            }
+            acc[8] += 0.5 * kin0;
+            acc[9] += 0.5 * ke0;
             acc[0] += 0.5 * kin;
             acc[1] += grad2 * inv_dx2 * 0.5;
             const double u = m2 - g.v * g.v;
@@ -350,6 +360,19 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
                     mg += 2.0 * (Pij.x * Pij.x + Pij.y * Pij.y + Pij.z * Pij.z) / (1.0 + Pij.w);
                 }
             acc[4] += 2.0 * mg / (g.g * g.g * g.dx * g.dx * g.dx * g.dx);
+        }
+        if (MODE == kSU2Kick && g.phi_out[0]) {
+            st32(g.phi_out[0], n, a0);
+            st32(g.phi_out[1], n, b0);
+            st32(g.phi_out[2], n, c0);
+            st32(g.phi_out[3], n, d0);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                st32(g.U_out[4 * i], n, Ul[i].w);
+                st32(g.U_out[4 * i + 1], n, Ul[i].x);
+                st32(g.U_out[4 * i + 2], n, Ul[i].y);
+                st32(g.U_out[4 * i + 3], n, Ul[i].z);
+            }
         }
         if (MODE == kSU2Step || AOS) {
             const double4 po{a0 + wt.hd * pn[0], b0 + wt.hd * pn[1], c0 + wt.hd * pn[2], d0 + wt.hd * pn[3]};
@@ -390,12 +413,9 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
 }
 
 // Drift only, with the record's weights hd = dw[4], hdU = dw[5], on the plain
-// arrays, one site per thread: the doublet phi + hd pi and the links
-// exp(-i hdU g dx E.T) U, the step pass's drift formed by the same expressions
-// (the compiler may contract them differently: equal to rounding).  The
-// self-consistent steps' drift pass has zero kick weight, where a step pass
-// computes the forces for nothing (p + 0 F = p) and rewrites the momenta and
-// electric fields unchanged: this reads 29 arrays and writes 16.
+// arrays, one site per thread and in place (a site's drift reads nothing else): the
+// doublet phi + hd pi and the links exp(-i hdU g dx E.T) U, the step pass's drift
+// formed by the same expressions.  Reads 29 arrays and writes 16, with no forces.
 __global__ void __launch_bounds__(256) su2_drift(const SU2Args g, unsigned vol)
 {
     const unsigned n = blockIdx.x * 256u + threadIdx.x;
@@ -443,7 +463,6 @@ __global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2))
     constexpr int NT = TX * TY;
     constexpr int NQ = kSU2Sums + kSU2Maxes;
     __shared__ double lds_red[(NT / 64) * NQ];
-    __shared__ int last_flag;
 
     const int tid = threadIdx.x;
     const int tx = tid % TX, ty = tid / TX;
@@ -488,55 +507,7 @@ __global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2))
     }
 
     if constexpr (MODE == kSU2Energy || MODE == kSU2KickSums) {
-        // block reduction: sums for [0, kSU2Sums), maxes for the rest; the last
-        // block (ticket) combines the block partials in block order
-        const int lane = tid & 63, w = tid >> 6;
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            const double r = k < kSU2Sums ? wave_sum(acc[k]) : wave_max(acc[k]);
-            if (lane == 0) lds_red[w * NQ + k] = r;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            for (int k = 0; k < NQ; ++k) {
-                double r = 0.0;
-                for (int i = 0; i < NT / 64; ++i)
-                    r = k < kSU2Sums ? r + lds_red[i * NQ + k] : fmax(r, lds_red[i * NQ + k]);
-                store_agent(&g.partials[(size_t)lid * NQ + k], r);
-            }
-            // defer: the block partials are combined by a kernel after this one
-            last_flag = g.defer ? 0 : (ticket_arrive(g.ticket, gridDim.x) ? 1 : 0);
-        }
-        __syncthreads();
-        if (last_flag) {
-            const int nb = gridDim.x;
-            double part[NQ];
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) part[k] = 0.0;
-            for (int i = tid; i < nb; i += NT) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    const double v = load_agent(&g.partials[(size_t)i * NQ + k]);
-                    part[k] = k < kSU2Sums ? part[k] + v : fmax(part[k], v);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                const double r = k < kSU2Sums ? wave_sum(part[k]) : wave_max(part[k]);
-                if (lane == 0) lds_red[w * NQ + k] = r;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                for (int k = 0; k < NQ; ++k) {
-                    double r = 0.0;
-                    for (int i = 0; i < NT / 64; ++i)
-                        r = k < kSU2Sums ? r + lds_red[i * NQ + k] : fmax(r, lds_red[i * NQ + k]);
-                    if (k < kSU2Sums) g.sc->sums[k] = r;
-                    else g.sc->maxes[k - kSU2Sums] = r;
-                }
-                __hip_atomic_store(g.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        u1_block_sums(acc, lds_red, &g.partials[(size_t)lid * NQ]);
     }
 }
 

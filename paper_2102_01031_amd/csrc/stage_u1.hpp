@@ -41,21 +41,40 @@ struct U1Args {
     // la3 = a^{3+alpha}, the magnetic force with lam1 = a^{alpha-1}; hdA is the
     // drift weight of A (time times a^{alpha-1}).  All 1 (hdA = hd) at a = 1.
     double la1, la3, lam1, hdA;
-    // if not null: {ck, la1, la3, lam1, hd, hdA} from device memory (written by
+    // if not null: {ck, la1, la3, lam1, hd, hdA, ck2} from device memory (written by
     // the self-consistent scale-factor kernels), in place of the values above
     const double *dw;
     double *partials;
-    unsigned *ticket;
-    ScaleRecord *sc;
-    int defer;   // summing passes: leave the block partials, take no ticket
+    double ck2;  // a second kick weight, applied after the first (and after the sums of kU1KickSums)
 };
 
-// kU1KickSums (row kernel only): the kick-only pass that also leaves the volume
-// sums [0, 5) of the kicked state, as an energy pass with zero kick weight after
-// it would (Gauss terms not measured: sums [5, 8) and the maxes are zero)
-// kU1Drift: the drift alone (u1_drift), for a step pass whose kick weight is zero
+// kU1KickSums (u1_span only): kicks by ck, forms the volume sums [0, 5) of that state and
+// the momentum sums [8, 10) before the kick, then kicks by ck2 (Gauss terms not
+// measured: sums [5, 8) and the maxes are zero).  kU1Kick with output arrays also
+// carries psi and A over to them.  kU1Drift: the drift alone (u1_drift).
 enum U1Mode : int { kU1Step = 0, kU1Kick = 1, kU1Energy = 2, kU1KickSums = 3, kU1Drift = 4 };
-constexpr int kU1Sums = 8, kU1Maxes = 3;
+// Volume sums of a summing pass: 0 scalar kinetic, 1 gradient, 2 potential, 3 electric,
+// 4 magnetic, 5-7 Gauss means, 8 and 9 the kinetic and electric sums of the momenta
+// before the pass's kick; then the Gauss maxima.
+constexpr int kU1Sums = 10, kU1Maxes = 3;
+
+// the block's sums and maxima of acc to out (thread 0)
+template <int NQ>
+__device__ inline void u1_block_sums(double (&acc)[NQ], double *lds_red, double *out)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x / 64;
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+        const double r = k < kU1Sums ? wave_sum(acc[k]) : wave_max(acc[k]);
+        if (lane == 0) lds_red[w * NQ + k] = r;
+    }
+    __syncthreads();
+    if (tid < NQ) {
+        double r = 0.0;
+        for (int i = 0; i < nw; ++i) r = tid < kU1Sums ? r + lds_red[i * NQ + tid] : fmax(r, lds_red[i * NQ + tid]);
+        out[tid] = r;
+    }
+}
 
 __device__ inline size_t u1_at(int N, int x, int y, int z)
 {
@@ -68,7 +87,6 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
     constexpr int NT = TX * TY;
     constexpr int NQ = kU1Sums + kU1Maxes;
     __shared__ double lds_red[(NT / 64) * NQ];
-    __shared__ int last_flag;
 
     const int tid = threadIdx.x;
     const int tx = tid % TX, ty = tid / TX;
@@ -138,7 +156,7 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
                 grad2 += dr * dr + di * di;
             }
         }
-        double ck = g.ck, la1 = g.la1, la3 = g.la3, lm1 = g.lam1, hdP = g.hd, hdA = g.hdA;
+        double ck = g.ck, ck2 = g.ck2, la1 = g.la1, la3 = g.la3, lm1 = g.lam1, hdP = g.hd, hdA = g.hdA;
         if (g.dw) {
             ck = g.dw[0];
             la1 = g.dw[1];
@@ -146,6 +164,7 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
             lm1 = g.dw[3];
             hdP = g.dw[4];
             hdA = g.dw[5];
+            ck2 = g.dw[6];
         }
         const double m2 = 0.5 * (pr * pr + pim * pim);
         const double vp = 0.5 * g.lam * (m2 - g.v * g.v);
@@ -186,20 +205,33 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
             t[5] = fabs(G);
             t[6] = fabs(div + charge);
             t[7] = fabs(div) + fabs(charge);
-            t[8] = fabs(G);
-            t[9] = fabs(div);
-            t[10] = fabs(charge);
+            t[8] = 0.5 * (p0 * p0 + p1 * p1);
+            t[9] = (pa[0] * pa[0] + pa[1] * pa[1] + pa[2] * pa[2]) / (2.0 * g.kappa_g);
+            t[10] = fabs(G);
+            t[11] = fabs(div);
+            t[12] = fabs(charge);
 #pragma unroll
             for (int k = 0; k < NQ; ++k) acc[k] = k < kU1Sums ? acc[k] + t[k] : fmax(acc[k], t[k]);
         } else {
-            const double q0 = p0 + ck * F0, q1 = p1 + ck * F1;
+            double q0 = p0 + ck * F0, q1 = p1 + ck * F1;
+            if (MODE == kU1Kick) {
+                q0 += ck2 * F0;
+                q1 += ck2 * F1;
+            }
             g.pi[0][n] = q0;
             g.pi[1][n] = q1;
             double qa[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 qa[i] = pa[i] + ck * FA[i];
+                if (MODE == kU1Kick) qa[i] += ck2 * FA[i];
                 g.piA[i][n] = qa[i];
+            }
+            if (MODE == kU1Kick && g.phi_out[0]) {
+                g.phi_out[0][n] = pr;
+                g.phi_out[1][n] = pim;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) g.A_out[i][n] = g.A_in[i][n];
             }
             if (MODE == kU1Step) {
                 g.phi_out[0][n] = pr + hdP * q0;
@@ -212,65 +244,16 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
     }
 
     if constexpr (MODE == kU1Energy) {
-        // block reduction: sums for [0, kU1Sums), maxes for the rest
-        const int lane = tid & 63, w = tid >> 6;
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            const double r = k < kU1Sums ? wave_sum(acc[k]) : wave_max(acc[k]);
-            if (lane == 0) lds_red[w * NQ + k] = r;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            for (int k = 0; k < NQ; ++k) {
-                double r = 0.0;
-                for (int i = 0; i < NT / 64; ++i)
-                    r = k < kU1Sums ? r + lds_red[i * NQ + k] : fmax(r, lds_red[i * NQ + k]);
-                store_agent(&g.partials[(size_t)lid * NQ + k], r);
-            }
-            // defer: the block partials are combined by a kernel after this one
-            last_flag = g.defer ? 0 : (ticket_arrive(g.ticket, gridDim.x) ? 1 : 0);
-        }
-        __syncthreads();
-        if (last_flag) {
-            const int nb = gridDim.x;
-            double part[NQ];
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) part[k] = 0.0;
-            for (int i = tid; i < nb; i += NT) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    const double v = load_agent(&g.partials[(size_t)i * NQ + k]);
-                    part[k] = k < kU1Sums ? part[k] + v : fmax(part[k], v);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                const double r = k < kU1Sums ? wave_sum(part[k]) : wave_max(part[k]);
-                if (lane == 0) lds_red[w * NQ + k] = r;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                for (int k = 0; k < NQ; ++k) {
-                    double r = 0.0;
-                    for (int i = 0; i < NT / 64; ++i)
-                        r = k < kU1Sums ? r + lds_red[i * NQ + k] : fmax(r, lds_red[i * NQ + k]);
-                    if (k < kU1Sums) g.sc->sums[k] = r;
-                    else g.sc->maxes[k - kU1Sums] = r;
-                }
-                __hip_atomic_store(g.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        u1_block_sums(acc, lds_red, &g.partials[(size_t)lid * NQ]);
     }
 }
 
 // Drift only, with the record's weights hd = dw[4], hdA = dw[5]: phi' = phi + hd pi,
-// A_i' = A_i + hdA piA_i into the other position buffers, one site per thread.
-// The self-consistent steps' drift pass has zero kick weight, where a step
-// pass forms the same values (p + 0 F = p) and rewrites the momenta unchanged:
-// this reads 10 and writes 5 arrays, with no forces.
-__global__ void __launch_bounds__(256) u1_drift(const U1Args g, unsigned vol)
+// A_i' = A_i + hdA piA_i, one site per thread.  A site's drift reads nothing else, so
+// it runs in place (15 arrays of traffic, no forces, no copy back after the call).
+__global__ void __launch_bounds__(256) u1_drift(const U1Args g, size_t vol)
 {
-    const unsigned n = blockIdx.x * 256u + threadIdx.x;
+    const size_t n = (size_t)blockIdx.x * 256u + threadIdx.x;
     if (n >= vol) return;
     const double hd = g.dw[4], hdA = g.dw[5];
 #pragma unroll
@@ -304,131 +287,143 @@ __device__ inline double u1_kernel_b(double a, const double *S, const U1SelfCons
            ((al - 2.0) * EK + al * EG + (al - 1.0) * EA + (al + 1.0) * EV);
 }
 
-// kick weights at the record's a: {ck, a^{1+alpha}, a^{3+alpha}, a^{alpha-1}, 0, 0}
-__global__ void u1_self_kick_w(ScaleRecord *S, double ck, double alpha)
+// weights of a kick at the record's a: {ck, a^{1+alpha}, a^{3+alpha}, a^{alpha-1}, 0, 0, ck2}
+__global__ void u1_self_kick_w(ScaleRecord *S, double ck, double ck2, double alpha)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        const double a = S->a;
-        S->w[0] = ck;
-        S->w[1] = pow(a, 1.0 + alpha);
-        S->w[2] = pow(a, 3.0 + alpha);
-        S->w[3] = pow(a, alpha - 1.0);
-        S->w[4] = 0.0;
-        S->w[5] = 0.0;
-    }
+    const int l = threadIdx.x;
+    const double a = S->a;
+    const double p = pow(a, l == 1 ? 1.0 + alpha : (l == 2 ? 3.0 + alpha : alpha - 1.0));
+    if (l < 7) S->w[l] = l == 0 ? ck : (l == 6 ? ck2 : (l < 4 ? p : 0.0));
 }
 
-// keep the sums of the state before a kick (sums[8..12])
-__global__ void u1_self_stash(ScaleRecord *S)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        for (int k = 0; k < 5; ++k) S->sums[8 + k] = S->sums[k];
-}
+// The scale-factor update after a summing pass, in the order
+//   b += cB K_a(a, before the kick); b += cA K_a(a, after it); b += cA2 K_a(a, after it)
+// (leapfrog, reading A3: cB = cA = h/2, or only cA after a start from synchronised
+// momenta; velocity-Verlet, reading R1: cA closes the sub-step behind, cA2 opens the
+// one ahead), a' = a + h b, then the weights of the drift {h abar^{alpha-3},
+// h abar^{alpha-1}}, abar = (a + a')/2, and of the next kicks c1, c2 at a'.
+struct GaugeUpdate {
+    int on;
+    double cB, cA, cA2, h, c1, c2;
+};
 
-// b += w K_a(a, sums[0..4]) (the sync's half kick, or a velocity-Verlet half kick)
-__global__ void u1_self_b_kick(ScaleRecord *S, double w, U1SelfConst k)
+// The block partials of a summing pass of the gauge models (kU1Sums sums, then
+// kU1Maxes maxima per block), combined by one block in a fixed order into the record;
+// then the update above, its five powers side by side in the lanes of one wave, and,
+// with `host`, a copy of the record in pinned host memory.  One launch of one block
+// behind each pass instead of four one-thread kernels (5 us each at any size).
+constexpr int kGaugeFinishThreads = 256;
+__global__ void __launch_bounds__(kGaugeFinishThreads) gauge_finish(const double *partials, int nb, ScaleRecord *S,
+                                                                    const GaugeUpdate u, const U1SelfConst k,
+                                                                    ScaleRecord *host)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) S->b += w * u1_kernel_b(S->a, S->sums, k);
-}
-
-// Leapfrog (reading A3): b += cL K_a(before, sums[8..12]) + cR K_a(after, sums[0..4]);
-// velocity-Verlet (reading R1, cL = 0): b += cR K_a(sums[0..4]).  Then a' = a + h b and
-// the drift weights {0, 1, 1, 1, h abar^{alpha-3}, h abar^{alpha-1}}, abar = (a + a')/2.
-// Every call leaves the momentum sums of the kicked state (sums[0], sums[3]) in
-// sums[8] and sums[11]: the drift that follows moves only the positions, so they
-// are the next step's momentum sums before its kick.  With carry != 0 the sums
-// before this step's kick were not measured: their momentum parts are those the
-// previous call left, and their position parts (sums[1], [2], [4]) are the
-// after-kick ones, the kick having moved only the momenta.  An energy pass with
-// zero kick weight sums p + 0 F = p, so the carried sums equal measured ones bit
-// for bit.
-__global__ void u1_self_drift_w(ScaleRecord *S, double h, double cL, double cR, U1SelfConst k, int carry)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        if (carry) {
-            S->sums[9] = S->sums[1];
-            S->sums[10] = S->sums[2];
-            S->sums[12] = S->sums[4];
+    constexpr int NQ = kU1Sums + kU1Maxes, NT = kGaugeFinishThreads;
+    __shared__ double lds_red[(NT / 64) * NQ];
+    __shared__ double tot[NQ];
+    const int tid = threadIdx.x;
+    double part[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) part[q] = 0.0;
+    for (int i = tid; i < nb; i += NT) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const double v = partials[(size_t)i * NQ + q];
+            part[q] = q < kU1Sums ? part[q] + v : fmax(part[q], v);
         }
+    }
+    u1_block_sums(part, lds_red, tot);
+    __syncthreads();
+    if (tid < kU1Sums) S->sums[tid] = tot[tid];
+    else if (tid < NQ) S->maxes[tid - kU1Sums] = tot[tid];
+    if (tid >= 64) return;
+    if (u.on) {
         const double a = S->a;
         double b = S->b;
-        if (cL != 0.0) b += cL * u1_kernel_b(a, S->sums + 8, k);
-        b += cR * u1_kernel_b(a, S->sums, k);
-        const double a1 = a + h * b;
-        const double am = 0.5 * (a + a1);
-        S->w[0] = 0.0;
-        S->w[1] = 1.0;
-        S->w[2] = 1.0;
-        S->w[3] = 1.0;
-        S->w[4] = h * pow(am, k.alpha - 3.0);
-        S->w[5] = h * pow(am, k.alpha - 1.0);
-        S->a = a1;
-        S->b = b;
-        S->sums[8] = S->sums[0];
-        S->sums[11] = S->sums[3];
+        const double after[5] = {tot[0], tot[1], tot[2], tot[3], tot[4]};
+        const double before[5] = {tot[8], tot[1], tot[2], tot[9], tot[4]};
+        if (u.cB != 0.0) b += u.cB * u1_kernel_b(a, before, k);
+        if (u.cA != 0.0) b += u.cA * u1_kernel_b(a, after, k);
+        if (u.cA2 != 0.0) b += u.cA2 * u1_kernel_b(a, after, k);
+        const double a1 = a + u.h * b, am = 0.5 * (a + a1);
+        const double ex = tid == 1 ? 1.0 + k.alpha : (tid == 2 ? 3.0 + k.alpha : (tid == 4 ? k.alpha - 3.0 : k.alpha - 1.0));
+        const double p = pow(tid < 4 ? a1 : am, ex);
+        if (tid < 7) S->w[tid] = tid == 0 ? u.c1 : (tid == 6 ? u.c2 : (tid < 4 ? p : u.h * p));
+        if (tid == 0) {
+            S->a = a1;
+            S->b = b;
+        }
+    }
+    if (host) {
+        __threadfence();   // the wave's stores to the record before its loads of them
+        static_assert(sizeof(ScaleRecord) == 32 * sizeof(double), "record size");
+        if (tid < 32) ((double *)host)[tid] = load_agent((const double *)S + tid);
     }
 }
 
-// Leapfrog pass for N = 64 * XS (XS in {1, 2}) that shares the transcendental
-// work between neighbouring sites.  A block owns TY whole x rows and marches z
-// over [z0, z1); each thread owns one site of each plane (row y0 + w / XS,
-// x = 64 (w % XS) + lane for wavefront w).  Per plane every site evaluates its
-// own three plaquette sines sin theta_ij(n) and its three link phases
-// (cos, sin)(e dx A_i(n)) once; the values at n - x and n - y are read from
-// LDS, those at n - z are carried in registers from the previous plane, and
-// the row y0 - 1 below the block is evaluated by the block's threads, one
-// operation each.  Every angle is formed by the same expression, in the same
-// order, as in u1_stage: the same arithmetic without the repeated sines.
-template <int XS, int TY, int MODE>
-__global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
-{
-    constexpr int NT = 64 * XS * TY;
-    constexpr int NX = 64 * XS;               // == N
-    constexpr int R = TY + 2;                 // LDS rows stand for y0 - 1 .. y0 + TY
-    constexpr int NH = 2 * NX;                // halo cells per plane: LDS rows 0 and TY + 1
-    constexpr int HPT = (NH + NT - 1) / NT;
-    constexpr int NOP = 3 * NX;               // halo-row transcendental operations per plane
-    constexpr int OPT = (NOP + NT - 1) / NT;
+// The passes of u1_stage for lattices whose block rows fit LDS (N up to 440), with
+// the transcendental work shared between neighbouring sites.  A block owns TY whole
+// x rows, one thread per site (threads rounded up to whole wavefronts), and marches
+// z over [z0, z1).  Per plane every site evaluates its own three plaquette sines
+// sin theta_ij(n) and its three link phases (cos, sin)(e dx A_i(n)) once; the values
+// at n - x and n - y are read from LDS, those at n - z are carried in registers from
+// the previous plane, and the row y0 - 1 below the block is evaluated by the block's
+// threads, one operation each.  Every angle is formed by the same expression, in the
+// same order, as in u1_stage, which evaluates 9 sines and 6 phases per site and reads
+// 44 values.  Bound by memory at 128^3 (58 us per step pass, 5.8 TB/s; 102 us while
+// the phases came back from a call through pointers, that is, through scratch), by
+// the sines and the halo row below it: 96^3 step pass 30 us, the kick pass of
+// u1_stage 47, its energy pass 110 against 45.
+constexpr int kU1SpanThreads = 512;
+// LDS of a block of TY rows (doubles)
+inline size_t u1_span_lds(int N, int TY) { return (size_t)N * (17 * (size_t)TY + 24); }
 
-    // psi and A of the current plane, double-buffered by plane parity so that
-    // storing plane z + 1 cannot race with the last reads of plane z
-    __shared__ double s_p0[2][R * NX], s_p1[2][R * NX];           // psi, rows 0 .. TY+1
-    __shared__ double s_ax[2][R * NX], s_az[2][R * NX];           // A_x, A_z, rows 0 .. TY+1
-    __shared__ double s_ay[2][(TY + 1) * NX], s_ayn[2][NX];       // A_y rows 0 .. TY; A_y(row 0, z+1)
-    __shared__ double s_sxy[(TY + 1) * NX], s_syz[(TY + 1) * NX]; // rows 0 .. TY
-    __shared__ double s_cy[(TY + 1) * NX], s_sy[(TY + 1) * NX];   // phase of A_y, rows 0 .. TY
-    __shared__ double s_sxz[TY * NX];                             // own rows (index row - 1)
-    __shared__ double s_cx[TY * NX], s_sx[TY * NX];               // phase of A_x, own rows
-    __shared__ double s_cz[TY * NX], s_sz[TY * NX];               // phase of A_z, own rows
+template <int HPT, int MODE>
+__global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY)
+{
+    extern __shared__ double u1_lds[];
     constexpr bool EN = MODE == kU1Energy || MODE == kU1KickSums;   // ends with the reduction
     constexpr int NQ = kU1Sums + kU1Maxes;
-    __shared__ double lds_red[EN ? (NT / 64) * NQ : 1];
-    __shared__ int last_flag;
+    __shared__ double lds_red[EN ? (kU1SpanThreads / 64) * NQ : 1];
 
+    const int N = g.N, NT = blockDim.x;
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
-    const int r = w / XS + 1;                 // LDS row of this thread's site
-    const int x = (w % XS) * 64 + lane;
-    const int xm = (x - 1) & (NX - 1), xp = (x + 1) & (NX - 1);
-    const int ro = r * NX + x;                // this site in rows 0 .. TY+1 arrays
-    const int wo = (r - 1) * NX + x;          // this site in own-row arrays
-    const int N = NX;
     const int lid = xcd_logical_block(blockIdx.x, gridDim.x);
     const int chunks = (N + g.zc - 1) / g.zc;
     const int bz = lid % chunks;
     const int by = lid / chunks;
-    const int y0 = by * TY;
+    const int y0 = by * TY, nr = min(TY, N - y0);   // the last block may own fewer rows
     const int z0 = bz * g.zc;
     const int z1 = min(z0 + g.zc, N);
-    const unsigned NN = (unsigned)N * (unsigned)N;   // N^3 < 2^32
+    const bool own = tid < nr * N;            // threads past the rows load and store nothing
+    const int r = own ? tid / N + 1 : 1;      // LDS row of this thread's site (rows 0 .. nr + 1 stand for y0 - 1 .. y0 + nr)
+    const int x = own ? tid - (r - 1) * N : 0;
+    const int xm = x == 0 ? N - 1 : x - 1, xp = x == N - 1 ? 0 : x + 1;
+    const int ro = r * N + x;                 // this site in rows 0 .. nr + 1 arrays
+    const int wo = (r - 1) * N + x;           // this site in own-row arrays
+
+    // LDS: psi and A of the current plane, double-buffered by plane parity so that
+    // storing plane z + 1 cannot race with the last reads of plane z; then the
+    // sines and phases
+    const int RN = (TY + 2) * N, RM = (TY + 1) * N, RO = TY * N;
+    double *const s_p0_ = u1_lds, *const s_p1_ = s_p0_ + 2 * RN, *const s_ax_ = s_p1_ + 2 * RN,
+                 *const s_az_ = s_ax_ + 2 * RN;                        // rows 0 .. TY + 1
+    double *const s_ay_ = s_az_ + 2 * RN, *const s_ayn_ = s_ay_ + 2 * RM;   // A_y rows 0 .. TY; A_y(row 0, z + 1)
+    double *const s_sxy = s_ayn_ + 2 * N, *const s_syz = s_sxy + RM;   // rows 0 .. TY
+    double *const s_cy = s_syz + RM, *const s_sy = s_cy + RM;          // phase of A_y, rows 0 .. TY
+    double *const s_sxz = s_sy + RM;                                   // own rows (index row - 1)
+    double *const s_cx = s_sxz + RO, *const s_sx = s_cx + RO;          // phase of A_x, own rows
+
+    const unsigned NN = (unsigned)N * (unsigned)N;   // 8 N^3 < 2^32
     const unsigned so = (unsigned)((y0 + r - 1) * N + x);   // site offset within a plane
     const int yb = (y0 == 0 ? N - 1 : y0 - 1) * N;
-    const int yt = ((y0 + TY) % N) * N;
+    const int yt = ((y0 + nr) % N) * N;
+    const int NH = 2 * N, NOP = 3 * N;        // halo cells and halo-row operations per plane
 
     const double edx = g.e * g.dx;
     const double inv_dx2 = 1.0 / (g.dx * g.dx);
     const double inv_edx3 = 1.0 / (g.e * g.dx * g.dx * g.dx);
-    double ck = g.ck, la1 = g.la1, la3 = g.la3, lm1 = g.lam1, hd = g.hd, hdA = g.hdA;
+    double ck = g.ck, ck2 = g.ck2, la1 = g.la1, la3 = g.la3, lm1 = g.lam1, hd = g.hd, hdA = g.hdA;
     if (g.dw) {
         ck = g.dw[0];
         la1 = g.dw[1];
@@ -436,9 +431,10 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
         lm1 = g.dw[3];
         hd = g.dw[4];
         hdA = g.dw[5];
+        ck2 = g.dw[6];
     }
 
-    // halo cells: c < NX is row 0 (y0 - 1), else row TY + 1 (y0 + TY)
+    // halo cells: c < N is row 0 (y0 - 1), else row nr + 1 (y0 + nr)
     int hrow[HPT], hx[HPT];
     unsigned hoff[HPT];
     bool hval[HPT];
@@ -446,9 +442,9 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
     for (int j = 0; j < HPT; ++j) {
         const int c = tid + j * NT;
         hval[j] = c < NH;
-        const bool bot = c < NX;
-        hx[j] = bot ? c : c - NX;
-        hrow[j] = bot ? 0 : TY + 1;
+        const bool bot = c < N;
+        hx[j] = bot ? c : c - N;
+        hrow[j] = bot ? 0 : nr + 1;
         hoff[j] = hval[j] ? (unsigned)((bot ? yb : yt) + hx[j]) : 0u;
     }
 
@@ -466,6 +462,7 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
         const unsigned o0 = (unsigned)z0 * NN;
         const unsigned o1 = (unsigned)((z0 + 1) % N) * NN;
         double am[3];
+        double *const s_az1 = s_az_ + RN;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             wm[c] = ld32(g.phi_in[c], om + so);
@@ -478,7 +475,7 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
             a0[i] = ld32(g.A_in[i], o0 + so);
             a1[i] = ld32(g.A_in[i], o1 + so);
         }
-        s_az[1][ro] = am[2];
+        if (own) s_az1[ro] = am[2];
 #pragma unroll
         for (int j = 0; j < HPT; ++j) {
             hp0[j] = hp1[j] = hax[j] = hay[j] = haz[j] = hayn[j] = 0.0;
@@ -491,13 +488,13 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
                     hay[j] = ld32(g.A_in[1], o0 + hoff[j]);
                     hayn[j] = ld32(g.A_in[1], o1 + hoff[j]);
                 } else {
-                    s_az[1][(TY + 1) * NX + hx[j]] = ld32(g.A_in[2], om + hoff[j]);
+                    s_az1[(nr + 1) * N + hx[j]] = ld32(g.A_in[2], om + hoff[j]);
                 }
             }
         }
         __syncthreads();
-        const double txz = edx * ((s_az[1][r * NX + xp] - am[2]) - a0[0] + am[0]);
-        const double tyz = edx * ((s_az[1][(r + 1) * NX + x] - am[2]) - a0[1] + am[1]);
+        const double txz = edx * ((s_az1[r * N + xp] - am[2]) - a0[0] + am[0]);
+        const double tyz = edx * ((s_az1[(r + 1) * N + x] - am[2]) - a0[1] + am[1]);
         sxzm = lat_sin(txz);
         syzm = lat_sin(tyz);
         lat_sincos(edx * am[2], &szm, &czm);
@@ -507,23 +504,27 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
     for (int z = z0; z < z1; ++z) {
         const unsigned oz = (unsigned)z * NN;
         const int b = (z - z0) & 1;
+        double *const s_p0 = s_p0_ + b * RN, *const s_p1 = s_p1_ + b * RN, *const s_ax = s_ax_ + b * RN,
+                     *const s_az = s_az_ + b * RN, *const s_ay = s_ay_ + b * RM, *const s_ayn = s_ayn_ + b * N;
         // (A) plane z into LDS
-        s_p0[b][ro] = w0[0];
-        s_p1[b][ro] = w0[1];
-        s_ax[b][ro] = a0[0];
-        s_ay[b][ro] = a0[1];
-        s_az[b][ro] = a0[2];
+        if (own) {
+            s_p0[ro] = w0[0];
+            s_p1[ro] = w0[1];
+            s_ax[ro] = a0[0];
+            s_ay[ro] = a0[1];
+            s_az[ro] = a0[2];
+        }
 #pragma unroll
         for (int j = 0; j < HPT; ++j) {
             if (hval[j]) {
-                const int hs = hrow[j] * NX + hx[j];
-                s_p0[b][hs] = hp0[j];
-                s_p1[b][hs] = hp1[j];
-                s_ax[b][hs] = hax[j];
-                s_az[b][hs] = haz[j];
+                const int hs = hrow[j] * N + hx[j];
+                s_p0[hs] = hp0[j];
+                s_p1[hs] = hp1[j];
+                s_ax[hs] = hax[j];
+                s_az[hs] = haz[j];
                 if (hrow[j] == 0) {
-                    s_ay[b][hx[j]] = hay[j];
-                    s_ayn[b][hx[j]] = hayn[j];
+                    s_ay[hx[j]] = hay[j];
+                    s_ayn[hx[j]] = hayn[j];
                 }
             }
         }
@@ -560,85 +561,78 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
         // (B) own plaquette sines and link phases into LDS; then the halo
         // row's, one operation per thread
         double th[3];   // own plaquette angles (the energy mode's magnetic term)
+        double ss[3], ps[3], pc[3];   // their sines; sine and cosine of the link phases
         {
-            const double txy = edx * ((s_ay[b][r * NX + xp] - a0[1]) - s_ax[b][(r + 1) * NX + x] + a0[0]);
-            const double txz = edx * ((s_az[b][r * NX + xp] - a0[2]) - a1[0] + a0[0]);
-            const double tyz = edx * ((s_az[b][(r + 1) * NX + x] - a0[2]) - a1[1] + a0[1]);
+            const double txy = edx * ((s_ay[r * N + xp] - a0[1]) - s_ax[(r + 1) * N + x] + a0[0]);
+            const double txz = edx * ((s_az[r * N + xp] - a0[2]) - a1[0] + a0[0]);
+            const double tyz = edx * ((s_az[(r + 1) * N + x] - a0[2]) - a1[1] + a0[1]);
             th[0] = txy;
             th[1] = txz;
             th[2] = tyz;
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const double t = j == 0 ? txy : (j == 1 ? txz : tyz);
-                double *dst = j == 0 ? &s_sxy[ro] : (j == 1 ? &s_sxz[wo] : &s_syz[ro]);
-                *dst = lat_sin(t);
+                ss[j] = lat_sin(t);
             }
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double t = edx * (j == 0 ? a0[0] : (j == 1 ? a0[1] : a0[2]));
-                double sv, cv;
-                lat_sincos(t, &sv, &cv);
-                const int sl = j == 1 ? ro : wo;
-                double *ds = j == 0 ? s_sx : (j == 1 ? s_sy : s_sz);
-                double *dc = j == 0 ? s_cx : (j == 1 ? s_cy : s_cz);
-                ds[sl] = sv;
-                dc[sl] = cv;
+            for (int j = 0; j < 3; ++j) lat_sincos(edx * a0[j], &ps[j], &pc[j]);
+            if (own) {
+                s_sxy[ro] = ss[0];
+                s_sxz[wo] = ss[1];
+                s_syz[ro] = ss[2];
+                s_sx[wo] = ps[0];
+                s_cx[wo] = pc[0];
+                s_sy[ro] = ps[1];
+                s_cy[ro] = pc[1];
             }
         }
-#pragma unroll
-        for (int j = 0; j < OPT; ++j) {
-            const int id = tid + j * NT;
-            if (id < NOP) {
-                const int op = id / NX, hxo = id % NX;
-                const int hxp = (hxo + 1) & (NX - 1);
-                if (op == 0) {
-                    double sv, cv;
-                    lat_sincos(edx * s_ay[b][hxo], &sv, &cv);
-                    s_sy[hxo] = sv;
-                    s_cy[hxo] = cv;
-                } else if (op == 1) {
-                    s_sxy[hxo] = lat_sin(edx * ((s_ay[b][hxp] - s_ay[b][hxo]) - s_ax[b][NX + hxo] + s_ax[b][hxo]));
-                } else {
-                    s_syz[hxo] = lat_sin(edx * ((s_az[b][NX + hxo] - s_az[b][hxo]) - s_ayn[b][hxo] + s_ay[b][hxo]));
-                }
+        for (int id = tid; id < NOP; id += NT) {
+            const int op = id / N, hxo = id - op * N;
+            const int hxp = hxo == N - 1 ? 0 : hxo + 1;
+            if (op == 0) {
+                double sv, cv;
+                lat_sincos(edx * s_ay[hxo], &sv, &cv);
+                s_sy[hxo] = sv;
+                s_cy[hxo] = cv;
+            } else if (op == 1) {
+                s_sxy[hxo] = lat_sin(edx * ((s_ay[hxp] - s_ay[hxo]) - s_ax[N + hxo] + s_ax[hxo]));
+            } else {
+                s_syz[hxo] = lat_sin(edx * ((s_az[N + hxo] - s_az[hxo]) - s_ayn[hxo] + s_ay[hxo]));
             }
         }
         __syncthreads();
 
         // (C) forces, kick, drift
-        {
+        if (own) {
             const unsigned o = oz + so;
             double pq[2], pa[3];
 #pragma unroll
             for (int c = 0; c < 2; ++c) pq[c] = ld32(g.pi[c], o);
 #pragma unroll
             for (int i = 0; i < 3; ++i) pa[i] = ld32(g.piA[i], o);
-            const double sxy = s_sxy[ro], sxz = s_sxz[wo], syz = s_syz[ro];
-            const double mag[3] = {(sxy - s_sxy[ro - NX]) + (sxz - sxzm),
-                                   (-sxy + s_sxy[r * NX + xm]) + (syz - syzm),
-                                   (-sxz + s_sxz[(r - 1) * NX + xm]) + (-syz + s_syz[ro - NX])};
+            const double sxy = ss[0], sxz = ss[1], syz = ss[2];
+            const double mag[3] = {(sxy - s_sxy[ro - N]) + (sxz - sxzm),
+                                   (-sxy + s_sxy[r * N + xm]) + (syz - syzm),
+                                   (-sxz + s_sxz[(r - 1) * N + xm]) + (-syz + s_syz[ro - N])};
             const double pr = w0[0], pim = w0[1];
             double d2r = 0.0, d2i = 0.0, J[3], grad2 = 0.0;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 double qr, qi, rr, ri, sm, cm;
                 if (i == 0) {
-                    qr = s_p0[b][r * NX + xp]; qi = s_p1[b][r * NX + xp];
-                    rr = s_p0[b][r * NX + xm]; ri = s_p1[b][r * NX + xm];
-                    sm = s_sx[(r - 1) * NX + xm]; cm = s_cx[(r - 1) * NX + xm];
+                    qr = s_p0[r * N + xp]; qi = s_p1[r * N + xp];
+                    rr = s_p0[r * N + xm]; ri = s_p1[r * N + xm];
+                    sm = s_sx[(r - 1) * N + xm]; cm = s_cx[(r - 1) * N + xm];
                 } else if (i == 1) {
-                    qr = s_p0[b][ro + NX]; qi = s_p1[b][ro + NX];
-                    rr = s_p0[b][ro - NX]; ri = s_p1[b][ro - NX];
-                    sm = s_sy[ro - NX]; cm = s_cy[ro - NX];
+                    qr = s_p0[ro + N]; qi = s_p1[ro + N];
+                    rr = s_p0[ro - N]; ri = s_p1[ro - N];
+                    sm = s_sy[ro - N]; cm = s_cy[ro - N];
                 } else {
                     qr = wp[0]; qi = wp[1];
                     rr = wm[0]; ri = wm[1];
                     sm = szm; cm = czm;
                 }
-                const int ow = i == 1 ? ro : wo;
-                const double *Ls = i == 0 ? s_sx : (i == 1 ? s_sy : s_sz);
-                const double *Lc = i == 0 ? s_cx : (i == 1 ? s_cy : s_cz);
-                const double s = -Ls[ow], c = Lc[ow];   // V_i(n) = c + i s
+                const double s = -ps[i], c = pc[i];   // V_i(n) = c + i s
                 const double ar = c * qr - s * qi, ai = c * qi + s * qr;
                 const double br = cm * rr - sm * ri, bi = cm * ri + sm * rr;
                 d2r += ar - 2.0 * pr + br;
@@ -683,30 +677,36 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
                 t[5] = fabs(G);
                 t[6] = fabs(div + charge);
                 t[7] = fabs(div) + fabs(charge);
-                t[8] = fabs(G);
-                t[9] = fabs(div);
-                t[10] = fabs(charge);
+                t[8] = 0.5 * (pq[0] * pq[0] + pq[1] * pq[1]);
+                t[9] = (pa[0] * pa[0] + pa[1] * pa[1] + pa[2] * pa[2]) / (2.0 * g.kappa_g);
+                t[10] = fabs(G);
+                t[11] = fabs(div);
+                t[12] = fabs(charge);
 #pragma unroll
                 for (int k = 0; k < NQ; ++k) acc[k] = k < kU1Sums ? acc[k] + t[k] : fmax(acc[k], t[k]);
             } else {
-                st32(g.pi[0], o, q0);
-                st32(g.pi[1], o, q1);
+                constexpr bool two = MODE == kU1KickSums;   // a second kick after the sums
+                st32(g.pi[0], o, two ? q0 + ck2 * F0 : q0);
+                st32(g.pi[1], o, two ? q1 + ck2 * F1 : q1);
+                const bool carry = MODE == kU1Kick && g.phi_out[0];
                 if constexpr (MODE == kU1Step) {
                     st32(g.phi_out[0], o, pr + hd * q0);
                     st32(g.phi_out[1], o, pim + hd * q1);
+                } else if (carry) {
+                    st32(g.phi_out[0], o, pr);
+                    st32(g.phi_out[1], o, pim);
                 }
                 double ka = 0.0;
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     const double FA = la1 * (g.kappa_g * J[i]) - lm1 * (mag[i] * inv_edx3);
                     const double qa = pa[i] + ck * FA;
-                    st32(g.piA[i], o, qa);
+                    st32(g.piA[i], o, two ? qa + ck2 * FA : qa);
                     if constexpr (MODE == kU1Step) st32(g.A_out[i], o, a0[i] + hdA * qa);
+                    else if (carry) st32(g.A_out[i], o, a0[i]);
                     if constexpr (MODE == kU1KickSums) ka += qa * qa;
                 }
                 if constexpr (MODE == kU1KickSums) {
-                    // the terms the energy mode forms after this kick: there the
-                    // stored momenta are q, qa and p + 0 F = p
                     double t[NQ];
                     t[0] = 0.5 * (q0 * q0 + q1 * q1);
                     t[1] = grad2 * inv_dx2 * 0.5;
@@ -716,14 +716,15 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
                     const double hxy = lat_sin(0.5 * th[0]), hxz = lat_sin(0.5 * th[1]), hyz = lat_sin(0.5 * th[2]);
                     const double mg = 2.0 * hxy * hxy + 2.0 * hxz * hxz + 2.0 * hyz * hyz;
                     t[4] = mg / (g.kappa_g * g.e * g.e * g.dx * g.dx * g.dx * g.dx);
+                    t[8] = 0.5 * (pq[0] * pq[0] + pq[1] * pq[1]);
+                    t[9] = (pa[0] * pa[0] + pa[1] * pa[1] + pa[2] * pa[2]) / (2.0 * g.kappa_g);
 #pragma unroll
-                    for (int k = 5; k < NQ; ++k) t[k] = 0.0;
-#pragma unroll
-                    for (int k = 0; k < NQ; ++k) acc[k] = k < kU1Sums ? acc[k] + t[k] : fmax(acc[k], t[k]);
+                    for (int k = 0; k < kU1Sums; ++k)
+                        if (k < 5 || k > 7) acc[k] += t[k];
                 }
             }
-            czm = s_cz[wo];
-            szm = s_sz[wo];
+            czm = pc[2];
+            szm = ps[2];
             sxzm = sxz;
             syzm = syz;
         }
@@ -743,53 +744,7 @@ __global__ void __launch_bounds__(64 * XS * TY) u1_rows(const U1Args g)
     }
 
     if constexpr (EN) {
-        // the block tree and last-block reduction of u1_stage's energy mode
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            const double rv = k < kU1Sums ? wave_sum(acc[k]) : wave_max(acc[k]);
-            if (lane == 0) lds_red[w * NQ + k] = rv;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            for (int k = 0; k < NQ; ++k) {
-                double rv = 0.0;
-                for (int i = 0; i < NT / 64; ++i)
-                    rv = k < kU1Sums ? rv + lds_red[i * NQ + k] : fmax(rv, lds_red[i * NQ + k]);
-                store_agent(&g.partials[(size_t)lid * NQ + k], rv);
-            }
-            // defer: the block partials are combined by a kernel after this one
-            last_flag = g.defer ? 0 : (ticket_arrive(g.ticket, gridDim.x) ? 1 : 0);
-        }
-        __syncthreads();
-        if (last_flag) {
-            const int nb = gridDim.x;
-            double part[NQ];
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) part[k] = 0.0;
-            for (int i = tid; i < nb; i += NT) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    const double v = load_agent(&g.partials[(size_t)i * NQ + k]);
-                    part[k] = k < kU1Sums ? part[k] + v : fmax(part[k], v);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                const double rv = k < kU1Sums ? wave_sum(part[k]) : wave_max(part[k]);
-                if (lane == 0) lds_red[w * NQ + k] = rv;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                for (int k = 0; k < NQ; ++k) {
-                    double rv = 0.0;
-                    for (int i = 0; i < NT / 64; ++i)
-                        rv = k < kU1Sums ? rv + lds_red[i * NQ + k] : fmax(rv, lds_red[i * NQ + k]);
-                    if (k < kU1Sums) g.sc->sums[k] = rv;
-                    else g.sc->maxes[k - kU1Sums] = rv;
-                }
-                __hip_atomic_store(g.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        u1_block_sums(acc, lds_red, &g.partials[(size_t)lid * NQ]);
     }
 }
 

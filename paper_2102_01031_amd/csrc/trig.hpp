@@ -92,10 +92,17 @@ LAT_HD inline double sin_reduced(double x)
 }
 
 // the library's full-range versions, kept out of line so that the rarely
-// taken branch does not add its registers to every call site
-LAT_HD __attribute__((noinline)) void sincos_full(double x, double *s, double *c)
+// taken branch does not add its registers to every call site; the pair by value,
+// since results returned through pointers would live in scratch memory at every
+// call site, taken or not (six pairs per site of a U(1) pass)
+struct SinCos {
+    double s, c;
+};
+LAT_HD __attribute__((noinline)) SinCos sincos_full(double x)
 {
-    sincos(x, s, c);
+    SinCos r;
+    sincos(x, &r.s, &r.c);
+    return r;
 }
 
 LAT_HD __attribute__((noinline)) double sin_full(double x)
@@ -120,7 +127,9 @@ LAT_HD inline void lat_sincos(double x, double *s, double *c)
     } else if (ax <= trig::kMaxReduced) {
         trig::sincos_reduced(x, s, c);
     } else {
-        trig::sincos_full(x, s, c);
+        const trig::SinCos r = trig::sincos_full(x);
+        *s = r.s;
+        *c = r.c;
     }
 }
 
