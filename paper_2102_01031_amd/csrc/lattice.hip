@@ -66,7 +66,7 @@ lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir);
 lat_status su2_sync(lat_ctx *c);
 lat_status su2_energy(lat_ctx *c, lat_energies *out);
 size_t su2_partial_capacity(int N);
-int su2_zc(int N, bool band);
+int su2_zc(const lat_ctx *c, bool sums);
 void su2_geometry(lat_ctx *c);
 size_t u1_partial_capacity(int N);
 void u1_geometry(lat_ctx *c);
@@ -101,7 +101,8 @@ struct lat_ctx {
     void *efl[9] = {};
     int cur_su2 = 0;
     int su2_zc = 1;
-    int su2_band = 0;   // y tiles per XCD band of the SU(2) block order (0: plane-wide order)
+    int su2_tx = 16, su2_ty = 16;   // SU(2) tile
+    int su2_band = 0;   // tiles of a plane per XCD (0: plane-wide order)
     int su2_nt = 1;     // step passes stream the momenta and output records non-temporally
     // per-site records of the doublet and links while lattice_step runs (ping-pong)
     double4 *su2_aos[2] = {};
@@ -1566,21 +1567,25 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
         }
     }
     if (c->su2) {
+        // steps run on per-site records (128^3: 228 against 335 us per pass on the plain
+        // arrays); LATTICE_SU2_AOS=0 keeps the plain arrays, which need shadows then
+        const char *aenv = std::getenv("LATTICE_SU2_AOS");
+        c->su2_aos_on = !gauge_self && !(aenv && std::atoi(aenv) == 0) && (double)c->vol * 32.0 < 4294967296.0;
+        const bool shadow = !gauge_self && !c->su2_aos_on;
         for (int k = 0; k < 4; ++k) {
             c->dbl[k][0] = f->doublet[k];
             c->dpi[k] = f->pi_doublet[k];
-            if (!gauge_self && hipMalloc(&c->dbl[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
+            if (shadow && hipMalloc(&c->dbl[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
         }
         for (int k = 0; k < 12; ++k) {
             c->lnk[k][0] = f->U[k];
-            if (!gauge_self && hipMalloc(&c->lnk[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
+            if (shadow && hipMalloc(&c->lnk[k][1], bytes) != hipSuccess) return bail(LAT_ENOMEM, "shadow allocation failed");
         }
         for (int k = 0; k < 9; ++k) c->efl[k] = f->E[k];
+        if (c->su2_aos_on)
+            for (auto &q : c->su2_aos)
+                if (hipMalloc(&q, 4 * c->vol * sizeof(double4)) != hipSuccess) return bail(LAT_ENOMEM, "record allocation failed");
         su2_geometry(c);
-        // per-site records during multi-pass lattice_step calls (12% faster step
-        // at 128^3); LATTICE_SU2_AOS=0 keeps the SoA arrays throughout
-        const char *aenv = std::getenv("LATTICE_SU2_AOS");
-        c->su2_aos_on = !(aenv && std::atoi(aenv) == 0) && (double)c->vol * 32.0 < 4294967296.0;
     }
     c->partial_cap = (size_t)std::max(c->nblocks > 1 ? c->nblocks : 1, c->en_nblocks) * kMaxQ + 64;
     if (c->su2) c->partial_cap = su2_partial_capacity(c->N) + 64;
@@ -2617,46 +2622,73 @@ lat_status u1_energy(lat_ctx *c, lat_energies *out)
 // ===========================================================================
 namespace {
 
-constexpr int kSU2TX = 64, kSU2TY = 4;
-
 size_t su2_partial_capacity(int N)
 {
-    // largest grid: one z plane per block
-    const size_t tiles = (size_t)((N + kSU2TX - 1) / kSU2TX) * ((N + kSU2TY - 1) / kSU2TY) * (size_t)N;
-    return tiles * (kSU2Sums + kSU2Maxes);
+    // largest grids: one z plane per block, tiles of 128 sites or more with one
+    // partly filled tile per row and column, XCD bands rounded up
+    const size_t tiles = (size_t)N * N / 64 + 2 * (size_t)N + 16;
+    return tiles * (size_t)N * (kSU2Sums + kSU2Maxes);
 }
 
-// SU(2) block order, z planes per block and cache policy.  With N a multiple
-// of 32 each XCD takes a y band of tiles_y / 8 tiles over all planes, one
-// plane per block, so the blocks an XCD runs at once form a compact region
-// whose neighbour planes stay in its L2 (LATTICE_SU2_BAND=0: the plane-wide
-// order, in which an XCD's blocks march whole planes).  LATTICE_SU2_ZC
-// overrides the planes per block.  The step passes read and write the
-// momenta and write the output records non-temporally (LATTICE_SU2_NT=0:
-// through the caches), which keeps the input records in L2.  At 128^3 on
-// one GPU: 286.7 us per pass plane-wide, 236.7-240.1 in bands, 227.6-228.0
-// in bands with the streams non-temporal.
+int su2_tiles(const lat_ctx *c)
+{
+    return ((c->N + c->su2_tx - 1) / c->su2_tx) * ((c->N + c->su2_ty - 1) / c->su2_ty);
+}
+
+// SU(2) tiles, block order, z planes per block and cache policy.  A tile row is a
+// k-th of a lattice row, a tile as many rows as 256 threads hold; of k = 1 .. 8 the one
+// that leaves the fewest threads idle, each cut counted as 8 % (a wavefront's accesses
+// break at a row's end): whole rows at 24, 40, 48, 64, 72, 128, halves at 96 and 100.
+// 64 x 4 on every size left up to half of the threads without a site: eight leapfrog
+// steps at 72^3 70.6 us each in 64 x 4, 58.8 in 36 x 7, 52.3 in 72 x 3 tiles.
+// The blocks of a plane are dealt to the XCDs in bands (su2_stage) unless that would
+// leave more than an eighth of the band places empty (48^3, 10 tiles in bands of 2:
+// 26.3 us a step against 18.1 plane-wide; 72^3 51.5 against 54.1), one plane per block
+// in step and kick passes; the summing passes run plane-wide.  LATTICE_SU2_BAND=0: no
+// bands.  LATTICE_SU2_ZC overrides the planes per block, LATTICE_SU2_TILE the sites per tile row (at least
+// 16 or N, at most 256).  The step passes read and write the momenta and write the
+// output records non-temporally (LATTICE_SU2_NT=0: through the caches), which keeps the
+// input records in L2.  At 128^3 in 64 x 4 tiles: 286.7 us per pass plane-wide,
+// 236.7-240.1 in bands, 227.6-228.0 in bands with the streams non-temporal.
 void su2_geometry(lat_ctx *c)
 {
-    const int ty = (c->N + kSU2TY - 1) / kSU2TY;
+    const int N = c->N, most = std::min(N, kSU2Threads);
+    const char *te = std::getenv("LATTICE_SU2_TILE");
+    const int want = te ? std::atoi(te) : 0;
+    double best = -1.0e9;
+    for (int k = 1; k <= 8; ++k) {
+        const int tx = (N + k - 1) / k;
+        if (tx > kSU2Threads) continue;
+        const int ty = std::min(N, kSU2Threads / tx);
+        const double used = (double)N * N / ((double)k * ((N + ty - 1) / ty) * kSU2Threads);
+        if (used - 0.08 * (k - 1) > best) {
+            best = used - 0.08 * (k - 1);
+            c->su2_tx = tx;
+            c->su2_ty = ty;
+        }
+    }
+    if (want >= std::min(N, 16) && want <= most) {
+        c->su2_tx = want;
+        c->su2_ty = std::min(N, kSU2Threads / want);
+    }
+    const int tiles = su2_tiles(c), band = (tiles + 7) / 8;
     const char *e = std::getenv("LATTICE_SU2_BAND");
-    c->su2_band = (ty % 8 == 0 && !(e && std::atoi(e) == 0)) ? ty / 8 : 0;
-    c->su2_zc = su2_zc(c->N, c->su2_band > 0);
+    c->su2_band = (e && std::atoi(e) == 0) || 8 * (8 * band - tiles) > tiles ? 0 : band;
+    c->su2_zc = su2_zc(c, false);
     const char *nt = std::getenv("LATTICE_SU2_NT");
     c->su2_nt = (nt && std::atoi(nt) == 0) ? 0 : 1;
 }
 
-// z planes per block: LATTICE_SU2_ZC if set (1 .. N), else 1 in the band
-// order and otherwise a default that keeps at least 512 blocks
-int su2_zc(int N, bool band)
+// z planes per block: LATTICE_SU2_ZC if set (1 .. N), else one plane; the summing
+// passes up to eight where that leaves 1024 blocks (128^3 step of the self-consistent
+// leapfrog 432 us with 8, 441 with 2; 100^3 172 with 2, 225 with 8)
+int su2_zc(const lat_ctx *c, bool sums)
 {
     const char *env = std::getenv("LATTICE_SU2_ZC");
     int zc = 0;
-    if (env && std::sscanf(env, "%d", &zc) == 1 && zc >= 1 && zc <= N) return zc;
-    if (band) return 1;
-    const int tiles = ((N + kSU2TX - 1) / kSU2TX) * ((N + kSU2TY - 1) / kSU2TY);
-    zc = 16;
-    while (zc > 1 && (size_t)tiles * ((N + zc - 1) / zc) < 512) zc /= 2;
+    if (env && std::sscanf(env, "%d", &zc) == 1 && zc >= 1 && zc <= c->N) return zc;
+    zc = sums ? 8 : 1;
+    while (zc > 1 && (long)su2_tiles(c) * ((c->N + zc - 1) / zc) < 1024) zc /= 2;
     return zc;
 }
 
@@ -2675,8 +2707,10 @@ SU2Args su2_args(lat_ctx *c, double ck, double hd, bool write_fields)
     }
     for (int k = 0; k < 9; ++k) a.E[k] = (double *)c->efl[k];
     a.N = c->N;
-    a.tiles_x = (c->N + kSU2TX - 1) / kSU2TX;
-    a.tiles_y = (c->N + kSU2TY - 1) / kSU2TY;
+    a.tx = c->su2_tx;
+    a.ty = c->su2_ty;
+    a.tiles_x = (c->N + a.tx - 1) / a.tx;
+    a.tiles_y = (c->N + a.ty - 1) / a.ty;
     a.zc = c->su2_zc;
     a.band = c->su2_band;
     a.dx = c->p.dx;
@@ -2724,21 +2758,18 @@ SU2Args su2_args_dev(lat_ctx *c)
 lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args, const GaugeUpdate &u = GaugeUpdate{},
                       bool host = false)
 {
-    // the energy pass keeps the plane-wide order with its z columns: in the
-    // band order's one-plane blocks its last block would sum 16x more block
-    // partials (654 against 357 us at 128^3)
     SU2Args a = args;
     const bool sums = mode == kSU2Energy || mode == kSU2KickSums;
     if (sums) {
         a.band = 0;
-        a.zc = su2_zc(c->N, false);
+        a.zc = su2_zc(c, true);
         // LATTICE_SU2_ENERGY_ZC: z planes per block of the summing passes alone
         if (const char *ez = std::getenv("LATTICE_SU2_ENERGY_ZC")) {
             const int v = std::atoi(ez);
             if (v >= 1 && v <= c->N) a.zc = v;
         }
     }
-    const size_t nbz = (size_t)a.tiles_x * a.tiles_y * (size_t)((c->N + a.zc - 1) / a.zc);
+    const size_t nbz = (size_t)(a.band > 0 ? 8 * a.band : a.tiles_x * a.tiles_y) * (size_t)((c->N + a.zc - 1) / a.zc);
     if (nbz > 0x7fffffffu || (sums && nbz * (kSU2Sums + kSU2Maxes) > c->partial_cap))
         return fail(c, LAT_EINVAL, "SU(2) launch exceeds the partials buffer");
     const int nb = (int)nbz;
@@ -2748,7 +2779,7 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args, const GaugeUpda
         lat_status st = timing_begin(c, &ev0, &ev1);
         if (st != LAT_OK) return st;
     }
-    const dim3 grid(nb), blk(kSU2TX * kSU2TY);
+    const dim3 grid(nb), blk(kSU2Threads);
     const bool nt = c->su2_nt != 0;
     switch (mode) {
     case kSU2Drift:
@@ -2756,19 +2787,23 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args, const GaugeUpda
                            (unsigned)c->vol);
         break;
     case kSU2Step:
-        if (nt) hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2Step, true>), grid, blk, 0, c->stream, a);
-        else hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2Step, false>), grid, blk, 0, c->stream, a);
+        if (nt) hipLaunchKernelGGL((su2_stage<kSU2Step, true>), grid, blk, 0, c->stream, a);
+        else hipLaunchKernelGGL((su2_stage<kSU2Step, false>), grid, blk, 0, c->stream, a);
         break;
-    case kSU2Kick: hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2Kick, false>), grid, blk, 0, c->stream, a); break;
+    case kSU2Kick: hipLaunchKernelGGL((su2_stage<kSU2Kick, false>), grid, blk, 0, c->stream, a); break;
     case kSU2KickSums:
-        hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2KickSums, false>), grid, blk, 0, c->stream, a);
+        hipLaunchKernelGGL((su2_stage<kSU2KickSums, false>), grid, blk, 0, c->stream, a);
+        break;
+    case kSU2StepOut:
+        if (nt) hipLaunchKernelGGL((su2_stage<kSU2StepOut, true>), grid, blk, 0, c->stream, a);
+        else hipLaunchKernelGGL((su2_stage<kSU2StepOut, false>), grid, blk, 0, c->stream, a);
         break;
     case kSU2StepAoS:
-        if (nt) hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2StepAoS, true>), grid, blk, 0, c->stream, a);
-        else hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2StepAoS, false>), grid, blk, 0, c->stream, a);
+        if (nt) hipLaunchKernelGGL((su2_stage<kSU2StepAoS, true>), grid, blk, 0, c->stream, a);
+        else hipLaunchKernelGGL((su2_stage<kSU2StepAoS, false>), grid, blk, 0, c->stream, a);
         break;
     default:
-        hipLaunchKernelGGL((su2_stage<kSU2TX, kSU2TY, kSU2Energy, false>), grid, blk, 0, c->stream, a);
+        hipLaunchKernelGGL((su2_stage<kSU2Energy, false>), grid, blk, 0, c->stream, a);
         break;
     }
     HIPCHK(c, hipGetLastError());
@@ -2784,17 +2819,12 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args, const GaugeUpda
     return LAT_OK;
 }
 
-// Per-site records: buffers on first use, conversion from / to the SoA arrays
-// of the current parity (from: back into the caller's arrays, parity 0).  A
-// call converts twice, so records are used from this many passes on.
-constexpr int64_t kSU2AosMinPasses = 4;
+// The plain arrays into per-site records, before a call's step passes; the last pass
+// reads records and writes the caller's arrays.  The conversion costs half a pass (104
+// against 228 us at 128^3), a pass on the plain arrays half again as much as one on
+// records, and an odd number of those a copy back of 16 arrays (170 us).
 lat_status su2_aos_enter(lat_ctx *c)
 {
-    for (auto &q : c->su2_aos)
-        if (!q && hipMalloc(&q, 4 * c->vol * sizeof(double4)) != hipSuccess) {
-            q = nullptr;
-            return fail(c, LAT_ENOMEM, "SU(2) record buffers");
-        }
     SU2Soa s{};
     for (int k = 0; k < 4; ++k) s.a[k] = (double *)c->dbl[k][c->cur_su2];
     for (int k = 0; k < 12; ++k) s.a[4 + k] = (double *)c->lnk[k][c->cur_su2];
@@ -2805,22 +2835,14 @@ lat_status su2_aos_enter(lat_ctx *c)
     return LAT_OK;
 }
 
-lat_status su2_aos_leave(lat_ctx *c, int buf)
-{
-    SU2Aos s{};
-    for (int q = 0; q < 4; ++q) s.r[q] = c->su2_aos[buf] + (size_t)q * c->vol;
-    SU2Soa d{};
-    for (int k = 0; k < 4; ++k) d.a[k] = (double *)c->dbl[k][0];
-    for (int k = 0; k < 12; ++k) d.a[4 + k] = (double *)c->lnk[k][0];
-    hipLaunchKernelGGL(su2_from_aos, dim3(2048), dim3(256), 0, c->stream, s, d, c->vol);
-    HIPCHK(c, hipGetLastError());
-    c->cur_su2 = 0;
-    return LAT_OK;
-}
-
-SU2Args su2_args_aos(lat_ctx *c, double ck, double hd, int buf)
+// (last: the caller's arrays are written instead of records)
+SU2Args su2_args_aos(lat_ctx *c, double ck, double hd, int buf, bool last)
 {
     SU2Args a = su2_args(c, ck, hd, false);
+    if (last) {
+        for (int k = 0; k < 4; ++k) a.phi_out[k] = (double *)c->dbl[k][0];
+        for (int k = 0; k < 12; ++k) a.U_out[k] = (double *)c->lnk[k][0];
+    }
     const double4 *in = c->su2_aos[buf];
     double4 *out = c->su2_aos[buf ^ 1];
     a.phi_in4 = in;
@@ -2860,23 +2882,22 @@ lat_status su2_step_lf(lat_ctx *c, int64_t ns, int dir)
     const double t0 = c->t;
     const bool fixed = c->p.expansion == LAT_EXP_FIXED;
     int stag = c->lf_stag;
-    if (c->su2_aos_on && ns >= kSU2AosMinPasses) {
+    if (c->su2_aos_on) {
         lat_status s = su2_aos_enter(c);
         if (s != LAT_OK) return s;
         int buf = 0;
         for (int64_t k = 0; k < ns; ++k) {
             const double ck = stag == 0 ? 0.5 * h : h;
-            SU2Args a = su2_args_aos(c, ck, h, buf);
+            SU2Args a = su2_args_aos(c, ck, h, buf, k == ns - 1);
             if (fixed) {   // kick at t, drift at the midpoint (reading R3)
                 const double t = t0 + (double)k * h;
                 su2_bg(c, a, h, scale_at(c, t), scale_at(c, t + 0.5 * h));
             }
             a.down = su2_alternate() ? (int)(k & 1) : 0;
-            if ((s = su2_launch(c, kSU2StepAoS, a)) != LAT_OK) return s;
+            if ((s = su2_launch(c, k == ns - 1 ? kSU2StepOut : kSU2StepAoS, a)) != LAT_OK) return s;
             buf ^= 1;
             stag = dir;
         }
-        if ((s = su2_aos_leave(c, buf)) != LAT_OK) return s;
         c->lf_stag = dir;
         c->t = t0 + (double)ns * h;
         return LAT_OK;
@@ -2938,7 +2959,7 @@ lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir)
     const double t_start = c->t;
     double tk = t_start;   // time of the current kick point
     double prev = 0.0;
-    const bool aos = c->su2 && c->su2_aos_on && M >= kSU2AosMinPasses;
+    const bool aos = c->su2 && c->su2_aos_on;
     int buf = 0;
     if (aos) {
         lat_status s = su2_aos_enter(c);
@@ -2952,9 +2973,9 @@ lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir)
         if (p % J == 0) tk = t_start + (double)(p / J) * h;
         lat_status s;
         if (aos) {
-            SU2Args a = su2_args_aos(c, ck, hp, buf);
+            SU2Args a = su2_args_aos(c, ck, hp, buf, p == M - 1);
             if (fixed) su2_bg(c, a, hp, scale_at(c, tk), scale_at(c, tk + 0.5 * hp));
-            s = su2_launch(c, kSU2StepAoS, a);
+            s = su2_launch(c, p == M - 1 ? kSU2StepOut : kSU2StepAoS, a);
             buf ^= 1;
         } else if (c->su2) {
             s = su2_launch(c, kSU2Step, fixed ? su2_args_bg(c, ck, hp, scale_at(c, tk), scale_at(c, tk + 0.5 * hp), true)
@@ -2968,10 +2989,6 @@ lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir)
         tk += hp;
         if (s != LAT_OK) return s;
         prev = hp;
-    }
-    if (aos) {
-        lat_status s = su2_aos_leave(c, buf);
-        if (s != LAT_OK) return s;
     }
     const double tend = t_start + (double)ns * h;
     const double ae = scale_at(c, tend);

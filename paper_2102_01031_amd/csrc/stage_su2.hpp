@@ -34,13 +34,14 @@ struct SU2Args {
     double *U_out[12];
     double *E[9];             // link i, colour a at 3 i + a
     // kSU2StepAoS: the doublet and the links as one 32-byte record per site
-    // (phi0..phi3; w, x, y, z), read from *_in4 and written to *_out4
+    // (phi0..phi3; w, x, y, z), read from *_in4 and written to *_out4;
+    // kSU2StepOut: read from *_in4 and written to the plain arrays
     const double4 *phi_in4;
     double4 *phi_out4;
     const double4 *U_in4[3];
     double4 *U_out4[3];
-    int N, tiles_x, tiles_y, zc;   // zc: z planes per block
-    int band;                      // > 0: y tiles per XCD band (tiles_y = 8 band), see su2_stage
+    int N, tx, ty, tiles_x, tiles_y, zc;   // tile of tx x ty <= 256 sites, z planes per block
+    int band;                      // > 0: tiles of a plane per XCD, see su2_stage
     int down;                      // march the z column downward (sites are independent)
     double dx, g, lam, v;
     double ck;   // kick weight
@@ -62,7 +63,8 @@ struct SU2Args {
 // sums [8, 10) before the kick, then kicks by ck2 (in the energy pass's launch shape;
 // Gauss terms not measured: the rest stays zero).  kSU2Kick with output arrays also
 // carries the doublet and the links over to them.
-enum SU2Mode : int { kSU2Step = 0, kSU2Kick = 1, kSU2Energy = 2, kSU2StepAoS = 3, kSU2Drift = 4, kSU2KickSums = 5 };
+enum SU2Mode : int { kSU2Step = 0, kSU2Kick = 1, kSU2Energy = 2, kSU2StepAoS = 3, kSU2Drift = 4, kSU2KickSums = 5,
+                     kSU2StepOut = 6 };
 
 // one 32-byte record through a 32-bit byte offset (valid while 32 N^3 < 2^32)
 __device__ __forceinline__ double4 ld4(const double4 *base, unsigned i)
@@ -124,6 +126,26 @@ __device__ __forceinline__ Q4 qdag(const Q4 &a) { return Q4{a.w, -a.x, -a.y, -a.
 
 __device__ __forceinline__ Q4 qadd(const Q4 &a, const Q4 &b) { return Q4{a.w + b.w, a.x + b.x, a.y + b.y, a.z + b.z}; }
 
+// exp(-i hgdx e.T) = cos(th/2) - i sin(th/2) e.sigma/|e|, th = hgdx |e|.  Up to
+// th/2 = pi/4 both factors come from the polynomials of trig.hpp in (th/2)^2
+// (sin(t)/t is the sine polynomial with t = 1 outside), so the usual small angles
+// need no square root, no division and no range reduction.
+__device__ __forceinline__ Q4 su2_exp(double hgdx, double ex, double ey, double ez)
+{
+    const double hh = 0.5 * hgdx, e2 = ex * ex + ey * ey + ez * ez, z = hh * hh * e2;
+    double f, w;
+    if (z <= kQuarterPi * kQuarterPi) {
+        f = hh * trig::sin_poly(1.0, z);
+        w = trig::cos_poly(z);
+    } else {
+        const double len = sqrt(e2);
+        const trig::SinCos sc = trig::sincos_full(hh * len);
+        f = sc.s / len;
+        w = sc.c;
+    }
+    return Q4{w, f * ex, f * ey, f * ez};
+}
+
 // (r0 + i s0, r1 + i s1) = U (a + i b, c + i d), U = w I - i v.sigma
 __device__ __forceinline__ void qapply(const Q4 &u, double a, double b, double c, double d, double &r0, double &s0,
                                        double &r1, double &s1)
@@ -176,7 +198,7 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
         q[j] = u;
         return off(q[0], q[1], q[2]);
     };
-    constexpr bool AOS = MODE == kSU2StepAoS;
+    constexpr bool AOS = MODE == kSU2StepAoS || MODE == kSU2StepOut, AOS_OUT = MODE == kSU2StepAoS;
     auto L = [&](int i, unsigned m) {
         if constexpr (AOS) {
             const double4 v = ld4(g.U_in4[i], m);
@@ -376,7 +398,7 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
         }
         if (MODE == kSU2Step || AOS) {
             const double4 po{a0 + wt.hd * pn[0], b0 + wt.hd * pn[1], c0 + wt.hd * pn[2], d0 + wt.hd * pn[3]};
-            if constexpr (AOS) {
+            if constexpr (AOS_OUT) {
                 st4_s<NT>(g.phi_out4, n, po);
             } else {
                 st_s<NT>(g.phi_out[0], n, po.x);
@@ -387,19 +409,9 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
             const double hgdx = wt.hdU * g.g * g.dx;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                // exp(-i hdU g dx E.T) = cos(th/2) - i sin(th/2) e.sigma, th = hdU g dx |E|
-                const double ex = en[3 * i], ey = en[3 * i + 1], ez = en[3 * i + 2];
-                const double len = sqrt(ex * ex + ey * ey + ez * ez);
-                double sh, chh;
-                sincos(0.5 * (hgdx * len), &sh, &chh);
-                Q4 R{chh, 0.0, 0.0, 0.0};
-                if (len > 0.0) {
-                    R.x = sh * ex / len;
-                    R.y = sh * ey / len;
-                    R.z = sh * ez / len;
-                }
+                const Q4 R = su2_exp(hgdx, en[3 * i], en[3 * i + 1], en[3 * i + 2]);
                 const Q4 Un = qmul(R, Ul[i]);
-                if constexpr (AOS) {
+                if constexpr (AOS_OUT) {
                     st4_s<NT>(g.U_out4[i], n, double4{Un.w, Un.x, Un.y, Un.z});
                 } else {
                     st_s<NT>(g.U_out[4 * i], n, Un.w);
@@ -427,15 +439,7 @@ __global__ void __launch_bounds__(256) su2_drift(const SU2Args g, unsigned vol)
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const double ex = g.E[3 * i][n], ey = g.E[3 * i + 1][n], ez = g.E[3 * i + 2][n];
-        const double len = sqrt(ex * ex + ey * ey + ez * ez);
-        double sh, chh;
-        sincos(0.5 * (hgdx * len), &sh, &chh);
-        Q4 R{chh, 0.0, 0.0, 0.0};
-        if (len > 0.0) {
-            R.x = sh * ex / len;
-            R.y = sh * ey / len;
-            R.z = sh * ez / len;
-        }
+        const Q4 R = su2_exp(hgdx, ex, ey, ez);
         const Q4 U{g.U_in[4 * i][n], g.U_in[4 * i + 1][n], g.U_in[4 * i + 2][n], g.U_in[4 * i + 3][n]};
         const Q4 Un = qmul(R, U);
         g.U_out[4 * i][n] = Un.w;
@@ -445,45 +449,44 @@ __global__ void __launch_bounds__(256) su2_drift(const SU2Args g, unsigned vol)
     }
 }
 
-// Block = TX x TY sites of a z column [z0, z0 + zc).  Logical blocks are
-// dealt to the XCDs in contiguous ranges.  Plane-wide order (band = 0): x
-// tile fastest, then y tile, then z chunk, so an XCD's resident blocks march
-// whole planes together.  Band order (band > 0): XCD k owns the y tiles
-// [k band, (k + 1) band) over all z chunks, x tile fastest, then y tile, then
-// z chunk (in reverse when marching down), so its resident blocks cover a
-// compact region and the records of the planes z - 1, z, z + 1 that a site's
-// stencil reads stay in that XCD's L2 between their uses.
+// Block = tx x ty sites (at most 256, tx and ty at run time so that any N is cut with
+// few idle threads) of a z column [z0, z0 + zc).  Plane-wide order (band = 0): logical
+// blocks are dealt to the XCDs in contiguous ranges, x tile fastest, then y tile, then
+// z chunk, so an XCD's resident blocks march whole planes together.  Band order
+// (band > 0): XCD k owns the tiles [k band, (k + 1) band) of a plane over all z chunks
+// (in reverse when marching down; band = tiles / 8 rounded up, the last XCD's may be
+// missing), so its resident blocks cover a compact region and the records of the
+// planes z - 1, z, z + 1 that a site's stencil reads stay in that XCD's L2 between
+// their uses.
 // Two waves per SIMD in every mode: the kick-only and energy passes then
 // spill 24 and 28 bytes per lane to scratch instead of holding 256 VGPRs and
 // 6 AGPRs at one wave (energy pass 361 -> 298 us at 128^3, self-consistent
 // leapfrog step 1316 -> 1133 us); the record step pass fits in 240 VGPRs.
-template <int TX, int TY, int MODE, bool STREAM>
-__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2))) su2_stage(const SU2Args g)
+constexpr int kSU2Threads = 256;
+template <int MODE, bool STREAM>
+__global__ void __launch_bounds__(kSU2Threads) __attribute__((amdgpu_waves_per_eu(2))) su2_stage(const SU2Args g)
 {
-    constexpr int NT = TX * TY;
+    constexpr int NT = kSU2Threads;
     constexpr int NQ = kSU2Sums + kSU2Maxes;
     __shared__ double lds_red[(NT / 64) * NQ];
 
     const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
     const int lid = xcd_logical_block(blockIdx.x, gridDim.x);
-    const int N = g.N;
-    int bx, by, bz;
+    const int N = g.N, tiles = g.tiles_x * g.tiles_y;
+    int t, bz;
     if (g.band > 0) {
-        const int per = gridDim.x / 8;   // the host launches 8 tiles_x band z-chunk blocks
+        const int per = gridDim.x / 8;   // the host launches 8 band z-chunk blocks
         const int xcd = lid / per, r = lid % per;
-        bx = r % g.tiles_x;
-        const int r2 = r / g.tiles_x;
-        by = xcd * g.band + r2 % g.band;
-        bz = r2 / g.band;
+        t = xcd * g.band + r % g.band;
+        bz = r / g.band;
         if (g.down) bz = (N + g.zc - 1) / g.zc - 1 - bz;
     } else {
-        bx = lid % g.tiles_x;
-        const int rest = lid / g.tiles_x;
-        by = rest % g.tiles_y;
-        bz = rest / g.tiles_y;
+        t = lid % tiles;
+        bz = lid / tiles;
     }
-    const int x = bx * TX + tx, y = by * TY + ty;
+    const int iy = tid / g.tx, ix = tid - iy * g.tx;
+    const bool on = t < tiles && iy < g.ty;
+    const int x = (t % g.tiles_x) * g.tx + ix, y = (t / g.tiles_x) * g.ty + iy;
     const int z0 = bz * g.zc, z1 = min(z0 + g.zc, N);
 
     double acc[NQ];
@@ -491,7 +494,7 @@ __global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2))
     for (int k = 0; k < NQ; ++k) acc[k] = 0.0;
 
     const SU2W wt = su2_weights(g);
-    if (x < N && y < N) {
+    if (on && x < N && y < N) {
         int c[3] = {x, y, z0}, cp[3], cm[3];
         cp[0] = x + 1 == N ? 0 : x + 1;
         cm[0] = x == 0 ? N - 1 : x - 1;
@@ -515,7 +518,8 @@ __global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(2))
 
 namespace lat {
 
-// SoA <-> per-site records of the doublet and the links (kSU2StepAoS):
+// Plain arrays to per-site records of the doublet and the links (kSU2StepAoS; the last
+// pass of a call writes the plain arrays itself, kSU2StepOut):
 // a[0..3] the doublet components, a[4 + 4 i + k] component k of link i;
 // r[0] the doublet records, r[1 + i] those of link i.
 struct SU2Soa {
@@ -531,20 +535,6 @@ __global__ void su2_to_aos(const SU2Soa s, const SU2Aos d, size_t V)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             d.r[q][n] = double4{s.a[4 * q][n], s.a[4 * q + 1][n], s.a[4 * q + 2][n], s.a[4 * q + 3][n]};
-    }
-}
-
-__global__ void su2_from_aos(const SU2Aos s, const SU2Soa d, size_t V)
-{
-    for (size_t n = (size_t)blockIdx.x * blockDim.x + threadIdx.x; n < V; n += (size_t)gridDim.x * blockDim.x) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const double4 v = s.r[q][n];
-            d.a[4 * q][n] = v.x;
-            d.a[4 * q + 1][n] = v.y;
-            d.a[4 * q + 2][n] = v.z;
-            d.a[4 * q + 3][n] = v.w;
-        }
     }
 }
 
