@@ -238,13 +238,8 @@ __device__ inline void finalise_prologue(const ScalarArgs<T> &g, double *lds_red
         for (int k = 0; k < NQ; ++k) part[k] += g.fin[(size_t)i * NQ + k];
     }
     double fin[NQ];
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) fin[k] = 0.0;
     block_sums<NT, NQ>(part, lds_red, fin);
-    if (tid < 64) {
-        // the sums from thread 0 to its wave, which applies the update
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) fin[k] = __shfl(fin[k], 0, 64);
+    if (tid < 64) {   // every lane of the first wave holds the sums
         const SelfOut o = self_compute_wave<NF>(g.fin_mode, *g.fin_coef, fin, g.fin_in, g.alpha, g.kappa2,
                                                 g.inv_vol, g.inv_dx2);
         if (tid == 0) {

@@ -63,10 +63,12 @@ template <int NQ>
 __device__ inline void u1_block_sums(double (&acc)[NQ], double *lds_red, double *out)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x / 64;
+    double v[NQ];
 #pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-        const double r = k < kU1Sums ? wave_sum(acc[k]) : wave_max(acc[k]);
-        if (lane == 0) lds_red[w * NQ + k] = r;
+    for (int k = 0; k < NQ; ++k) v[k] = k < kU1Sums ? wave_sum(acc[k]) : wave_max(acc[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) lds_red[w * NQ + k] = v[k];
     }
     __syncthreads();
     if (tid < NQ) {
