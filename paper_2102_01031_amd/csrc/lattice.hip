@@ -1854,10 +1854,19 @@ lat_status lattice_energy_noalloc(const lat_params *p, const lat_fields *f, doub
     g.vol = (size_t)p->N * p->N * p->N;
     geometry_from_env(&g);
     const int NQ = 3 * g.nf;
-    if ((size_t)g.nblocks * NQ > kNaPartialDoubles)
+    // the sizes this call takes are those whose tiled pass fits the scratch, whichever
+    // kernel runs (the plane-run kernel needs fewer partials)
+    size_t need = (size_t)g.nblocks * NQ;
+    if (!g.rows) {
+        lat_ctx tiled;
+        tiled.N = g.N;
+        set_geometry(&tiled, pick_tile(g.N), 0);
+        if (!std::getenv("LATTICE_TILE")) need = std::max(need, (size_t)tiled.nblocks * NQ);
+    }
+    if (need > kNaPartialDoubles)
         return fail(nullptr, LAT_EINVAL,
                     "lattice too large for the fixed scratch of lattice_energy_noalloc (" +
-                        std::to_string((size_t)g.nblocks * NQ) + " block partials, at most " +
+                        std::to_string(need) + " block partials, at most " +
                         std::to_string(kNaPartialDoubles) + ")");
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) return fail(nullptr, LAT_ENODEV, "no current GPU");
