@@ -144,6 +144,8 @@ struct lat_ctx {
     int rows_zpair = 0;       // whole-row kernel: odd z chunks march the other way
     bool plane = false;       // plane-run kernel (stage_plane.hpp): tiles_x runs of tiles_y sites per plane
     PlaneCfg plane_cfg{};
+    bool site_red = false;    // reducing passes: one-site-per-thread kernel (stage_site.hpp), zc sites per thread
+    int site_nblocks = 0;     // other passes: that kernel's blocks (0: the reducing passes' kernel)
     int zc = 0;
     int tiles_x = 0, tiles_y = 0, chunks_z = 0, nblocks = 0;
     // launch statistics and optional event timing
@@ -283,6 +285,7 @@ int auto_chunk(int N, long xy_blocks, long target)
 // threads per block of the stage passes
 int stage_threads(const lat_ctx *c)
 {
+    if (c->site_red) return kSiteThreads;
     return c->rows ? 64 * c->rows_ty : (c->plane ? c->plane_cfg.nt : kTiles[c->tile].tx * kTiles[c->tile].ty);
 }
 
@@ -372,6 +375,44 @@ bool plane_geometry(lat_ctx *c, const char *spec)
     return true;
 }
 
+// One-site-per-thread kernel (stage_site.hpp).  Passes without sums take it while the
+// three arrays per field that a pass touches are well inside the caches: up to 72 MB in
+// float64, 96 MB in float32.  Beyond, the marching kernels read each plane once and
+// win as soon as another lattice's passes have passed through the caches in between
+// (leapfrog pass, repeated calls on one lattice | two-step calls on lattices in turn, us,
+// marching and this kernel: two float64 fields 110^3, 61 MB, 17.6 16.1 | 26.3 25.3,
+// 128^3, 96 MB, 23.7 23.1 | 30.4 33.9; two float32 fields 160^3, 94 MB, 25.7 21.0 |
+// 32.9 31.2, 176^3, 125 MB, 30.5 27.0 | 42.5 44.8).  Passes with sums take it on small
+// lattices, where every block can add all blocks' sums in its prologue: float64 up to 72^3
+// but not at 64^3, where the whole-row kernel is there (72^3 14.2 and 12.6, 64^3 9.8
+// and 10.7, 80^3 14.7 and 14.9), float32 below 128^3 (110^3 19.6 and 16.9, 144^3
+// 27.6 and 28.2), in at most 512 blocks of a few sites per thread, 768 from 96^3
+// (float32 72^3: 9.4 us in 512, 10.5 in 768; 110^3 18.1 and 16.9).
+// LATTICE_TILE="site[,kick[,red[,blocks]]]" overrides (kick, red: 0 or 1).
+void site_geometry(lat_ctx *c, const char *spec)
+{
+    const size_t size = c->f32 ? 4 : 8;
+    c->site_red = false;
+    c->site_nblocks = 0;
+    if ((double)c->vol * size >= 4294967296.0) return;
+    int kick = -1, red = -1, cap = c->N < 96 ? 512 : 768;
+    if (spec) std::sscanf(spec, ",%d,%d,%d", &kick, &red, &cap);
+    const size_t nb = (c->vol + kSiteThreads - 1) / kSiteThreads;
+    const size_t mb = (3 * (size_t)c->nf * size * c->vol) >> 20;
+    if (kick < 0) kick = mb <= (c->f32 ? 96u : 72u);
+    if (red < 0) red = !rows_ok(c->N) && c->N <= (c->f32 ? 127 : 72);
+    if (kick) c->site_nblocks = (int)nb;
+    if (red) {
+        cap = std::max(cap, 1);
+        c->site_red = true;
+        c->rows = c->plane = false;
+        c->zc = (int)((nb + cap - 1) / cap);
+        c->nblocks = (int)((nb + c->zc - 1) / c->zc);
+        c->tiles_x = c->nblocks;
+        c->tiles_y = c->chunks_z = 1;
+    }
+}
+
 // Energy pass geometry of the whole-row kernel.  Read-only, the pass needs
 // more bytes in flight than the stage passes' one wave per SIMD give: at
 // N = 256 it runs 32-plane z chunks with two waves per SIMD, in float64 one
@@ -399,7 +440,7 @@ void energy_geometry(lat_ctx *c)
     c->en_nblocks = ((c->N + ty - 1) / ty) * ((c->N + zc - 1) / zc);
 }
 
-void geometry_from_env(lat_ctx *c)
+void stage_geometry(lat_ctx *c)
 {
     // prefetch depth of the whole-row kernel at N = 256: two planes in float64
     // (3% faster than one; three spill to 118 AGPRs and ran 5% slower), four in
@@ -473,6 +514,16 @@ void geometry_from_env(lat_ctx *c)
     }
     if (plane_geometry(c, nullptr)) return;
     set_geometry(c, tile, zc);
+}
+
+// Launch geometry of a lattice's passes; a LATTICE_TILE that names another
+// kernel keeps every pass on that one.
+void geometry_from_env(lat_ctx *c)
+{
+    stage_geometry(c);
+    const char *s = std::getenv("LATTICE_TILE");
+    const bool site = s && std::strncmp(s, "site", 4) == 0;
+    if (!s || site) site_geometry(c, site ? s + 4 : nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -669,7 +720,11 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
         pf = c->en_pf;
         lp = 0;
     }
-    if (c->rows)
+    const bool red = variant == kKickOnlyRed || variant == kDriftKickRed || variant == kKickCopyRed || variant == kEnergy;
+    if (red ? c->site_red : c->site_nblocks > 0) {
+        nb = red ? c->nblocks : c->site_nblocks;
+        e = c->nf == 1 ? launch_site<T, 1>(variant, a, nb, stream) : launch_site<T, 2>(variant, a, nb, stream);
+    } else if (c->rows)
         e = c->nf == 1 ? launch_rows<T, 1>(c->N, ty, pf, c->rows_vw, variant, a, nb, stream, lp)
                        : launch_rows<T, 2>(c->N, ty, pf, c->rows_vw, variant, a, nb, stream, lp);
     else if (c->plane)
@@ -1919,6 +1974,7 @@ lat_status lattice_energy_noalloc(const lat_params *p, const lat_fields *f, doub
         using T = std::remove_pointer_t<decltype(tag)>;
         constexpr int NF = decltype(nfc)::value;
         const ScalarArgs<T> A = args(tag);
+        if (g.site_red) return launch_site<T, NF>(kEnergy, A, g.nblocks, st);
         if (g.rows) return launch_rows<T, NF>(g.N, g.rows_ty, g.rows_pf, g.rows_vw, kEnergy, A, g.nblocks, st);
         if (g.plane) return launch_plane<T, NF>(g.plane_cfg, kEnergy, A, g.nblocks, st);
         return launch_tile<T, NF>(g.tile, kEnergy, A, g.nblocks, st);
@@ -2251,8 +2307,8 @@ lat_status lattice_stats(lat_ctx *c, int reset, lat_stats *out)
     }
     out->blocks = c->nblocks;
     out->threads = stage_threads(c);
-    out->tile_x = c->rows ? c->N : (c->plane ? c->tiles_y : kTiles[c->tile].tx);
-    out->tile_y = c->rows ? c->rows_ty : (c->plane ? 1 : kTiles[c->tile].ty);
+    out->tile_x = c->site_red ? kSiteThreads : (c->rows ? c->N : (c->plane ? c->tiles_y : kTiles[c->tile].tx));
+    out->tile_y = c->site_red ? 1 : (c->rows ? c->rows_ty : (c->plane ? 1 : kTiles[c->tile].ty));
     out->z_chunk = c->zc;
     if (reset) {
         std::memset(c->launches, 0, sizeof(c->launches));

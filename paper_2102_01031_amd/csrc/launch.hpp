@@ -42,6 +42,12 @@ struct PlaneCfg {
 template <typename T, int NF>
 hipError_t launch_plane(const PlaneCfg &c, int variant, const ScalarArgs<T> &a, int nb, hipStream_t s);
 
+// one pass of the one-site-per-thread kernel (stage_site.hpp): any N with
+// N^3 sizeof(T) < 2^32; blocks of kSiteThreads
+constexpr int kSiteThreads = 256;
+template <typename T, int NF>
+hipError_t launch_site(int variant, const ScalarArgs<T> &a, int nb, hipStream_t s);
+
 // the lf_slab instance for S steps per launch and ZS planes per block, and its
 // dynamic LDS for yb rows per block; false if that shape is not compiled
 template <typename T, int NF>
