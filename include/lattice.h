@@ -233,8 +233,8 @@ lat_status lattice_energy_batch(lat_ctx *ctx, int32_t r, lat_energies *out);
  * delta[b] = k_b^3/(2 pi^2) (dx/N)^3 sum[b]/(4 pi b^2) with k_b = b k_IR,
  * k_IR = 2 pi/(N dx) (delta[0] = 0), so that sum_{b>=1} (k_IR/k_b) delta[b]
  * = <f^2> - <f>^2 (eq. discretePSII).  Float64 transform whatever the field
- * precision (the library's own line transforms for N up to 512 without a prime
- * factor above 7, hipFFT otherwise); bin sums are accumulated in an order that may vary at
+ * precision (the library's own line transforms up to N = 512 where N times its
+ * largest prime factor above 7 is at most 65536, hipFFT otherwise); bin sums are accumulated in an order that may vary at
  * the last bit.  The transform buffers (about 2 N^3 doubles) are allocated on
  * the first call.  Synchronizes the context stream.  Errors: LAT_EINVAL for a
  * batch context, a field or array out of range, or nbins outside [1, 448]. */
@@ -255,7 +255,7 @@ lat_status lattice_spectrum(lat_ctx *ctx, int32_t field, int32_t which, int32_t 
  * homogeneous charge that no periodic field can absorb: after the call the
  * Gauss residual is -<rho^a> at every site (zero for charged fluctuations
  * whose modes carry no charge, as the paper's constrained phases give).
- * float64 hipFFT transforms; buffers and plans as lattice_spectrum's.
+ * float64 hipFFT transforms; buffers and plans are kept like lattice_spectrum's.
  * Synchronizes the stream.  Errors: LAT_EINVAL for other models or a batch
  * context, LAT_ESTATE, LAT_ENOMEM, LAT_EHIP. */
 lat_status lattice_gauss_init(lat_ctx *ctx, double *mean_charge);
@@ -388,8 +388,8 @@ typedef struct lat_grad_out {
  * until lattice_destroy.  N^3 must stay below 2^32 (LAT_EUNSUPPORTED).
  * LAT_OBS_SPECTRUM_BIN seeds the adjoint with dDelta(b)/dphi_s: the
  * unnormalised inverse transform of phi_s's spectrum kept on shell b, scaled
- * by 2 c_b (hipFFT float64 transforms; their buffers and plans are kept like
- * lattice_spectrum's).  A bad observable, field, bin or a nonzero reserved
+ * by 2 c_b (the transforms of lattice_spectrum; their buffers and plans are kept
+ * like its).  A bad observable, field, bin or a nonzero reserved
  * member gives LAT_EINVAL.  Synchronises the stream. */
 lat_status lattice_grad(lat_ctx *ctx, const lat_grad_spec *spec, lat_grad_out *out);
 

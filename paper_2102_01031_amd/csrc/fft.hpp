@@ -13,7 +13,8 @@
 // A pass reads and writes the spectrum once, and the last one only reads it:
 // bound by memory.  At 256^3 in float64 one spectrum moves 0.70 GB.
 // Lines are transformed by Stockham's self-sorting algorithm with radices 8, 4, 2,
-// 3, 5 and 7, one butterfly per thread and stage where a block has the threads, so
+// 3, 5 and 7 (a plain sum per output for larger primes, between two buffers after a
+// copy into LDS), one butterfly per thread and stage where a block has the threads, so
 // that a stage can write over the LDS buffer it read (half the LDS of two buffers,
 // twice the blocks per CU); the first stage reads its points from memory and the
 // last stage of the y pass writes them without another trip through LDS.  At 256^3
@@ -39,7 +40,9 @@ __device__ __forceinline__ double2 cmi(double2 a) { return double2{a.y, -a.x}; }
 template <int R>
 __device__ __forceinline__ void dft(double2 (&v)[R])
 {
-    if constexpr (R == 2) {
+    if constexpr (R == 1) {
+        (void)v;
+    } else if constexpr (R == 2) {
         const double2 a = v[0];
         v[0] = cadd(a, v[1]);
         v[1] = csub(a, v[1]);
@@ -177,6 +180,58 @@ __device__ __forceinline__ void fft_stage(const FftPlan &P, unsigned Ns, unsigne
     __syncthreads();
 }
 
+// A stage of odd radix r, its sums taken over the r points as they lie in LDS (never
+// in place): for the prime factors above 7, which have no butterfly of their own.  In
+// a first stage (no roots on its points) a thread takes outputs q and r - q of a
+// butterfly, which share the sums and differences of the points p and r - p; one
+// output per thread and turn otherwise.  r / 2 complex products per output: a 61^3
+// transform's three passes cost less than their launches, a spectrum and an occupation
+// number of a 251^3 field 4.2 ms (7.0 with single outputs, 4.5 with the library).
+template <bool COLS, typename LD, typename ST>
+__device__ __forceinline__ void fft_stage_prime(unsigned r, const FftPlan &P, unsigned Ns, unsigned lines,
+                                                const double2 *tw, LD ld, ST st)
+{
+    const unsigned N = (unsigned)P.N, M = N / r;
+    if (Ns == 1) {
+        const unsigned h = (r + 1) / 2, per = M * h, total = lines * per;
+        for (unsigned b = threadIdx.x; b < total; b += blockDim.x) {
+            const unsigned l = COLS ? b % kFftCols : b / per, e = COLS ? b / kFftCols : b - l * per;
+            const unsigned j = e / h, q = e - j * h;
+            double2 A = ld(l, j), B{0.0, 0.0};
+            unsigned t = 0;
+#pragma unroll 4
+            for (unsigned p = 1; p < h; ++p) {
+                t += q * M;
+                if (t >= N) t -= N;
+                const double2 x = ld(l, j + p * M), y = ld(l, j + (r - p) * M), w = tw[t];
+                A.x += w.x * (x.x + y.x);
+                A.y += w.x * (x.y + y.y);
+                B.x += w.y * (x.x - y.x);
+                B.y += w.y * (x.y - y.y);
+            }
+            st(l, j * r + q, double2{A.x - B.y, A.y + B.x});
+            if (q) st(l, j * r + r - q, double2{A.x + B.y, A.y - B.x});
+        }
+    } else {
+        const unsigned total = lines * N;
+        for (unsigned b = threadIdx.x; b < total; b += blockDim.x) {
+            const unsigned l = COLS ? b % kFftCols : b / N, o = COLS ? b / kFftCols : b - l * N;
+            // output o = (j / Ns) Ns r + j % Ns + q Ns of butterfly j
+            const unsigned hi = o / (Ns * r), rest = o - hi * (Ns * r), q = rest / Ns, k = rest - q * Ns;
+            const unsigned j = hi * Ns + k, step = k * (N / (Ns * r)) + q * M;   // root of point p: tw[p step]
+            double2 acc = ld(l, j);
+            unsigned t = 0;
+            for (unsigned p = 1; p < r; ++p) {
+                t += step;
+                if (t >= N) t -= N;
+                acc = cadd(acc, cmul(ld(l, j + p * M), tw[t]));
+            }
+            st(l, o, acc);
+        }
+    }
+    __syncthreads();
+}
+
 template <bool COLS, typename LD, typename ST>
 __device__ __forceinline__ void fft_any(int r, const FftPlan &P, unsigned Ns, unsigned lines, const double2 *tw, LD ld,
                                         ST st)
@@ -187,19 +242,20 @@ __device__ __forceinline__ void fft_any(int r, const FftPlan &P, unsigned Ns, un
     case 2: fft_stage<2, COLS>(P, Ns, lines, tw, ld, st); break;
     case 3: fft_stage<3, COLS>(P, Ns, lines, tw, ld, st); break;
     case 5: fft_stage<5, COLS>(P, Ns, lines, tw, ld, st); break;
-    default: fft_stage<7, COLS>(P, Ns, lines, tw, ld, st); break;
+    case 7: fft_stage<7, COLS>(P, Ns, lines, tw, ld, st); break;
+    case 1: fft_stage<1, COLS>(P, Ns, lines, tw, ld, st); break;
+    default: fft_stage_prime<COLS>((unsigned)r, P, Ns, lines, tw, ld, st); break;
     }
 }
 
 // Transform of `lines` lines: the first stage reads through `in`, the last one
-// writes through `out`, the stages between them through LDS.  lds: the line buffer
-// (two of them unless P.inplace).  Every thread of the block calls it.
+// writes through `out`, the stages between them through LDS: first into b, then from
+// b into a, and so on (a == b if P.inplace).  Every thread of the block calls it.
 template <bool COLS, typename LD, typename ST>
-__device__ __forceinline__ void fft_lines(const FftPlan &P, unsigned lines, const double2 *tw, double2 *lds, LD in,
-                                          ST out)
+__device__ __forceinline__ void fft_lines(const FftPlan &P, unsigned lines, const double2 *tw, double2 *a, double2 *b,
+                                          LD in, ST out)
 {
     const unsigned pitch = (unsigned)(COLS ? P.pitch : P.xpitch);
-    double2 *a = lds, *b = P.inplace ? lds : lds + lines * pitch;
     auto rd = [&](unsigned l, unsigned i) { return a[l * pitch + fft_slot<COLS>(i)]; };
     auto wr = [&](unsigned l, unsigned i, double2 v) { b[l * pitch + fft_slot<COLS>(i)] = v; };
     if (P.nst == 1) {
@@ -228,15 +284,15 @@ __global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_waves_pe
 {
     extern __shared__ double2 fft_lds[];
     double2 *tw = fft_lds, *a = tw + P.N;
-    double2 *z = a + (P.inplace ? 0 : P.lines * P.xpitch);   // the last stage's result
-    if (!P.inplace && P.nst % 2 == 0) z = a;
+    double2 *b = a + (P.inplace ? 0 : P.lines * P.xpitch);
+    double2 *z = P.nst % 2 == 0 ? a : b;                  // the last stage's result
     const unsigned N = (unsigned)P.N, rows = N * N;
     const unsigned nl = pairs ? rows : (rows + 1) / 2;    // complex lines in all
     const unsigned l0 = blockIdx.x * (unsigned)P.lines;
     const unsigned mine = min((unsigned)P.lines, nl - l0);
     for (unsigned i = threadIdx.x; i < N; i += blockDim.x) tw[i] = P.tw[i];
     fft_lines<false>(
-        P, mine, tw, a,
+        P, mine, tw, a, b,
         [&](unsigned l, unsigned x) {
             double2 v;
             if (pairs) {
@@ -286,7 +342,8 @@ static __global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_w
     // the first stage's reads all happen before the last stage's writes (the LDS
     // stages between them, or the in-place stage's barrier)
     fft_lines<true>(
-        P, kFftCols, tw, a, [&](unsigned l, unsigned i) { return G[i * (unsigned)P.HP + l]; },
+        P, kFftCols, tw, a, a + (P.inplace ? 0 : kFftCols * P.pitch),
+        [&](unsigned l, unsigned i) { return G[i * (unsigned)P.HP + l]; },
         [&](unsigned l, unsigned i, double2 v) { G[i * (unsigned)P.HP + l] = v; });
 }
 
@@ -312,7 +369,7 @@ fft_z_bin(const double2 *__restrict__ G0, const double2 *__restrict__ G1, int nq
 {
     extern __shared__ double2 fft_lds[];
     double2 *tw = fft_lds, *a = tw + P.N;
-    const double2 *res = a + (!P.inplace && P.nst % 2 == 1 ? kFftCols * P.pitch : 0);   // the last stage's result
+    double2 *b = a + (P.inplace ? 0 : kFftCols * P.pitch), *res = P.nst % 2 == 0 ? a : b;   // res: the last stage's result
     double *bins = (double *)(a + (P.inplace ? 1 : 2) * kFftCols * P.pitch);            // [nq][nbins]
     unsigned *cnt = (unsigned *)(bins + nq * nbins);                                    // [nbins]
     const int N = P.N, tiles = P.HP / kFftCols, H = N / 2 + 1;
@@ -329,26 +386,113 @@ fft_z_bin(const double2 *__restrict__ G0, const double2 *__restrict__ G1, int nq
         const int ny = y <= N / 2 ? y : y - N;
         __syncthreads();   // the bins' reset; the tile before has been read
         fft_lines<true>(
-            P, kFftCols, tw, a, [&](unsigned l, unsigned i) { return G[i * plane + l]; },
-            [&](unsigned l, unsigned i, double2 v) { ((double2 *)res)[l * P.pitch + i] = v; });
+            P, kFftCols, tw, a, b, [&](unsigned l, unsigned i) { return G[i * plane + l]; },
+            [&](unsigned l, unsigned i, double2 v) { res[l * P.pitch + i] = v; });
 #pragma unroll 1
         for (int e = threadIdx.x; e < N * kFftCols; e += blockDim.x) {
             const int l = e % kFftCols, z = e / kFftCols, kx = tile * kFftCols + l;
             const int nz = z <= N / 2 ? z : z - N;
-            const int b = shell_of(kx * kx + ny * ny + nz * nz);
-            if (kx >= H || b >= nbins) continue;
+            const int bin = shell_of(kx * kx + ny * ny + nz * nz);
+            if (kx >= H || bin >= nbins) continue;
             const unsigned w = (kx == 0 || 2 * kx == N) ? 1u : 2u;
             const double2 f = res[l * P.pitch + z];
-            atomicAdd(&bins[q * nbins + b], (double)w * (f.x * f.x + f.y * f.y));
+            atomicAdd(&bins[q * nbins + bin], (double)w * (f.x * f.x + f.y * f.y));
             // the modes -ny and -nz lie in the same bin: a quarter of the modes counts them all
             if (q == 0 && 2 * y <= N && 2 * z <= N)
-                atomicAdd(&cnt[b], w * (y == 0 || 2 * y == N ? 1u : 2u) * (z == 0 || 2 * z == N ? 1u : 2u));
+                atomicAdd(&cnt[bin], w * (y == 0 || 2 * y == N ? 1u : 2u) * (z == 0 || 2 * z == N ? 1u : 2u));
         }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < nq * nbins; i += blockDim.x) part[(size_t)i * gridDim.x + blockIdx.x] = bins[i];
     for (int i = threadIdx.x; i < nbins; i += blockDim.x)
         part[(size_t)(nq * nbins + i) * gridDim.x + blockIdx.x] = (double)cnt[i];
+}
+
+// Derivative of one bin's power with respect to the field, after the x and y passes:
+// per tile the z transform, the modes of shell `bin` times `scale` and zeros for the
+// others, conjugated, and the z transform again, in place in G; the y pass and
+// fft_x_back then end at the real field, since a real field is the forward transform
+// of its conjugated spectrum.  part[block]: the tile's share of the shell's power
+// (w |F|^2, mirror modes counted).  Tiles that hold no mode of the shell are zeroed
+// unread.
+static __global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
+fft_z_shell(double2 *__restrict__ G, const FftPlan P, int bin, double scale, double *__restrict__ part)
+{
+    extern __shared__ double2 fft_lds[];
+    __shared__ double red[kFftMaxThreads / 64];
+    double2 *tw = fft_lds, *a = tw + P.N;
+    double2 *b = a + (P.inplace ? 0 : kFftCols * P.pitch), *res = P.nst % 2 == 0 ? a : b, *oth = res == a ? b : a;
+    const int N = P.N, tiles = P.HP / kFftCols, H = N / 2 + 1;
+    const size_t plane = (size_t)N * P.HP;
+    const int lid = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int tile = lid % tiles, y = lid / tiles, ny = y <= N / 2 ? y : y - N;
+    double2 *T = G + (size_t)y * P.HP + tile * kFftCols;
+    // |k|^2 of the tile's modes lies between these two
+    const int k0 = tile * kFftCols, k1 = min(k0 + kFftCols - 1, N / 2);
+    const int lo = k0 * k0 + ny * ny, hi = k1 * k1 + ny * ny + (N / 2) * (N / 2);
+    double acc = 0.0;
+    if (lo < (bin + 1) * (bin + 1) && hi >= bin * bin) {
+        for (int i = threadIdx.x; i < N; i += blockDim.x) tw[i] = P.tw[i];
+        fft_lines<true>(
+            P, kFftCols, tw, a, b, [&](unsigned l, unsigned i) { return T[i * plane + l]; },
+            [&](unsigned l, unsigned i, double2 v) { res[l * P.pitch + i] = v; });
+        for (int e = threadIdx.x; e < N * kFftCols; e += blockDim.x) {
+            const int l = e % kFftCols, z = e / kFftCols, kx = k0 + l;
+            const int nz = z <= N / 2 ? z : z - N;
+            double2 f = res[l * P.pitch + z];
+            if (kx < H && shell_of(kx * kx + ny * ny + nz * nz) == bin) {
+                acc += (kx == 0 || 2 * kx == N ? 1.0 : 2.0) * (f.x * f.x + f.y * f.y);
+                f = double2{scale * f.x, -scale * f.y};
+            } else {
+                f = double2{0.0, 0.0};
+            }
+            res[l * P.pitch + z] = f;
+        }
+        __syncthreads();
+        fft_lines<true>(
+            P, kFftCols, tw, res, oth, [&](unsigned l, unsigned i) { return res[l * P.pitch + i]; },
+            [&](unsigned l, unsigned i, double2 v) { T[i * plane + l] = v; });
+    } else {
+        for (int e = threadIdx.x; e < N * kFftCols; e += blockDim.x)
+            T[(size_t)(e / kFftCols) * plane + e % kFftCols] = double2{0.0, 0.0};
+    }
+    const double s = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int i = 0; i < (int)(blockDim.x / 64); ++i) t += red[i];
+        part[lid] = t;
+    }
+}
+
+// Two real rows per complex line from their conjugated half spectra (fft_z_shell and
+// the y pass after it): the line A + i B, whose upper half follows from the symmetry of
+// real transforms, transforms to the rows a + i b.
+static __global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
+fft_x_back(const double2 *__restrict__ G, double *__restrict__ f, const FftPlan P)
+{
+    extern __shared__ double2 fft_lds[];
+    double2 *tw = fft_lds, *a = tw + P.N;
+    const unsigned N = (unsigned)P.N, rows = N * N, nl = (rows + 1) / 2;
+    const unsigned l0 = blockIdx.x * (unsigned)P.lines;
+    const unsigned mine = min((unsigned)P.lines, nl - l0);
+    for (unsigned i = threadIdx.x; i < N; i += blockDim.x) tw[i] = P.tw[i];
+    fft_lines<false>(
+        P, mine, tw, a, a + (P.inplace ? 0 : P.lines * P.xpitch),
+        [&](unsigned l, unsigned x) {
+            const size_t r = 2 * (size_t)(l0 + l);
+            const bool up = x > N / 2;
+            const unsigned k = up ? N - x : x;
+            const double sg = up ? -1.0 : 1.0;
+            const double2 A = G[r * P.HP + k], B = r + 1 < rows ? G[(r + 1) * P.HP + k] : double2{0.0, 0.0};
+            return double2{A.x - sg * B.y, sg * A.y + B.x};
+        },
+        [&](unsigned l, unsigned i, double2 v) {
+            const size_t r = 2 * (size_t)(l0 + l);
+            f[r * N + i] = v.x;
+            if (r + 1 < rows) f[(r + 1) * N + i] = v.y;
+        });
 }
 
 // out[row] = sum of the row's nb block values, one block per row, fixed order

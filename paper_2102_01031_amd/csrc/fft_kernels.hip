@@ -35,7 +35,24 @@ bool fft_radices(int N, FftPlan *p)
     p->threads = std::min(kFftMaxThreads, std::max(64, (most + 63) / 64 * 64));
     p->inplace = most <= p->threads;
     p->lines = kFftCols;
-    return n == 1;
+    if (n > 1) {
+        // prime factors above 7: summed between two LDS buffers, after a stage of
+        // radix 1 that brings the lines there.  Their cost grows with N r: spectrum and
+        // occupation number 61^3 94 us (library transform 688), 251^3 2.6 ms (4.5),
+        // 334 = 2 167 7.0 ms (7.0), 382 = 2 191 10.3 ms (9.4), 509^3 47 ms (35); the
+        // library's plan costs 140 ms and more once per size besides
+        int big[kFftMaxStages], nb = 0;
+        for (int r = 11; n > 1 && nb < kFftMaxStages; r += 2)
+            for (; n % r == 0 && nb < kFftMaxStages; n /= r) big[nb++] = r;
+        if (n > 1 || N * big[nb - 1] > 65536 || p->nst + nb + 1 > kFftMaxStages) return false;
+        for (int i = p->nst - 1; i >= 0; --i) p->rad[i + nb + 1] = p->rad[i];
+        p->rad[0] = 1;
+        for (int i = 0; i < nb; ++i) p->rad[1 + i] = big[i];
+        p->nst += nb + 1;
+        p->inplace = 0;
+        p->threads = std::min(kFftMaxThreads, (kFftCols * (N + 1) / 2 + 63) / 64 * 64);
+    }
+    return true;
 }
 
 void fft_roots(int N, double2 *tw)
@@ -85,6 +102,29 @@ hipError_t fft_spectra(const FftPlan &p, bool f32, const void *f0, const void *f
     hipLaunchKernelGGL(fft_z_bin, dim3(nb), dim3(p.threads), lds, st, G0, G1, nq, p, nbins, part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return sum_rows(part, nb, (nq + 1) * nbins, out, st);
+}
+
+hipError_t fft_shell_seed(const FftPlan &p, const double *f0, int bin, double scale, double2 *G, double *part,
+                          double *power, double *out, hipStream_t st)
+{
+    hipError_t e = x_pass<double>(p, f0, nullptr, 0.0, 0.0, 1, G, nullptr, st);
+    if (e != hipSuccess) return e;
+    const int tiles = p.N * (p.HP / kFftCols);
+    if ((e = allow_lds(fft_y)) != hipSuccess || (e = allow_lds(fft_z_shell)) != hipSuccess ||
+        (e = allow_lds(fft_x_back)) != hipSuccess)
+        return e;
+    const size_t lds = lines_lds(p, p.pitch);
+    hipLaunchKernelGGL(fft_y, dim3(tiles), dim3(p.threads), lds, st, G, (double2 *)nullptr, p);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(fft_z_shell, dim3(tiles), dim3(p.threads), lds, st, G, p, bin, scale, part);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = sum_rows(part, tiles, 1, power, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(fft_y, dim3(tiles), dim3(p.threads), lds, st, G, (double2 *)nullptr, p);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const long nl = ((long)p.N * p.N + 1) / 2;
+    hipLaunchKernelGGL(fft_x_back, dim3((unsigned)((nl + p.lines - 1) / p.lines)), dim3(p.threads),
+                       lines_lds(p, p.xpitch), st, (const double2 *)G, out, p);
+    return hipGetLastError();
 }
 
 hipError_t sum_rows(const double *part, int nb, int rows, double *out, hipStream_t st)

@@ -24,7 +24,8 @@ struct FftPlan {
 
 constexpr int kFftBinBlocks = 1024; // blocks of the z pass (each leaves a row of bins)
 
-// The stages for length N; false if N has a prime factor above 7 or is too long.
+// The stages for length N; false if N is too long, or too long for its largest prime
+// factor.
 bool fft_radices(int N, FftPlan *p);
 // tw[k] = exp(-2 pi i k / N), k < N (host)
 void fft_roots(int N, double2 *tw);
@@ -35,6 +36,13 @@ void fft_roots(int N, double2 *tw);
 // kFftBinBlocks doubles; out may be pinned host memory.
 hipError_t fft_spectra(const FftPlan &p, bool f32, const void *f0, const void *f1, double c0, double c1, int nq,
                        double2 *G0, double2 *G1, int nbins, double *part, double *out, hipStream_t st);
+
+// Derivative of the power of shell `bin`, sum over its modes (mirror modes included)
+// of |F|^2, with respect to the real field f0, times scale / 2: out[n] = scale times
+// the inverse transform (unnormalised) of the shell's modes; *power = the shell sum.
+// G as above, part N HP / kFftCols doubles.
+hipError_t fft_shell_seed(const FftPlan &p, const double *f0, int bin, double scale, double2 *G, double *part,
+                          double *power, double *out, hipStream_t st);
 
 // out[r] = sum of part[r nb .. r nb + nb), r < rows, in a fixed order
 hipError_t sum_rows(const double *part, int nb, int rows, double *out, hipStream_t st);

@@ -1992,8 +1992,8 @@ lat_status lattice_energy_noalloc(const lat_params *p, const lat_fields *f, doub
 }
 
 // Power spectrum of one stored array (sec. 3.1, eq. discretePS): float64
-// real-to-complex transform of the array (hipFFT), radial binning on the
-// device, normalisation on the host.
+// real-to-complex transform of the array (fft.hpp, or hipFFT for the sizes it
+// leaves), radial binning on the device, normalisation on the host.
 constexpr int kSpecBlocks = 1024;
 
 // Partial and pinned result buffers of the shell sums, on first use.
@@ -2012,12 +2012,10 @@ static lat_status ensure_spec_sums(lat_ctx *c)
     return LAT_OK;
 }
 
-// The spectrum passes' plan, roots and nq half-spectrum buffers, on first use;
+// The line transforms' plan, roots and nq half-spectrum buffers, on first use;
 // spec_own = 0 where N needs the library transform.
-static lat_status ensure_spec(lat_ctx *c, int nq)
+static lat_status ensure_lines(lat_ctx *c, int nq)
 {
-    lat_status st = ensure_spec_sums(c);
-    if (st != LAT_OK) return st;
     if (c->spec_own < 0) {
         if (!fft_radices(c->N, &c->spec_plan)) {
             c->spec_own = 0;
@@ -2041,6 +2039,12 @@ static lat_status ensure_spec(lat_ctx *c, int nq)
             return fail(c, LAT_ENOMEM, "spectrum buffers");
         }
     return LAT_OK;
+}
+
+static lat_status ensure_spec(lat_ctx *c, int nq)
+{
+    lat_status st = ensure_spec_sums(c);
+    return st == LAT_OK ? ensure_lines(c, nq) : st;
 }
 
 // Transform buffers and plans on first use (kept until lattice_destroy).
@@ -3339,25 +3343,32 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
         // dO/dphi_s = inverse transform of the shell-b half spectrum scaled by
         // 2 c_b; every other adjoint array starts at zero; O has no explicit q
         const int s = spec->field;
-        GCHK(ensure_fft(c, false));
-        GCHK(ensure_fft(c, true));
         cb = shell_weight(N, c->p.dx, spec->bin);
         hipLaunchKernelGGL(zero_doubles, dim3(1), dim3(64), 0, c->stream, &c->sc->sums[kMaxQ - 2], 2);
         HIPCHK(c, hipGetLastError());
-        HIPCHK(c, hipMemcpyAsync(c->fft_in, c->phi[s][c->cur_phi[s]], bytes, hipMemcpyDeviceToDevice, c->stream));
-        if (hipfftExecD2Z(c->fft_plan, c->fft_in, (hipfftDoubleComplex *)c->fft_out) != HIPFFT_SUCCESS) {
-            cleanup();
-            return fail(c, LAT_EHIP, "hipfftExecD2Z failed");
-        }
-        const size_t H = (size_t)N * N * (N / 2 + 1);
-        hipLaunchKernelGGL(spectrum_shell_seed, dim3((unsigned)((H + kSpecThreads - 1) / kSpecThreads)),
-                           dim3(kSpecThreads), 0, c->stream, c->fft_out, N, (long)spec->bin, 2.0 * cb,
-                           c->adj_partials, c->ticket, &c->sc->sums[kMaxQ - 2]);
-        HIPCHK(c, hipGetLastError());
-        if (hipfftExecZ2D(c->fft_inv, (hipfftDoubleComplex *)c->fft_out, (double *)c->lam[0][s][c->cur_lam[0][s]]) !=
-            HIPFFT_SUCCESS) {
-            cleanup();
-            return fail(c, LAT_EHIP, "hipfftExecZ2D failed");
+        GCHK(ensure_lines(c, 1));
+        double *seed = (double *)c->lam[0][s][c->cur_lam[0][s]];
+        if (c->spec_own > 0) {
+            // (a library plan costs milliseconds, more than the whole run of a small lattice)
+            HIPCHK(c, fft_shell_seed(c->spec_plan, (const double *)c->phi[s][c->cur_phi[s]], (int)spec->bin, 2.0 * cb,
+                                     c->spec_g[0], c->adj_partials, &c->sc->sums[kMaxQ - 2], seed, c->stream));
+        } else {
+            GCHK(ensure_fft(c, false));
+            GCHK(ensure_fft(c, true));
+            HIPCHK(c, hipMemcpyAsync(c->fft_in, c->phi[s][c->cur_phi[s]], bytes, hipMemcpyDeviceToDevice, c->stream));
+            if (hipfftExecD2Z(c->fft_plan, c->fft_in, (hipfftDoubleComplex *)c->fft_out) != HIPFFT_SUCCESS) {
+                cleanup();
+                return fail(c, LAT_EHIP, "hipfftExecD2Z failed");
+            }
+            const size_t H = (size_t)N * N * (N / 2 + 1);
+            hipLaunchKernelGGL(spectrum_shell_seed, dim3((unsigned)((H + kSpecThreads - 1) / kSpecThreads)),
+                               dim3(kSpecThreads), 0, c->stream, c->fft_out, N, (long)spec->bin, 2.0 * cb,
+                               c->adj_partials, c->ticket, &c->sc->sums[kMaxQ - 2]);
+            HIPCHK(c, hipGetLastError());
+            if (hipfftExecZ2D(c->fft_inv, (hipfftDoubleComplex *)c->fft_out, seed) != HIPFFT_SUCCESS) {
+                cleanup();
+                return fail(c, LAT_EHIP, "hipfftExecZ2D failed");
+            }
         }
         HIPCHK(c, hipMemsetAsync(c->lam[0][1 - s][c->cur_lam[0][1 - s]], 0, bytes, c->stream));
         for (int f = 0; f < 2; ++f) HIPCHK(c, hipMemsetAsync(c->lam[1][f][c->cur_lam[1][f]], 0, bytes, c->stream));

@@ -9,7 +9,8 @@
 // with b <= |n| < b + 1.  Per block: sums of |F|^2 and mode counts per bin in
 // LDS, left as one row of block values per bin (part[row gridDim.x + block]) that
 // sum_rows adds up, one block per row.  These kernels and the library transform
-// serve the sizes that fft.hpp does not (N above 512 or with a prime factor above 7).
+// serve the sizes that fft.hpp does not (N above 512, or N times its
+// largest prime factor above 65536).
 #pragma once
 #include "common.hpp"
 
