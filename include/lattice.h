@@ -393,6 +393,17 @@ typedef struct lat_grad_out {
  * member gives LAT_EINVAL.  Synchronises the stream. */
 lat_status lattice_grad(lat_ctx *ctx, const lat_grad_spec *spec, lat_grad_out *out);
 
+/* lattice_grad with a device work array of the caller's (16-byte aligned, used until
+ * the call returns): if it holds lattice_grad_work(ctx, spec) bytes, the forward
+ * sweep keeps the whole trajectory there and the reverse sweep reads it, with no
+ * checkpoints and nothing allocated for them.  lattice_grad_work returns 0 where a
+ * trajectory is not kept: checkpoint_stride > 0, more than 8 GiB (16 N^3 bytes a
+ * step, 32 with the self-consistent expansion), or a context lattice_grad does not
+ * take.  A null or smaller work array gives lattice_grad. */
+size_t lattice_grad_work(const lat_ctx *ctx, const lat_grad_spec *spec);
+lat_status lattice_grad_in(lat_ctx *ctx, const lat_grad_spec *spec, lat_grad_out *out, void *work,
+                           size_t work_bytes);
+
 /* Launch statistics of the stencil kernels, per kernel kind:
  *   0 kick only, 1 kick only + reductions, 2 drift only (the end of a
  *   self-consistent leapfrog call), 3 drift on load + kick + reductions,

@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
 
+#include <functional>
+
 #include <algorithm>
 #include <cmath>
 #include <cstddef>
@@ -160,6 +162,7 @@ struct lat_ctx {
     std::vector<hipEvent_t> spare; // reusable events
     // adjoint scratch: lphi, lpi per field, two buffers each; checkpoints; partials
     void *lam[2][2][2] = {};       // [kind 0 = lphi, 1 = lpi][field][buffer]
+    double *lam_base = nullptr;    // their allocation
     int cur_lam[2][2] = {};
     double *ckpt = nullptr;
     size_t ckpt_count = 0;
@@ -173,6 +176,13 @@ struct lat_ctx {
     int slab_steps = 0, slab_zs = 0, slab_yb = 0;   // lf_slab: steps per launch (0: off), planes and rows per block
     const void *slab_fn = nullptr;      // the lf_slab instance for those, and its dynamic LDS
     size_t slab_lds = 0;
+    // set while a gradient's forward sweep keeps its trajectory: the arrays of a pass,
+    // in place of the ping-pong buffers, which then stay as they are
+    struct PassIO {
+        const void *phi_in[2], *pi_in[2];
+        void *phi_out[2], *pi_out[2], *pi_mid[2];
+    };
+    std::function<void(int variant, int pass, PassIO &)> pass_io;
     double *traj_rec = nullptr;         // set: velocity-Verlet passes store (a, b) of kick point p at traj_rec + 2 p
     double *self_traj = nullptr;        // a, a' of every step, scale records of the checkpoints, scalars
     size_t self_traj_cap = 0;           // (in doubles)
@@ -412,6 +422,29 @@ void site_geometry(lat_ctx *c, const char *spec)
         c->tiles_y = c->chunks_z = 1;
     }
 }
+
+// The stage passes' geometry, to be put back after a spell in another.
+struct StageGeom {
+    bool rows, plane, site_red;
+    int site_nblocks, zc, tiles_x, tiles_y, chunks_z, nblocks;
+    explicit StageGeom(const lat_ctx *c)
+        : rows(c->rows), plane(c->plane), site_red(c->site_red), site_nblocks(c->site_nblocks), zc(c->zc),
+          tiles_x(c->tiles_x), tiles_y(c->tiles_y), chunks_z(c->chunks_z), nblocks(c->nblocks)
+    {
+    }
+    void restore(lat_ctx *c) const
+    {
+        c->rows = rows;
+        c->plane = plane;
+        c->site_red = site_red;
+        c->site_nblocks = site_nblocks;
+        c->zc = zc;
+        c->tiles_x = tiles_x;
+        c->tiles_y = tiles_y;
+        c->chunks_z = chunks_z;
+        c->nblocks = nblocks;
+    }
+};
 
 // Energy pass geometry of the whole-row kernel.  Read-only, the pass needs
 // more bytes in flight than the stage passes' one wave per SIMD give: at
@@ -705,6 +738,17 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
         a.fin_in = lk->fin_in;
         a.fin_out = lk->fin_out;
     }
+    if (c->pass_io) {
+        lat_ctx::PassIO x{};
+        c->pass_io(variant, pass_index, x);
+        for (int f = 0; f < c->nf; ++f) {
+            a.phi_in[f] = (const T *)x.phi_in[f];
+            a.pi_in[f] = (const T *)x.pi_in[f];
+            a.phi_out[f] = (T *)x.phi_out[f];
+            a.pi_out[f] = (T *)x.pi_out[f];
+            a.pi_mid[f] = (T *)x.pi_mid[f];
+        }
+    }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (c->profiling) {
         lat_status st = timing_begin(c, &ev0, &ev1);
@@ -744,6 +788,7 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
         if (st != LAT_OK) return st;
     }
     c->launches[variant_kind(variant)] += 1;
+    if (c->pass_io) return LAT_OK;
     for (int f = 0; f < c->nf; ++f) {
         if (io.wphi) c->cur_phi[f] ^= 1;
         if (io.wpi && io.pi_halo) c->cur_pi[f] ^= 1;
@@ -846,7 +891,7 @@ void drop_step_graphs(lat_ctx *c)
 template <typename F>
 lat_status launch_passes(lat_ctx *c, int64_t key_n, int64_t passes, F &&enqueue)
 {
-    if (c->profiling || passes < kGraphMinPasses || std::getenv("LATTICE_NO_GRAPH")) return enqueue(c->stream);
+    if (c->profiling || c->pass_io || passes < kGraphMinPasses || std::getenv("LATTICE_NO_GRAPH")) return enqueue(c->stream);
     for (int f = 0; f < c->nf; ++f)
         if (c->cur_phi[f] || c->cur_pi[f]) return enqueue(c->stream);
     if (!c->capture_stream && hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) != hipSuccess)
@@ -955,6 +1000,18 @@ lat_status upload_coef(lat_ctx *c, size_t n)
     return LAT_OK;
 }
 
+// arrays of the lattice's size copied in one launch: each copy of its own costs a
+// launch gap, more than the copy itself on small lattices (two arrays of 32^3: 6 us)
+lat_status copy_all(lat_ctx *c, const CopySet &cs)
+{
+    if (cs.n == 0) return LAT_OK;
+    const size_t words = c->vol * c->esize / 4;
+    const unsigned nb = (unsigned)std::min<size_t>((words / 4 + 255) / 256 + 1, 2048);
+    hipLaunchKernelGGL(copy_arrays, dim3(nb, cs.n), dim3(256), 0, c->stream, cs, words);
+    HIPCHK(c, hipGetLastError());
+    return LAT_OK;
+}
+
 // copy shadow buffers back so the caller's arrays hold the state
 lat_status settle(lat_ctx *c)
 {
@@ -977,14 +1034,7 @@ lat_status settle(lat_ctx *c)
         for (int k = 0; k < 12; ++k) back(c->lnk[k], one = 1);
         c->cur_su2 = 0;
     }
-    if (cs.n == 0) return LAT_OK;
-    // one launch for all of them: each copy of its own costs a launch gap, more
-    // than the copy itself on small lattices (two arrays of 32^3: 6 us)
-    const size_t words = c->vol * c->esize / 4;
-    const unsigned nb = (unsigned)std::min<size_t>((words / 4 + 255) / 256 + 1, 2048);
-    hipLaunchKernelGGL(copy_arrays, dim3(nb, cs.n), dim3(256), 0, c->stream, cs, words);
-    HIPCHK(c, hipGetLastError());
-    return LAT_OK;
+    return copy_all(c, cs);
 }
 
 // ---------------------------------------------------------------------------
@@ -1337,7 +1387,7 @@ lat_status step_vv(lat_ctx *c, int64_t ns, int dir)
             HIPCHK(c, hipGetLastError());
         }
         for (int64_t p = 0; p <= M; ++p) {
-            const bool odd = M % 2 != 0;
+            const bool odd = M % 2 != 0 && !c->pass_io;
             const int v = self ? (p > 0 ? kDriftKickRed : (odd ? kKickCopyRed : kKickOnlyRed))
                                : (p < M ? kKickDrift : (odd ? kKickCopy : kKickOnly));
             const PassLink lk = self ? pass_link(c, p, kLastSelf, true) : PassLink{};
@@ -1473,10 +1523,7 @@ void free_ctx(lat_ctx *c)
         (void)hipEventDestroy(t.stop);
     }
     for (auto e : c->spare) (void)hipEventDestroy(e);
-    for (int k = 0; k < 2; ++k)
-        for (int f = 0; f < 2; ++f)
-            for (int b = 0; b < 2; ++b)
-                if (c->lam[k][f][b]) (void)hipFree(c->lam[k][f][b]);
+    if (c->lam_base) (void)hipFree(c->lam_base);
     if (c->ckpt) (void)hipFree(c->ckpt);
     if (c->adj_partials) (void)hipFree(c->adj_partials);
     if (c->self_seg) (void)hipFree(c->self_seg);
@@ -1642,7 +1689,8 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
                 if (hipMalloc(&q, 4 * c->vol * sizeof(double4)) != hipSuccess) return bail(LAT_ENOMEM, "record allocation failed");
         su2_geometry(c);
     }
-    c->partial_cap = (size_t)std::max(c->nblocks > 1 ? c->nblocks : 1, c->en_nblocks) * kMaxQ + 64;
+    // (768: the one-site-per-thread kernel's, which a gradient's forward sweep may take)
+    c->partial_cap = (size_t)std::max(std::max(c->nblocks, 768), c->en_nblocks) * kMaxQ + 64;
     if (c->su2) c->partial_cap = su2_partial_capacity(c->N) + 64;
     if (c->u1) {
         u1_geometry(c);
@@ -3140,25 +3188,103 @@ lat_status adj_pass(lat_ctx *c, double dphi, double dlam, double cA, double cB, 
 
 lat_status checkpoint_io(lat_ctx *c, size_t j, bool store)
 {
-    const size_t bytes = c->vol * sizeof(double);
+    CopySet cs{};
     for (int f = 0; f < 2; ++f) {
-        double *slot_phi = c->ckpt + (j * 4 + (size_t)f) * c->vol;
-        double *slot_pi = c->ckpt + (j * 4 + 2 + (size_t)f) * c->vol;
-        void *phi = c->phi[f][c->cur_phi[f]], *pi = c->pi[f][c->cur_pi[f]];
-        if (store) {
-            HIPCHK(c, hipMemcpyAsync(slot_phi, phi, bytes, hipMemcpyDeviceToDevice, c->stream));
-            HIPCHK(c, hipMemcpyAsync(slot_pi, pi, bytes, hipMemcpyDeviceToDevice, c->stream));
-        } else {
-            HIPCHK(c, hipMemcpyAsync(phi, slot_phi, bytes, hipMemcpyDeviceToDevice, c->stream));
-            HIPCHK(c, hipMemcpyAsync(pi, slot_pi, bytes, hipMemcpyDeviceToDevice, c->stream));
+        void *slot[2] = {c->ckpt + (j * 4 + (size_t)f) * c->vol, c->ckpt + (j * 4 + 2 + (size_t)f) * c->vol};
+        void *state[2] = {c->phi[f][c->cur_phi[f]], c->pi[f][c->cur_pi[f]]};
+        for (int w = 0; w < 2; ++w) {
+            cs.src[cs.n] = (const unsigned *)(store ? state[w] : slot[w]);
+            cs.dst[cs.n] = (unsigned *)(store ? slot[w] : state[w]);
+            ++cs.n;
         }
     }
+    return copy_all(c, cs);
+}
+
+// The arrays a gradient needs besides the state, lphi and lpi of both fields, two buffers
+// each, in `work` or in one allocation of the context's (beyond a megabyte each costs
+// 12 us and its release 18)
+lat_status place_lam(lat_ctx *c, double *work)
+{
+    if (!work && !c->lam_base && hipMalloc(&c->lam_base, 8 * c->vol * sizeof(double)) != hipSuccess) {
+        c->lam_base = nullptr;
+        return fail(c, LAT_ENOMEM, "adjoint array allocation failed");
+    }
+    double *b = work ? work : c->lam_base;
+    for (int i = 0; i < 8; ++i) c->lam[i >> 2][(i >> 1) & 1][i & 1] = b + (size_t)i * c->vol;
+    return LAT_OK;
+}
+
+// Work array of a gradient over a kept trajectory, the adjoint arrays and states 1 .. T:
+// no checkpoints to copy, no state to rebuild in the reverse sweep (stage_adjoint.hpp),
+// no steps to run again with the self-consistent expansion.  200 steps of 64^3 take
+// 0.86 GB, 1.7 self-consistent.  It is the caller's, whose allocator keeps it from one
+// gradient to the next: a fresh gigabyte from the driver costs 0.35 ms with its release,
+// and up to 20 ms when its pages are first touched.  0: over 8 GiB, or N too large for
+// the pass that reads it.
+constexpr size_t kTrajectoryBytes = (size_t)8 << 30;
+
+size_t trajectory_doubles(const lat_ctx *c, int64_t T)
+{
+    const size_t per = c->p.expansion == LAT_EXP_SELF ? 4 : 2;
+    if (T < 1 || T > (1LL << 26) || (double)c->vol * 8.0 >= 4294967296.0 ||
+        (8.0 + (double)T * per) * (double)c->vol * 8.0 > (double)kTrajectoryBytes)
+        return 0;
+    return (8 + (size_t)T * per) * c->vol;
+}
+
+// a pass of the reverse sweep on the stored fields phi
+lat_status adj_site_pass(lat_ctx *c, const double *const (&phi)[2], double cc, double d, double kL, double kV,
+                         double *dq_slots)
+{
+    AdjSiteArgs a{};
+    for (int f = 0; f < 2; ++f) {
+        a.phi[f] = phi[f];
+        a.lphi[f] = (double *)c->lam[0][f][c->cur_lam[0][f]];
+        a.lpi_in[f] = (const double *)c->lam[1][f][c->cur_lam[1][f]];
+        a.lpi_out[f] = (double *)c->lam[1][f][c->cur_lam[1][f] ^ 1];
+    }
+    a.N = c->N;
+    a.inv_dx2 = 1.0 / (c->p.dx * c->p.dx);
+    a.lam = c->p.lambda;
+    a.q = c->p.q;
+    a.c = cc;
+    a.kL = kL;
+    a.kV = kV;
+    a.d = d;
+    a.dq_slots = dq_slots;
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    if (c->profiling) {
+        lat_status st = timing_begin(c, &ev0, &ev1);
+        if (st != LAT_OK) return st;
+    }
+    const unsigned nb = (unsigned)((c->vol + kAdjSiteThreads - 1) / kAdjSiteThreads);
+    hipLaunchKernelGGL(adjoint_site, dim3(nb), dim3(kAdjSiteThreads), 0, c->stream, a);
+    HIPCHK(c, hipGetLastError());
+    if (c->profiling) {
+        lat_status st = timing_end(c, ev0, ev1, 7);
+        if (st != LAT_OK) return st;
+    }
+    c->launches[7] += 1;
+    for (int f = 0; f < 2; ++f) c->cur_lam[1][f] ^= 1;
     return LAT_OK;
 }
 
 }  // namespace
 
+extern "C" size_t lattice_grad_work(const lat_ctx *c, const lat_grad_spec *spec)
+{
+    if (!c || !spec || c->batch || c->u1 || c->su2 || c->nf != 2 || c->f32 || spec->checkpoint_stride > 0) return 0;
+    return trajectory_doubles(c, spec->nsteps) * sizeof(double);
+}
+
 extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_grad_out *out)
+{
+    return lattice_grad_in(c, spec, out, nullptr, 0);
+}
+
+extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat_grad_out *out, void *work,
+                                      size_t work_bytes)
 {
     if (!c || !spec || !out) return fail(c, LAT_EINVAL, "null argument");
     c->sums_fresh = false;
@@ -3193,12 +3319,15 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
     lat_status s;
 
     // scratch
-    for (int kk = 0; kk < 2; ++kk)
-        for (int f = 0; f < 2; ++f)
-            for (int b = 0; b < 2; ++b)
-                if (!c->lam[kk][f][b] && hipMalloc(&c->lam[kk][f][b], bytes) != hipSuccess)
-                    return fail(c, LAT_ENOMEM, "adjoint array allocation failed");
-    if (ncp > c->ckpt_count) {
+    // states 1 .. T of the trajectory (phi of both fields, and pi where the reverse
+    // sweep reads it); state 0 is the caller's arrays, which no pass then writes
+    const size_t slot_arrays = self ? 4 : 2;
+    const size_t work_need = lattice_grad_work(c, spec);
+    const bool keep = work && work_need > 0 && work_bytes >= work_need;
+    if (keep && !aligned(work, 16)) return fail(c, LAT_EINVAL, "misaligned work array");
+    if ((s = place_lam(c, keep ? (double *)work : nullptr)) != LAT_OK) return s;
+    double *const hist = keep ? (double *)work + 8 * c->vol : nullptr;
+    if (!keep && ncp > c->ckpt_count) {
         if (c->ckpt) HIPCHK(c, hipFree(c->ckpt));
         c->ckpt = nullptr;
         if (hipMalloc(&c->ckpt, ncp * 4 * bytes) != hipSuccess) {
@@ -3235,7 +3364,7 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
         // the k + 1 states of a segment (phi, pi of both fields) and two
         // generations of the re-run's half-step momenta
         const size_t seg_arrays = ((size_t)k + 1) * 4 + 4;
-        if (seg_arrays > c->self_seg_cap) {
+        if (!keep && seg_arrays > c->self_seg_cap) {
             if (c->self_seg) HIPCHK(c, hipFree(c->self_seg));
             c->self_seg = nullptr;
             if (hipMalloc(&c->self_seg, seg_arrays * bytes) != hipSuccess) {
@@ -3266,6 +3395,18 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
             c->self_part_cap = pneed;
         }
     }
+    // with a kept trajectory the self-consistent passes run on the one-site-per-thread
+    // kernel, which also stores the momenta at the kick points
+    struct Guard {
+        lat_ctx *c;
+        StageGeom g;
+        ~Guard()
+        {
+            c->pass_io = nullptr;
+            g.restore(c);
+        }
+    } guard{c, StageGeom(c)};
+    if (keep && self) site_geometry(c, ",1,1");
     hipEvent_t e0, e1, e2;
     HIPCHK(c, hipEventCreate(&e0));
     HIPCHK(c, hipEventCreate(&e1));
@@ -3293,7 +3434,40 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
     auto drift_d = [&](int64_t p) { return std::pow(scale_at(c, t_start + ((double)p + 0.5) * h), al - 3.0); };
     // ---- forward sweep (leapfrog form of T VV2 steps) with checkpoints
     HIPCHK(c, hipEventRecord(e0, c->stream));
-    GCHK(checkpoint_io(c, 0, true));
+    // where a point's state is: phi (w = 0) or pi of field f at point p, the caller's
+    // arrays at p = 0
+    double *start[2][2] = {{(double *)c->phi[0][c->cur_phi[0]], (double *)c->phi[1][c->cur_phi[1]]},
+                           {(double *)c->pi[0][c->cur_pi[0]], (double *)c->pi[1][c->cur_pi[1]]}};
+    auto at = [&](int64_t p, int w, int f) {
+        return p == 0 ? start[w][f] : hist + ((size_t)(p - 1) * slot_arrays + (size_t)(2 * w + f)) * c->vol;
+    };
+    if (keep) {
+        for (auto &l : c->cur_lam) l[0] = l[1] = 0;
+        // momenta between the passes in the second buffers of lphi and lpi, which the
+        // reverse sweep writes last: one of each field in place, or two in turn
+        auto mom = [&](int64_t p, int f) { return c->lam[self ? (int)(p & 1) : 0][f][1]; };
+        c->pass_io = [&, mom](int variant, int pass, lat_ctx::PassIO &x) {
+            for (int f = 0; f < 2; ++f) {
+                if (variant == kEnergy) {
+                    x.phi_in[f] = at(T, 0, f);
+                    x.pi_in[f] = self ? (void *)at(T, 1, f) : mom(0, f);
+                } else if (self) {   // point `pass`: drift from the point before, both kicks
+                    x.phi_in[f] = at(pass > 0 ? pass - 1 : 0, 0, f);
+                    x.pi_in[f] = pass > 0 ? mom(pass - 1, f) : (void *)start[1][f];
+                    x.phi_out[f] = pass > 0 ? at(pass, 0, f) : nullptr;
+                    x.pi_out[f] = mom(pass, f);
+                    x.pi_mid[f] = pass > 0 ? at(pass, 1, f) : nullptr;
+                } else {             // point `pass`: both kicks, drift to the next point
+                    x.phi_in[f] = at(pass, 0, f);
+                    x.pi_in[f] = pass > 0 ? mom(0, f) : (void *)start[1][f];
+                    x.phi_out[f] = pass < T ? at(pass + 1, 0, f) : nullptr;
+                    x.pi_out[f] = mom(0, f);
+                }
+            }
+        };
+    } else {
+        GCHK(checkpoint_io(c, 0, true));
+    }
     // self-consistent expansion: the library's own VV2 steps, one call per
     // segment between checkpoints, each pass storing (a, a') of its point on
     // the device; the scale factors come back to the host once, at the end
@@ -3304,13 +3478,14 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
     ScaleRecord *rec_dev = self ? (ScaleRecord *)(c->self_traj + 2 * ((size_t)T + 1)) : nullptr;
     if (self) {
         HIPCHK(c, hipMemcpyAsync(rec_dev, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToDevice, c->stream));
-        for (int64_t s0 = 0; s0 < T; s0 += k) {
-            const int64_t len = std::min<int64_t>(k, T - s0);
+        const int64_t span = keep ? T : k;
+        for (int64_t s0 = 0; s0 < T; s0 += span) {
+            const int64_t len = std::min<int64_t>(span, T - s0);
             c->traj_rec = traj_dev + 2 * (size_t)s0;
             const lat_status r = step_vv(c, len, 1);
             c->traj_rec = nullptr;
             GCHK(r);
-            if (s0 + len < T) GCHK(checkpoint_io(c, (size_t)((s0 + len) / k), true));
+            if (!keep && s0 + len < T) GCHK(checkpoint_io(c, (size_t)((s0 + len) / k), true));
         }
         std::vector<double> tr(2 * ((size_t)T + 1));
         HIPCHK(c, hipMemcpyAsync(tr.data(), traj_dev, tr.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -3330,13 +3505,19 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
         GCHK(upload_coef(c, (size_t)T + 1));
         for (int64_t p = 0; p < T; ++p) {
             GCHK(run_pass(c, kKickDrift, (int)p, kLastStore));
-            if ((p + 1) % k == 0 && p + 1 < T) GCHK(checkpoint_io(c, (size_t)((p + 1) / k), true));
+            if (!keep && (p + 1) % k == 0 && p + 1 < T) GCHK(checkpoint_io(c, (size_t)((p + 1) / k), true));
         }
         GCHK(run_pass(c, kKickOnly, (int)T, kLastStore));   // closing half kick: (phi_T, pi_T)
     }
     HIPCHK(c, hipEventRecord(e1, c->stream));
 
     // ---- observable and seed
+    const double *phi_T[2], *pi_T[2];
+    for (int f = 0; f < 2; ++f) {
+        phi_T[f] = keep ? at(T, 0, f) : (const double *)c->phi[f][c->cur_phi[f]];
+        pi_T[f] = !keep ? (const double *)c->pi[f][c->cur_pi[f]]
+                        : (self ? at(T, 1, f) : (const double *)c->lam[0][f][1]);
+    }
     const double V = (double)c->vol;
     double O = 0.0, rho = 0.0, cb = 0.0, la_T = 0.0;
     if (spec_obs) {
@@ -3350,12 +3531,12 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
         double *seed = (double *)c->lam[0][s][c->cur_lam[0][s]];
         if (c->spec_own > 0) {
             // (a library plan costs milliseconds, more than the whole run of a small lattice)
-            HIPCHK(c, fft_shell_seed(c->spec_plan, (const double *)c->phi[s][c->cur_phi[s]], (int)spec->bin, 2.0 * cb,
+            HIPCHK(c, fft_shell_seed(c->spec_plan, phi_T[s], (int)spec->bin, 2.0 * cb,
                                      c->spec_g[0], c->adj_partials, &c->sc->sums[kMaxQ - 2], seed, c->stream));
         } else {
             GCHK(ensure_fft(c, false));
             GCHK(ensure_fft(c, true));
-            HIPCHK(c, hipMemcpyAsync(c->fft_in, c->phi[s][c->cur_phi[s]], bytes, hipMemcpyDeviceToDevice, c->stream));
+            HIPCHK(c, hipMemcpyAsync(c->fft_in, phi_T[s], bytes, hipMemcpyDeviceToDevice, c->stream));
             if (hipfftExecD2Z(c->fft_plan, c->fft_in, (hipfftDoubleComplex *)c->fft_out) != HIPFFT_SUCCESS) {
                 cleanup();
                 return fail(c, LAT_EHIP, "hipfftExecD2Z failed");
@@ -3393,8 +3574,8 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
         HIPCHK(c, hipGetLastError());
         SeedArgs a{};
         for (int f = 0; f < 2; ++f) {
-            a.phi[f] = (const double *)c->phi[f][c->cur_phi[f]];
-            a.pi[f] = (const double *)c->pi[f][c->cur_pi[f]];
+            a.phi[f] = phi_T[f];
+            a.pi[f] = pi_T[f];
             a.lphi[f] = (double *)c->lam[0][f][c->cur_lam[0][f]];
             a.lpi[f] = (double *)c->lam[1][f][c->cur_lam[1][f]];
         }
@@ -3416,7 +3597,19 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
 
     // ---- reverse sweep
     double la = la_T, lb = 0.0, dq_self = 0.0, seed_sum = 0.0;
-    if (!self) {
+    if (keep && !self) {
+        double *slots = c->adj_partials;   // free once the seed has finished
+        hipLaunchKernelGGL(zero_doubles, dim3((seed_blocks + 255) / 256), dim3(256), 0, c->stream, slots, seed_blocks);
+        HIPCHK(c, hipGetLastError());
+        for (int64_t p = T; p >= 0; --p) {
+            const double *ph[2] = {at(p, 0, 0), at(p, 0, 1)};
+            GCHK(adj_site_pass(c, ph, p > 0 && p < T ? h : 0.5 * h, p > 0 ? h * drift_d(p - 1) : 0.0, kick_l(p),
+                               kick_v(p), slots));
+        }
+        hipLaunchKernelGGL(adj_dq_finish, dim3(1), dim3(256), 0, c->stream, (const double *)slots, seed_blocks,
+                           &c->sc->sums[kMaxQ - 1]);
+        HIPCHK(c, hipGetLastError());
+    } else if (!self) {
         // dO/dq: every block of the passes adds its partial to its own slot
         // (c->adj_partials, free once the seed has finished), summed after the
         // sweep, so no pass ends with ticket releases; LATTICE_ENERGY_DEFER=0
@@ -3479,11 +3672,12 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
             return c->self_seg + (((size_t)k + 1) * 4 + (size_t)(2 * (j & 1) + f)) * c->vol;
         };
         const dim3 grid_site((unsigned)seed_blocks), grid_rev((unsigned)nbr), blk(kSelfAdjThreads);
-        for (int64_t s0 = ((T - 1) / k) * k; s0 >= 0; s0 -= k) {
-            const int64_t s1 = std::min<int64_t>(s0 + k, T);
+        const int64_t span = keep ? T : k;
+        for (int64_t s0 = ((T - 1) / span) * span; s0 >= 0; s0 -= span) {
+            const int64_t s1 = std::min<int64_t>(s0 + span, T);
             const int64_t m = s1 == T ? s1 - s0 : s1 - s0 - 1;   // states s0 .. s0 + m
             // re-run: the checkpoint into state 0, then m steps
-            for (int64_t j = 0; j <= m; ++j) {
+            for (int64_t j = 0; !keep && j <= m; ++j) {
                 SelfRerunArgs r{};
                 for (int f = 0; f < 2; ++f) {
                     if (j == 0) {
@@ -3515,8 +3709,8 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
             for (int64_t n = s0 + m; n >= s0; --n) {
                 SelfRevArgs g{};
                 for (int f = 0; f < 2; ++f) {
-                    g.phi[f] = state(n - s0, 0, f);
-                    g.pi[f] = state(n - s0, 1, f);
+                    g.phi[f] = keep ? at(n, 0, f) : state(n - s0, 0, f);
+                    g.pi[f] = keep ? at(n, 1, f) : state(n - s0, 1, f);
                     g.lphi[f] = (double *)c->lam[0][f][c->cur_lam[0][f]];
                     g.lpi_in[f] = (const double *)c->lam[1][f][c->cur_lam[1][f]];
                     g.lpi_out[f] = (double *)c->lam[1][f][c->cur_lam[1][f] ^ 1];
@@ -3549,7 +3743,7 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
             dq_self = sf.dq;
         }
         // the initial state, scale record, time and step count again
-        GCHK(checkpoint_io(c, 0, false));
+        if (!keep) GCHK(checkpoint_io(c, 0, false));
         HIPCHK(c, hipMemcpyAsync(c->sc, rec_dev, sizeof(ScaleRecord), hipMemcpyDeviceToDevice, c->stream));
         c->t = t_start;
         c->step = step_save;
@@ -3557,14 +3751,14 @@ extern "C" lat_status lattice_grad(lat_ctx *c, const lat_grad_spec *spec, lat_gr
     HIPCHK(c, hipEventRecord(e2, c->stream));
 
     // ---- outputs
-    for (int f = 0; f < 2; ++f) {
-        if (out->dO_dphi[f])
-            HIPCHK(c, hipMemcpyAsync(out->dO_dphi[f], c->lam[0][f][c->cur_lam[0][f]], bytes,
-                                     hipMemcpyDeviceToDevice, c->stream));
-        if (out->dO_dpi[f])
-            HIPCHK(c, hipMemcpyAsync(out->dO_dpi[f], c->lam[1][f][c->cur_lam[1][f]], bytes,
-                                     hipMemcpyDeviceToDevice, c->stream));
-    }
+    CopySet res{};
+    for (int w = 0; w < 2; ++w)
+        for (int f = 0; f < 2; ++f)
+            if (void *dst = (w ? out->dO_dpi : out->dO_dphi)[f]) {
+                res.src[res.n] = (const unsigned *)c->lam[w][f][c->cur_lam[w][f]];
+                res.dst[res.n++] = (unsigned *)dst;
+            }
+    GCHK(copy_all(c, res));
     GCHK(settle(c));
     HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));

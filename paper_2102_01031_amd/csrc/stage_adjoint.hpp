@@ -244,6 +244,72 @@ __global__ void __launch_bounds__(TX *TY) adjoint_stage(const AdjArgs g)
     }
 }
 
+// The reverse pass on a stored trajectory: phi_p is read instead of rebuilt, so per site
+//   adjoint kick    lphi += c [kL Lap lpi - kV H_V(phi_p) lpi],  c = cA + cB
+//   coupling        dO/dq as above
+//   adjoint drift   lpi  += d lphi, the drift of the pass below (0 at p = 0)
+// with only lpi read at neighbours: ten arrays in and out instead of sixteen, and the
+// pass is the forward kick and drift with another force.  One site per thread, as
+// stage_site.hpp; lphi in place.  Bound by the launch on small lattices, by the caches
+// above: 64^3 7.1 us a pass (10.0 with adjoint_stage and its checkpoints).
+struct AdjSiteArgs {
+    const double *phi[2];
+    double *lphi[2];
+    const double *lpi_in[2];
+    double *lpi_out[2];
+    int N;                // N^3 8 < 2^32
+    double inv_dx2, lam, q, c, kL, kV, d;
+    double *dq_slots;     // one per block, as AdjArgs::dq_slots
+};
+
+constexpr int kAdjSiteThreads = 256;
+
+__global__ void __launch_bounds__(kAdjSiteThreads) adjoint_site(const AdjSiteArgs g)
+{
+    __shared__ double lds_red[kAdjSiteThreads / 64];
+    const int tid = threadIdx.x;
+    const int lid = xcd_logical_block(blockIdx.x, gridDim.x);
+    const unsigned N = (unsigned)g.N, NN = N * N, V = NN * N;
+    const unsigned n = (unsigned)lid * kAdjSiteThreads + tid;
+    const double slot = tid == 0 ? g.dq_slots[lid] : 0.0;   // ahead of its use at the end
+    double dq = 0.0;
+    if (n < V) {
+        const unsigned yz = n / N, x = n - yz * N, z = yz / N, y = yz - z * N;
+        const unsigned xm = x == 0 ? n + (N - 1) : n - 1, xp = x == N - 1 ? n - (N - 1) : n + 1;
+        const unsigned ym = y == 0 ? n + (NN - N) : n - N, yp = y == N - 1 ? n - (NN - N) : n + N;
+        const unsigned zm = z == 0 ? n + (V - NN) : n - NN, zp = z == N - 1 ? n - (V - NN) : n + NN;
+        double l[2], lap[2], m[2], ph[2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const double *L = g.lpi_in[f];
+            const double c0 = ld32(L, n);
+            l[f] = c0;
+            lap[f] = ((ld32(L, xp) - 2.0 * c0 + ld32(L, xm)) + (ld32(L, yp) - 2.0 * c0 + ld32(L, ym)) +
+                      (ld32(L, zp) - 2.0 * c0 + ld32(L, zm))) * g.inv_dx2;
+            m[f] = ld32(g.lphi[f], n);
+            ph[f] = ld32(g.phi[f], n);
+        }
+        const double u = ph[0], v = ph[1];
+        const double h00 = 3.0 * g.lam * u * u + g.q * v * v, h01 = 2.0 * g.q * u * v, h11 = g.q * u * u;
+        const double a0 = m[0] + g.c * (g.kL * lap[0] - g.kV * (h00 * l[0] + h01 * l[1]));
+        const double a1 = m[1] + g.c * (g.kL * lap[1] - g.kV * (h01 * l[0] + h11 * l[1]));
+        st32(g.lphi[0], n, a0);
+        st32(g.lphi[1], n, a1);
+        st32(g.lpi_out[0], n, l[0] + g.d * a0);
+        st32(g.lpi_out[1], n, l[1] + g.d * a1);
+        dq = g.c * g.kV * (-(l[0] * u * v * v) - (l[1] * u * u * v));
+    }
+    const double ws = wave_sum(dq);
+    if ((tid & 63) == 0) lds_red[tid >> 6] = ws;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < kAdjSiteThreads / 64; ++i) t += lds_red[i];
+        g.dq_slots[lid] = slot + t;
+    }
+}
+
 // Seed of the adjoint from O = (E_K^f + E_G^f)/rho, the energy fraction of
 // field f, at scale factor a (sec. 4.4 energies, eq. EK_EG_EV: E_K =
 // <pi^2>/(2 a^6), E_G = <|grad phi|^2>/(2 a^2)):  with w_s = [s == f] and V = N^3,

@@ -25,8 +25,8 @@
 // chain of scalar adjoints (la, lb, dO/dq) runs on the device, in a fixed order,
 // without a launch of its own.  (3) is the scalar step between points.
 //
-// The states of a segment are re-run from its checkpoint by self_rerun with
-// the scale factors the forward sweep recorded.
+// The states come from the kept trajectory, or are re-run by self_rerun from a
+// segment's checkpoint with the scale factors the forward sweep recorded.
 #pragma once
 #include "common.hpp"
 

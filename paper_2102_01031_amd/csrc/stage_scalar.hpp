@@ -34,6 +34,7 @@ struct ScalarArgs {
     const T *pi_in[2];
     T *phi_out[2];
     T *pi_out[2];
+    T *pi_mid[2];           // one-site-per-thread kernel's drifting passes: if set, the momenta at the kick point
     int N, zc, tiles_x, tiles_y;
     int y_fastest;          // whole-row kernel block order: 0 z chunk fastest, 1 y tile fastest
     int down;               // whole-row kernel: march each z chunk downward

@@ -109,6 +109,9 @@ __global__ void __launch_bounds__(NT) scalar_site(const ScalarArgs<T> g)
                              gz = (double)(up[f][2] - c0[f]);
                 acc[NF + f] += gx * gx + gy * gy + gz * gz;
             }
+            if constexpr (DLOAD) {
+                if (g.pi_mid[f]) st32(g.pi_mid[f], n, pm);
+            }
             const T pn = pm + c2 * F;
             if (WPHI) st32(g.phi_out[f], n, DEND ? c0[f] + de * pn : c0[f]);
             if (WPI) st32(g.pi_out[f], n, pn);

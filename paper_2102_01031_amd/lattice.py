@@ -104,6 +104,10 @@ def lib():
         L.lattice_profile.restype = C.c_int
         L.lattice_grad.argtypes = [vp, C.POINTER(LatGradSpec), C.POINTER(LatGradOut)]
         L.lattice_grad.restype = C.c_int
+        L.lattice_grad_in.argtypes = L.lattice_grad.argtypes + [vp, C.c_size_t]
+        L.lattice_grad_in.restype = C.c_int
+        L.lattice_grad_work.argtypes = [vp, C.POINTER(LatGradSpec)]
+        L.lattice_grad_work.restype = C.c_size_t
         dp = C.POINTER(C.c_double)
         L.lattice_spectrum.argtypes = [vp, C.c_int32, C.c_int32, C.c_int32, dp, dp, C.POINTER(C.c_int64)]
         L.lattice_spectrum.restype = C.c_int
@@ -278,7 +282,17 @@ class Lattice:
         for i in range(2):
             out.dO_dphi[i] = gphi[i].data_ptr() if gphi else None
             out.dO_dpi[i] = gpi[i].data_ptr() if gpi else None
-        _check(lib().lattice_grad(self._ctx, C.byref(spec), C.byref(out)), self._ctx)
+        work, need = None, lib().lattice_grad_work(self._ctx, C.byref(spec))
+        if need:
+            # the trajectory, in torch's memory of the lattice's stream: its allocator
+            # keeps it between gradients; the checkpoints do without it
+            try:
+                with torch.cuda.stream(self.stream):
+                    work = torch.empty(need, dtype=torch.uint8, device="cuda")
+            except torch.OutOfMemoryError:
+                need = 0
+        _check(lib().lattice_grad_in(self._ctx, C.byref(spec), C.byref(out), work.data_ptr() if need else None, need),
+               self._ctx)
         return dict(value=out.value, dO_dq=out.dO_dq, dO_dphi=gphi, dO_dpi=gpi, forward_ms=out.forward_ms,
                     reverse_ms=out.reverse_ms, dO_da0=out.dO_da0, dO_db0=out.dO_db0)
 
