@@ -183,6 +183,7 @@ struct lat_ctx {
         void *phi_out[2], *pi_out[2], *pi_mid[2];
     };
     std::function<void(int variant, int pass, PassIO &)> pass_io;
+    bool by_value = false;              // this call's passes take their coefficients as kernel arguments
     double *traj_rec = nullptr;         // set: velocity-Verlet passes store (a, b) of kick point p at traj_rec + 2 p
     double *self_traj = nullptr;        // a, a' of every step, scale records of the checkpoints, scalars
     size_t self_traj_cap = 0;           // (in doubles)
@@ -399,13 +400,14 @@ bool plane_geometry(lat_ctx *c, const char *spec)
 // 27.6 and 28.2), in at most 512 blocks of a few sites per thread, 768 from 96^3
 // (float32 72^3: 9.4 us in 512, 10.5 in 768; 110^3 18.1 and 16.9).
 // LATTICE_TILE="site[,kick[,red[,blocks]]]" overrides (kick, red: 0 or 1).
+constexpr int kSiteMaxSumBlocks = 768;
 void site_geometry(lat_ctx *c, const char *spec)
 {
     const size_t size = c->f32 ? 4 : 8;
     c->site_red = false;
     c->site_nblocks = 0;
     if ((double)c->vol * size >= 4294967296.0) return;
-    int kick = -1, red = -1, cap = c->N < 96 ? 512 : 768;
+    int kick = -1, red = -1, cap = c->N < 96 ? 512 : kSiteMaxSumBlocks;
     if (spec) std::sscanf(spec, ",%d,%d,%d", &kick, &red, &cap);
     const size_t nb = (c->vol + kSiteThreads - 1) / kSiteThreads;
     const size_t mb = (3 * (size_t)c->nf * size * c->vol) >> 20;
@@ -549,6 +551,14 @@ void stage_geometry(lat_ctx *c)
     set_geometry(c, tile, zc);
 }
 
+// The energy pass alone, whose sums no other pass adds up, takes that kernel wherever
+// the passes without sums do (in at most 768 blocks): 64^3 two float64 fields, the call
+// 26.4 us with the whole-row pass, 20.2 here.  LATTICE_ENERGY_GEOM keeps the rows.
+bool energy_on_site(const lat_ctx *c)
+{
+    return !c->site_red && c->site_nblocks > 0 && c->en_nblocks == 0;
+}
+
 // Launch geometry of a lattice's passes; a LATTICE_TILE that names another
 // kernel keeps every pass on that one.
 void geometry_from_env(lat_ctx *c)
@@ -640,6 +650,7 @@ struct PassLink {
     // defer = 1 on a store-only pass: sums_finish adds this pass's block sums
     // into store_to->sums right after it (inside the pass's timed region)
     ScaleRecord *store_to = nullptr;
+    ScaleRecord *host = nullptr;   // and the record to this pinned copy, so that no copy follows
 };
 
 // The deferred block sums of a store-only pass (the energy pass), added by one
@@ -647,10 +658,13 @@ struct PassLink {
 // reduction) into Sout->sums: the same values as that reduction, with no
 // ticket release in the pass's blocks.
 template <int NT, int NQ>
-__global__ void __launch_bounds__(NT) sums_finish(const double *partials, int nb, ScaleRecord *Sout)
+__global__ void __launch_bounds__(NT) sums_finish(const double *partials, int nb, ScaleRecord *Sout, ScaleRecord *host)
 {
+    constexpr int W = sizeof(ScaleRecord) / sizeof(double), S0 = offsetof(ScaleRecord, sums) / sizeof(double);
+    static_assert(W <= 64, "a record per wave");
     __shared__ double lds_red[(NT / 64) * NQ];
     const int tid = threadIdx.x;
+    const double old = tid < W ? ((const double *)Sout)[tid] : 0.0;
     double part[NQ];
 #pragma unroll
     for (int k = 0; k < NQ; ++k) part[k] = 0.0;
@@ -660,18 +674,22 @@ __global__ void __launch_bounds__(NT) sums_finish(const double *partials, int nb
     }
     double fin[NQ];
     block_sums<NT, NQ>(part, lds_red, fin);
-    if (tid == 0) {
+    if (tid < W) {   // the first wave's lanes all hold the sums
+        double v = old;
 #pragma unroll
-        for (int k = 0; k < NQ; ++k) Sout->sums[k] = fin[k];
+        for (int k = 0; k < NQ; ++k) v = tid == S0 + k ? fin[k] : v;
+        if (tid >= S0 && tid < S0 + NQ) ((double *)Sout)[tid] = v;
+        if (host) ((double *)host)[tid] = v;
     }
 }
 
-hipError_t launch_sums_finish(int NT, int nf, const double *partials, int nb, ScaleRecord *S, hipStream_t st)
+hipError_t launch_sums_finish(int NT, int nf, const double *partials, int nb, ScaleRecord *S, ScaleRecord *host,
+                              hipStream_t st)
 {
 #define SUMS_FIN(nt)                                                                                       \
     if (NT == nt) {                                                                                        \
-        if (nf == 1) hipLaunchKernelGGL((sums_finish<nt, 3>), dim3(1), dim3(nt), 0, st, partials, nb, S); \
-        else hipLaunchKernelGGL((sums_finish<nt, 6>), dim3(1), dim3(nt), 0, st, partials, nb, S);         \
+        if (nf == 1) hipLaunchKernelGGL((sums_finish<nt, 3>), dim3(1), dim3(nt), 0, st, partials, nb, S, host); \
+        else hipLaunchKernelGGL((sums_finish<nt, 6>), dim3(1), dim3(nt), 0, st, partials, nb, S, host);         \
         return hipGetLastError();                                                                          \
     }
     SUMS_FIN(64)
@@ -765,8 +783,17 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
         lp = 0;
     }
     const bool red = variant == kKickOnlyRed || variant == kDriftKickRed || variant == kKickCopyRed || variant == kEnergy;
-    if (red ? c->site_red : c->site_nblocks > 0) {
+    const bool en_site = variant == kEnergy && energy_on_site(c);
+    if (en_site || (red ? c->site_red : c->site_nblocks > 0)) {
+        if (c->by_value) {
+            a.imm = c->coef_host[pass_index];
+            a.by_value = 1;
+        }
         nb = red ? c->nblocks : c->site_nblocks;
+        if (en_site) {
+            a.zc = (c->site_nblocks + kSiteMaxSumBlocks - 1) / kSiteMaxSumBlocks;
+            nb = (c->site_nblocks + a.zc - 1) / a.zc;
+        }
         e = c->nf == 1 ? launch_site<T, 1>(variant, a, nb, stream) : launch_site<T, 2>(variant, a, nb, stream);
     } else if (c->rows)
         e = c->nf == 1 ? launch_rows<T, 1>(c->N, ty, pf, c->rows_vw, variant, a, nb, stream, lp)
@@ -779,8 +806,8 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
                        : launch_tile<T, 2>(c->tile, variant, a, c->nblocks, stream);
     if (e != hipSuccess) return fail(c, LAT_EHIP, std::string("stage launch: ") + hipGetErrorString(e));
     if (lk && lk->defer && lk->store_to) {
-        const int NT = c->rows ? 64 * ty : stage_threads(c);
-        e = launch_sums_finish(NT, c->nf, lk->partials, c->rows ? nb : c->nblocks, lk->store_to, stream);
+        const int NT = en_site ? kSiteThreads : c->rows ? 64 * ty : stage_threads(c);
+        e = launch_sums_finish(NT, c->nf, lk->partials, en_site || c->rows ? nb : c->nblocks, lk->store_to, lk->host, stream);
         if (e != hipSuccess) return fail(c, LAT_EHIP, std::string("sums launch: ") + hipGetErrorString(e));
     }
     if (c->profiling) {
@@ -997,7 +1024,24 @@ lat_status upload_coef(lat_ctx *c, size_t n)
     HIPCHK(c, hipMemcpyAsync(c->coef, c->coef_host, n * sizeof(PassCoef), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipEventRecord(c->ring_ev[k], c->stream));
     c->ring_pending[k] = true;
+    c->by_value = false;
     return LAT_OK;
+}
+
+// The coefficients of a call of `launches` launches on a known background: by value
+// where the kernels take them so and the launches go to the stream one by one, else the
+// n entries uploaded.  The upload and the gap it leaves cost a small lattice's call
+// about 8 us of 60 (ten leapfrog steps of 32^3 and their energies).  A call that is
+// being captured keeps the table.
+lat_status place_coef(lat_ctx *c, size_t n, int64_t launches, bool kernel_takes)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (kernel_takes && launches < kGraphMinPasses && !c->pass_io && c->p.expansion != LAT_EXP_SELF &&
+        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        c->by_value = true;
+        return LAT_OK;
+    }
+    return upload_coef(c, n);
 }
 
 // arrays of the lattice's size copied in one launch: each copy of its own costs a
@@ -1218,7 +1262,8 @@ lat_status slab_launch_t(lat_ctx *c, int64_t first, int steps, hipStream_t st)
     a.inv_dx2 = 1.0 / (c->p.dx * c->p.dx);
     a.lam = c->p.lambda;
     a.q = c->p.potential == LAT_PHI4_CHI2 ? c->p.q : 0.0;
-    a.coef = c->coef + first;
+    a.coef = c->by_value ? nullptr : c->coef + first;
+    for (int i = 0; c->by_value && i < steps; ++i) a.imm[i] = c->coef_host[first + i];
     const dim3 grid((unsigned)((c->N + c->slab_zs - 1) / c->slab_zs),
                     (unsigned)((c->N + c->slab_yb - 1) / c->slab_yb));
     const dim3 blk((unsigned)((((c->slab_yb + 2 * c->slab_steps) * c->N + 63) / 64) * 64));
@@ -1262,9 +1307,9 @@ lat_status step_lf(lat_ctx *c, int64_t ns, int dir)
         P.t = t;
         stag = dir;
     }
-    if ((s = upload_coef(c, (size_t)ns)) != LAT_OK) return s;
+    const int64_t S = std::max(c->slab_steps, 1), nl = (ns + S - 1) / S;
+    if ((s = place_coef(c, (size_t)ns, nl, c->slab_steps > 0 || c->site_nblocks > 0)) != LAT_OK) return s;
     if (c->slab_steps > 0) {
-        const int64_t S = c->slab_steps, nl = (ns + S - 1) / S;
         s = launch_passes(c, dir * ns, nl, [&](hipStream_t st) {
             for (int64_t j = 0; j < nl; ++j) {
                 const int steps = (int)std::min<int64_t>(S, ns - j * S);
@@ -1379,7 +1424,7 @@ lat_status step_vv(lat_ctx *c, int64_t ns, int dir)
             P.dend = p < M ? hn * std::pow(scale_at(c, ts(p) + 0.5 * hn), al - 3.0) : 0.0;
         }
     }
-    if ((s = upload_coef(c, (size_t)M + 2)) != LAT_OK) return s;
+    if ((s = place_coef(c, (size_t)M + 2, M + 1, !self && c->site_nblocks > 0)) != LAT_OK) return s;
     const int mode = self ? kLastSelf : kLastStore;
     s = launch_passes(c, dir * ns, M + 1, [&](hipStream_t st) {
         if (self) {
@@ -1412,7 +1457,7 @@ lat_status energy_sums(lat_ctx *c, double kick_c1)
     P.ka3 = std::pow(a, 3.0 + c->p.alpha);
     P.c1 = kick_c1;
     P.t = c->t;
-    if ((s = upload_coef(c, 1)) != LAT_OK) return s;
+    if ((s = place_coef(c, 1, 1, c->site_red || energy_on_site(c))) != LAT_OK) return s;
     if (c->p.expansion == LAT_EXP_SELF && kick_c1 != 0.0) {
         hipLaunchKernelGGL(self_prologue, dim3(1), dim3(64), 0, c->stream, c->coef, c->sc, c->p.alpha);
         HIPCHK(c, hipGetLastError());
@@ -1425,9 +1470,11 @@ lat_status energy_sums(lat_ctx *c, double kick_c1)
     el.defer = 1;
     el.partials = c->partials;
     el.store_to = c->sc;
-    if ((s = run_pass(c, kEnergy, 0, kLastStore, c->stream, (ed && std::atoi(ed) == 0) ? nullptr : &el)) != LAT_OK)
-        return s;
-    HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
+    el.host = c->sc_host;
+    const bool ticket = ed && std::atoi(ed) == 0;
+    if ((s = run_pass(c, kEnergy, 0, kLastStore, c->stream, ticket ? nullptr : &el)) != LAT_OK) return s;
+    if (ticket)
+        HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return LAT_OK;
 }
@@ -1690,7 +1737,7 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
         su2_geometry(c);
     }
     // (768: the one-site-per-thread kernel's, which a gradient's forward sweep may take)
-    c->partial_cap = (size_t)std::max(std::max(c->nblocks, 768), c->en_nblocks) * kMaxQ + 64;
+    c->partial_cap = (size_t)std::max(std::max(c->nblocks, kSiteMaxSumBlocks), c->en_nblocks) * kMaxQ + 64;
     if (c->su2) c->partial_cap = su2_partial_capacity(c->N) + 64;
     if (c->u1) {
         u1_geometry(c);

@@ -44,6 +44,8 @@ struct ScalarArgs {
     double inv_dx2;
     double lam, q;
     const PassCoef *coef;   // this pass
+    PassCoef imm;           // the same by value (one-site-per-thread kernel, by_value = 1)
+    int by_value;
     PassCoef *coef_next;    // next pass (self-consistent mode)
     double *partials;       // [blocks][3*NF]
     unsigned *ticket;

@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(NT) scalar_site(const ScalarArgs<T> g)
     Raw r;
     if (base < V) load(base, r);   // issued before the prologue's sums
 
-    PassCoef C = *g.coef;
+    PassCoef C = g.by_value ? g.imm : *g.coef;
     if constexpr (RED) {   // the other passes follow no deferring pass
         if (g.fin) {
             __shared__ double lds_coef[4];

@@ -38,7 +38,8 @@ struct SlabArgs {
     T *phi_out[2], *pi_out[2];
     int N, yb, steps;        // rows per block (the last band may own fewer), steps of this launch (1 .. S)
     double inv_dx2, lam, q;
-    const PassCoef *coef;    // coefficients of the launch's first step, then one per step
+    const PassCoef *coef;    // coefficients of the launch's first step, then one per step; null: imm
+    PassCoef imm[5];
 };
 
 // LDS the kernel needs: the step coefficients, then phi of the ZS + 2 S - 2
@@ -88,7 +89,7 @@ __global__ void __launch_bounds__(kSlabMaxThreads) lf_slab(const SlabArgs<T> g)
     }
     if (tid < 5 * S) {
         const int s = tid / 5, m = tid % 5;
-        const PassCoef *C = g.coef + (s < g.steps ? s : 0);
+        const PassCoef *C = (g.coef ? g.coef : g.imm) + (s < g.steps ? s : 0);
         Cl[tid] = m == 0 ? C->c1 : m == 1 ? C->c2 : m == 2 ? C->dend : m == 3 ? C->ka1 : C->ka3;
     }
 
