@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = [os.path.join(CSRC, f) for f in ("lattice.hip", "tile_kernels.hip", "rows_kernels_f64.hip",
                                            "rows_kernels_f32.hip", "plane_kernels_f64.hip", "plane_kernels_f32.hip",
-                                           "site_kernels.hip", "slab_kernels.hip", "fft_kernels.hip")]
+                                           "site_kernels.hip", "pair_kernels.hip", "slab_kernels.hip", "fft_kernels.hip")]
 LIB = os.path.join(CSRC, "liblattice.so")
 
 HIPCC_FLAGS = [

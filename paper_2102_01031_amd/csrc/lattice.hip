@@ -147,6 +147,9 @@ struct lat_ctx {
     bool plane = false;       // plane-run kernel (stage_plane.hpp): tiles_x runs of tiles_y sites per plane
     PlaneCfg plane_cfg{};
     bool site_red = false;    // reducing passes: one-site-per-thread kernel (stage_site.hpp), zc sites per thread
+    // two passes in one (stage_pair.hpp): sites per thread (0: off), planes and runs per plane, sites of a run
+    bool pi_across = false;   // the pass being launched writes the momenta it reads at their own site to the other buffer
+    int pair_xs = 0, pair_zc = 0, pair_runs = 0, pair_seg = 0;
     int site_nblocks = 0;     // other passes: that kernel's blocks (0: the reducing passes' kernel)
     int zc = 0;
     int tiles_x = 0, tiles_y = 0, chunks_z = 0, nblocks = 0;
@@ -551,6 +554,54 @@ void stage_geometry(lat_ctx *c)
     set_geometry(c, tile, zc);
 }
 
+// Two passes in one launch on a known background (stage_pair.hpp), for lattices whose
+// passes stream: three arrays per field of 45 MB or more in float64 (two fields 96^3,
+// 40 MB, 14.6 us a step in single passes, 14.2 in pairs; 110^3, 61 MB, 19.6 and 17.4),
+// 95 MB in float32, whose halves cost as much arithmetic (two fields 160^3, 94 MB, 23.3
+// and 25.6; 176^3, 125 MB, 32.8 and 27.6).  Sites per thread, runs and z chunks: of all
+// cuts the one with the least rounds of 256 blocks (one per CU) times planes, with 6 of
+// a block's start-up, times the threads' sites, whose cost grows a little faster than
+// their number (float64 one field 384^3: 177 us with 6, 188 with 8; 320^3 113 and 107;
+// two fields 256^3: 113 with 3, 121 with 4; 320^3 263 and 238).  LATTICE_PAIR="xs[,zc[,runs]]"
+// overrides, "0": off.
+void pair_geometry(lat_ctx *c)
+{
+    c->pair_xs = 0;
+    const int N = c->N, NN = N * N;
+    if (c->batch || c->u1 || c->su2 || N < 16 || N > kPairThreads || std::getenv("LATTICE_TILE")) return;
+    const size_t size = c->f32 ? 4 : 8;
+    int exs = 0, ezc = 0, eruns = 0;
+    if (const char *e = std::getenv("LATTICE_PAIR")) {
+        if (std::sscanf(e, "%d,%d,%d", &exs, &ezc, &eruns) < 1 || exs <= 0) return;
+    } else if (((3 * c->nf * size * c->vol) >> 20) < (c->f32 ? 95u : 45u)) {
+        return;
+    }
+    double best = 0.0;
+    auto take = [&](int xs, int zc, int runs, double cost) {
+        if (best != 0.0 && cost >= best) return;
+        best = cost;
+        c->pair_xs = xs;
+        c->pair_zc = std::min(std::max(zc, 1), N);
+        c->pair_seg = (NN + runs - 1) / runs;
+        c->pair_runs = (NN + c->pair_seg - 1) / c->pair_seg;
+    };
+    const int few = c->nf == 1 ? (c->f32 ? 8 : 6) : (c->f32 ? 6 : 3), many = c->nf == 1 ? (c->f32 ? 12 : 8) : (c->f32 ? 6 : 4);
+    for (int xs : {few, many}) {
+        if (exs > 0 && xs != exs) continue;
+        // sites of a run: the widened run fits the threads, the four planes the LDS,
+        // and a run and its neighbours no plane twice
+        const long lds_sites = kPairLds / (long)(size * c->nf);
+        const int most = (int)std::min<long>(NN - 4L * N, std::min<long>((long)kPairThreads * xs - 2 * N, (lds_sites - 12L * N) / 4));
+        if (most < 1) continue;
+        const int rmin = (NN + most - 1) / most;
+        if (ezc > 0) take(xs, ezc, std::min(std::max(eruns, rmin), NN), 1.0);
+        for (int z = 1; ezc <= 0 && z <= N; ++z) {
+            const long nb = (long)rmin * ((N + z - 1) / z), rounds = (nb + 255) / 256;
+            take(xs, z, rmin, (double)rounds * (z + 6) * std::pow((double)xs, 1.15));
+        }
+    }
+}
+
 // The energy pass alone, whose sums no other pass adds up, takes that kernel wherever
 // the passes without sums do (in at most 768 blocks): 64^3 two float64 fields, the call
 // 26.4 us with the whole-row pass, 20.2 here.  LATTICE_ENERGY_GEOM keeps the rows.
@@ -719,7 +770,7 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
         a.phi_in[f] = (const T *)c->phi[f][cp];
         a.pi_in[f] = (const T *)c->pi[f][cq];
         a.phi_out[f] = io.wphi ? (T *)c->phi[f][cp ^ 1] : nullptr;
-        a.pi_out[f] = io.wpi ? (io.pi_halo ? (T *)c->pi[f][cq ^ 1] : (T *)c->pi[f][cq]) : nullptr;
+        a.pi_out[f] = io.wpi ? (io.pi_halo || c->pi_across ? (T *)c->pi[f][cq ^ 1] : (T *)c->pi[f][cq]) : nullptr;
     }
     a.N = c->N;
     a.zc = c->zc;
@@ -818,7 +869,7 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
     if (c->pass_io) return LAT_OK;
     for (int f = 0; f < c->nf; ++f) {
         if (io.wphi) c->cur_phi[f] ^= 1;
-        if (io.wpi && io.pi_halo) c->cur_pi[f] ^= 1;
+        if (io.wpi && (io.pi_halo || c->pi_across)) c->cur_pi[f] ^= 1;
     }
     return LAT_OK;
 }
@@ -1286,6 +1337,65 @@ lat_status slab_launch_t(lat_ctx *c, int64_t first, int steps, hipStream_t st)
     return LAT_OK;
 }
 
+// two kick-and-drift passes, points `first` and first + 1, in one launch
+template <typename T>
+lat_status run_pair_t(lat_ctx *c, int64_t first, hipStream_t st)
+{
+    PairArgs<T> a{};
+    for (int f = 0; f < c->nf; ++f) {
+        a.phi_in[f] = (const T *)c->phi[f][c->cur_phi[f]];
+        a.pi_in[f] = (const T *)c->pi[f][c->cur_pi[f]];
+        a.phi_out[f] = (T *)c->phi[f][c->cur_phi[f] ^ 1];
+        a.pi_out[f] = (T *)c->pi[f][c->cur_pi[f] ^ 1];
+    }
+    a.N = c->N;
+    a.zc = c->pair_zc;
+    a.runs = c->pair_runs;
+    a.seg = c->pair_seg;
+    a.inv_dx2 = 1.0 / (c->p.dx * c->p.dx);
+    a.lam = c->p.lambda;
+    a.q = c->p.potential == LAT_PHI4_CHI2 ? c->p.q : 0.0;
+    a.coef = c->coef + first;
+    const int nb = c->pair_runs * ((c->N + c->pair_zc - 1) / c->pair_zc);
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    if (c->profiling) {
+        lat_status s = timing_begin(c, &ev0, &ev1);
+        if (s != LAT_OK) return s;
+    }
+    const hipError_t e = c->nf == 1 ? launch_pair<T, 1>(c->pair_xs, a, nb, st) : launch_pair<T, 2>(c->pair_xs, a, nb, st);
+    if (e != hipSuccess) return fail(c, LAT_EHIP, std::string("pair launch: ") + hipGetErrorString(e));
+    if (c->profiling) {
+        lat_status s = timing_end(c, ev0, ev1, kKickDrift);
+        if (s != LAT_OK) return s;
+    }
+    c->launches[kKickDrift] += 1;
+    for (int f = 0; f < c->nf; ++f) {
+        c->cur_phi[f] ^= 1;
+        c->cur_pi[f] ^= 1;
+    }
+    return LAT_OK;
+}
+
+// How many launches take passes two at a time, of K passes in all, such that the call ends
+// in the arrays it began in: an even number, or an odd one before one last single pass,
+// which then brings the momenta across too.  (One pair more where two passes are left
+// would pay with a copy back.)
+int64_t pair_launches(const lat_ctx *c, int64_t K)
+{
+    if (c->pair_xs <= 0 || c->pass_io) return 0;
+    return K % 4 == 3 ? (K - 1) / 2 : K / 4 * 2;
+}
+
+// those launches, for passes 0, 1, ...
+lat_status run_pairs(lat_ctx *c, int64_t launches, hipStream_t st)
+{
+    for (int64_t j = 0; j < launches; ++j) {
+        const lat_status r = c->f32 ? run_pair_t<float>(c, 2 * j, st) : run_pair_t<double>(c, 2 * j, st);
+        if (r != LAT_OK) return r;
+    }
+    return LAT_OK;
+}
+
 lat_status step_lf(lat_ctx *c, int64_t ns, int dir)
 {
     if (c->p.expansion == LAT_EXP_SELF) return step_lf_self(c, ns, dir);
@@ -1308,7 +1418,8 @@ lat_status step_lf(lat_ctx *c, int64_t ns, int dir)
         stag = dir;
     }
     const int64_t S = std::max(c->slab_steps, 1), nl = (ns + S - 1) / S;
-    if ((s = place_coef(c, (size_t)ns, nl, c->slab_steps > 0 || c->site_nblocks > 0)) != LAT_OK) return s;
+    const int64_t m = c->slab_steps > 0 ? 0 : pair_launches(c, ns);
+    if ((s = place_coef(c, (size_t)ns, nl, c->slab_steps > 0 || (c->site_nblocks > 0 && m == 0))) != LAT_OK) return s;
     if (c->slab_steps > 0) {
         s = launch_passes(c, dir * ns, nl, [&](hipStream_t st) {
             for (int64_t j = 0; j < nl; ++j) {
@@ -1320,12 +1431,12 @@ lat_status step_lf(lat_ctx *c, int64_t ns, int dir)
             return LAT_OK;
         });
     } else {
-        s = launch_passes(c, dir * ns, ns, [&](hipStream_t st) {
-            for (int64_t k = 0; k < ns; ++k) {
-                lat_status r = run_pass(c, kKickDrift, (int)k, kLastStore, st);
-                if (r != LAT_OK) return r;
-            }
-            return LAT_OK;
+        s = launch_passes(c, dir * ns, ns - m, [&](hipStream_t st) {
+            lat_status r = run_pairs(c, m, st);
+            c->pi_across = m % 2 != 0;
+            for (int64_t k = 2 * m; r == LAT_OK && k < ns; ++k) r = run_pass(c, kKickDrift, (int)k, kLastStore, st);
+            c->pi_across = false;
+            return r;
         });
     }
     if (s != LAT_OK) return s;
@@ -1424,22 +1535,29 @@ lat_status step_vv(lat_ctx *c, int64_t ns, int dir)
             P.dend = p < M ? hn * std::pow(scale_at(c, ts(p) + 0.5 * hn), al - 3.0) : 0.0;
         }
     }
-    if ((s = place_coef(c, (size_t)M + 2, M + 1, !self && c->site_nblocks > 0)) != LAT_OK) return s;
+    // (the closing kick is a pass whose drift is zero)
+    const int64_t m = self ? 0 : pair_launches(c, M + 1);
+    if ((s = place_coef(c, (size_t)M + 2, M + 1, !self && c->site_nblocks > 0 && m == 0)) != LAT_OK) return s;
     const int mode = self ? kLastSelf : kLastStore;
-    s = launch_passes(c, dir * ns, M + 1, [&](hipStream_t st) {
-        if (self) {
-            hipLaunchKernelGGL(self_prologue, dim3(1), dim3(64), 0, st, c->coef, c->sc, al);
-            HIPCHK(c, hipGetLastError());
+    s = launch_passes(c, dir * ns, M + 1 - m, [&](hipStream_t st) {
+        if (!self) {
+            lat_status r = run_pairs(c, m, st);
+            c->pi_across = m % 2 != 0;
+            for (int64_t p = 2 * m; r == LAT_OK && p <= M; ++p)
+                r = run_pass(c, p < M ? kKickDrift : ((M - m) % 2 != 0 ? kKickCopy : kKickOnly), (int)p, mode, st);
+            c->pi_across = false;
+            return r;
         }
+        hipLaunchKernelGGL(self_prologue, dim3(1), dim3(64), 0, st, c->coef, c->sc, al);
+        HIPCHK(c, hipGetLastError());
         for (int64_t p = 0; p <= M; ++p) {
             const bool odd = M % 2 != 0 && !c->pass_io;
-            const int v = self ? (p > 0 ? kDriftKickRed : (odd ? kKickCopyRed : kKickOnlyRed))
-                               : (p < M ? kKickDrift : (odd ? kKickCopy : kKickOnly));
-            const PassLink lk = self ? pass_link(c, p, kLastSelf, true) : PassLink{};
-            lat_status r = run_pass(c, v, (int)p, mode, st, self ? &lk : nullptr);
+            const int v = p > 0 ? kDriftKickRed : (odd ? kKickCopyRed : kKickOnlyRed);
+            const PassLink lk = pass_link(c, p, kLastSelf, true);
+            const lat_status r = run_pass(c, v, (int)p, mode, st, &lk);
             if (r != LAT_OK) return r;
         }
-        return self ? finish_chain(c, M, kLastSelf, st) : LAT_OK;
+        return finish_chain(c, M, kLastSelf, st);
     });
     if (s != LAT_OK) return s;
     c->t = t_start + (double)ns * h;
@@ -1690,6 +1808,7 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
     geometry_from_env(c);
     slab_config(c);
     energy_geometry(c);
+    pair_geometry(c);
     const size_t bytes = c->vol * c->esize;
 
     auto bail = [&](lat_status st, const std::string &m) {

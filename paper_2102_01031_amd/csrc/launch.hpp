@@ -48,6 +48,21 @@ constexpr int kSiteThreads = 256;
 template <typename T, int NF>
 hipError_t launch_site(int variant, const ScalarArgs<T> &a, int nb, hipStream_t s);
 
+// Two kick-and-drift passes in one launch (stage_pair.hpp): runs of seg sites, zc planes
+// per block, the coefficients of both passes.  xs: sites per thread of the run widened
+// by 2 N; 4 <= N <= 512, and the runs' planes fit kPairLds bytes of LDS.
+template <typename T>
+struct PairArgs {
+    const T *phi_in[2], *pi_in[2];
+    T *phi_out[2], *pi_out[2];
+    int N, zc, runs, seg;
+    double inv_dx2, lam, q;
+    const PassCoef *coef;
+};
+constexpr int kPairLds = 156 * 1024, kPairThreads = 512;
+template <typename T, int NF>
+hipError_t launch_pair(int xs, const PairArgs<T> &a, int nb, hipStream_t s);
+
 // the lf_slab instance for S steps per launch and ZS planes per block, and its
 // dynamic LDS for yb rows per block; false if that shape is not compiled
 template <typename T, int NF>
