@@ -1087,10 +1087,12 @@ lat_status upload_coef(lat_ctx *c, size_t n)
 lat_status place_coef(lat_ctx *c, size_t n, int64_t launches, bool kernel_takes)
 {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (kernel_takes && launches < kGraphMinPasses && !c->pass_io && c->p.expansion != LAT_EXP_SELF &&
-        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-        c->by_value = true;
-        return LAT_OK;
+    if (kernel_takes && launches < kGraphMinPasses && !c->pass_io && c->p.expansion != LAT_EXP_SELF) {
+        if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+            c->by_value = true;
+            return LAT_OK;
+        }
+        (void)hipGetLastError();   // a refused query must not be taken for a launch's error
     }
     return upload_coef(c, n);
 }
@@ -2540,7 +2542,7 @@ void lattice_destroy(lat_ctx *c) { free_ctx(c); }
 }  // extern "C"
 
 // ===========================================================================
-// U(1) sector (a = 1, leapfrog)
+// U(1) sector
 // ===========================================================================
 namespace {
 

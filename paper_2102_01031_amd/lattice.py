@@ -287,7 +287,10 @@ class Lattice:
             # the trajectory, in torch's memory of the lattice's stream: its allocator
             # keeps it between gradients; the checkpoints do without it
             try:
-                with torch.cuda.stream(self.stream):
+                s = self.stream
+                if not isinstance(s, torch.cuda.Stream):
+                    s = torch.cuda.ExternalStream(s.cuda_stream)
+                with torch.cuda.stream(s):
                     work = torch.empty(need, dtype=torch.uint8, device="cuda")
             except torch.OutOfMemoryError:
                 need = 0
