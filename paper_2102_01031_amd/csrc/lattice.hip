@@ -117,6 +117,11 @@ struct lat_ctx {
     unsigned *ticket = nullptr;
     ScaleRecord *sc = nullptr;
     ScaleRecord *sc_host = nullptr;
+    // gauge models' self-consistent calls: the record the passes read, and the finish of
+    // the last summing pass, left to the drift that follows it (nb > 0)
+    ScaleRecord *grec = nullptr;
+    GaugeFin gfin{};
+    bool gfin_defer = false;
     PassCoef *coef = nullptr;
     size_t coef_cap = 0;
     // pinned staging for the table: a ring of slots, so the host fills the next
@@ -1868,6 +1873,7 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
     if (hipMalloc(&c->ticket, 64) != hipSuccess) return bail(LAT_ENOMEM, "scratch allocation failed");
     // the record, then two records for the deferred updates inside a call
     if (hipMalloc(&c->sc, 3 * sizeof(ScaleRecord)) != hipSuccess) return bail(LAT_ENOMEM, "scratch allocation failed");
+    c->grec = c->sc;
     if (hipHostMalloc((void **)&c->sc_host, sizeof(ScaleRecord), hipHostMallocDefault) != hipSuccess)
         return bail(LAT_ENOMEM, "pinned allocation failed");
     for (auto &e : c->ring_ev)
@@ -2606,7 +2612,7 @@ U1Args u1_args_dev(lat_ctx *c)
     U1Args a = u1_args(c, 0.0, 0.0, false);
     for (int i = 0; i < 2; ++i) a.phi_out[i] = (double *)c->phi[i][0];
     for (int i = 0; i < 3; ++i) a.A_out[i] = (double *)c->A[i][0];
-    a.dw = c->sc->w;
+    a.dw = c->grec->w;
     return a;
 }
 
@@ -2687,11 +2693,38 @@ hipError_t launch_u1_span(const lat_ctx *c, const U1Args &a, int nb)
 lat_status gauge_finish_launch(lat_ctx *c, int nb, const GaugeUpdate &u, bool host)
 {
     const U1SelfConst k{c->p.alpha, c->p.kappa2, 1.0 / (double)c->vol};
+    if (c->gfin_defer) {
+        c->gfin = GaugeFin{c->partials, nb, c->grec, c->grec == c->sc + 1 ? c->sc + 2 : c->sc + 1, u, k};
+        return LAT_OK;
+    }
     hipLaunchKernelGGL(gauge_finish, dim3(1), dim3(kGaugeFinishThreads), 0, c->stream, (const double *)c->partials, nb,
-                       c->sc, u, k, host ? c->sc_host : nullptr);
+                       (const ScaleRecord *)c->grec, c->sc, u, k, host ? c->sc_host : nullptr);
+    HIPCHK(c, hipGetLastError());
+    c->grec = c->sc;
+    return LAT_OK;
+}
+
+// the blocks of a drift, and its launch with or without a finish left to it
+template <typename PLAIN, typename FUSED>
+lat_status gauge_drift_launch(lat_ctx *c, PLAIN plain, FUSED fused)
+{
+    const dim3 grid((unsigned)((c->vol + kGaugeFinishThreads - 1) / kGaugeFinishThreads));
+    if (c->gfin.nb > 0) {
+        fused(grid);
+        c->grec = c->gfin.out;
+        c->gfin = GaugeFin{};
+    } else {
+        plain(grid);
+    }
     HIPCHK(c, hipGetLastError());
     return LAT_OK;
 }
+
+// The drift finishes the summing pass before it up to 56^3, where its blocks are few
+// enough to add all partials each (ten leapfrog steps and energies, three launches a
+// sub-step and two: U(1) 16^3 180 and 160 us, 48^3 234 and 221, 64^3 the same; SU(2) 32^3
+// 273 and 257, 56^3 506 and 487).
+bool gauge_defer_ok(const lat_ctx *c) { return c->vol <= 56 * 56 * 56; }
 
 lat_status u1_launch(lat_ctx *c, int mode, const U1Args &a, const GaugeUpdate &u = GaugeUpdate{}, bool host = false)
 {
@@ -2714,8 +2747,13 @@ lat_status u1_launch(lat_ctx *c, int mode, const U1Args &a, const GaugeUpdate &u
         else hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Kick>), dim3(nb), tb, 0, c->stream, a);
         break;
     case kU1Drift:
-        hipLaunchKernelGGL(u1_drift, dim3((unsigned)((c->vol + 255) / 256)), dim3(256), 0, c->stream, a, c->vol);
+    {
+        const lat_status st = gauge_drift_launch(
+            c, [&](dim3 g) { hipLaunchKernelGGL(u1_drift<false>, g, dim3(kGaugeFinishThreads), 0, c->stream, a, c->vol, c->gfin); },
+            [&](dim3 g) { hipLaunchKernelGGL(u1_drift<true>, g, dim3(kGaugeFinishThreads), 0, c->stream, a, c->vol, c->gfin); });
+        if (st != LAT_OK) return st;
         break;
+    }
     default: {   // the summing passes
         U1Args e = a;
         if (span) {
@@ -2766,17 +2804,21 @@ lat_status u1_flip(lat_ctx *c)
 // meet at a kick point use the same fields and the same a: one force evaluation, the
 // sums taken between them; leapfrog: one full kick, the momentum sums taken before
 // and after it), gauge_finish (b, a and the next weights from the sums), and the
-// drift, in place.
-lat_status gauge_kick_sums(lat_ctx *c, const GaugeUpdate &u);   // with the record's weights
+// drift, in place.  (defer: the drift that follows takes the finish)
+lat_status gauge_kick_sums(lat_ctx *c, const GaugeUpdate &u, bool defer = false);   // with the record's weights
 lat_status gauge_drift(lat_ctx *c);
 
 lat_status gauge_step_self_lf(lat_ctx *c, int64_t ns, int dir)
 {
     const double h = dir * c->p.dt;
     int stag = c->lf_stag;
+    c->grec = c->sc;
+    c->gfin = GaugeFin{};
     U1K(u1_self_kick_w, c->sc, stag == 0 ? 0.5 * h : h, 0.0, c->p.alpha);
     for (int64_t k = 0; k < ns; ++k) {
-        lat_status s = gauge_kick_sums(c, GaugeUpdate{1, stag == 0 ? 0.0 : 0.5 * h, 0.5 * h, 0.0, h, h, 0.0});
+        // (the last one's record is the context's)
+        lat_status s = gauge_kick_sums(c, GaugeUpdate{1, stag == 0 ? 0.0 : 0.5 * h, 0.5 * h, 0.0, h, h, 0.0},
+                                       k + 1 < ns && gauge_defer_ok(c));
         if (s != LAT_OK) return s;
         if ((s = gauge_drift(c)) != LAT_OK) return s;
         stag = dir;
@@ -2792,9 +2834,12 @@ lat_status gauge_step_self_vv(lat_ctx *c, int64_t ns, int dir)
     const std::vector<double> w = vv_weights(c->p.integrator);
     const int64_t J = (int64_t)w.size(), M = J * ns;
     auto half = [&](int64_t p) { return p < 0 || p >= M ? 0.0 : 0.5 * (w[(size_t)(p % J)] * h); };
+    c->grec = c->sc;
+    c->gfin = GaugeFin{};
     U1K(u1_self_kick_w, c->sc, 0.0, half(0), c->p.alpha);
     for (int64_t p = 0; p <= M; ++p) {
-        lat_status s = gauge_kick_sums(c, GaugeUpdate{1, 0.0, half(p - 1), half(p), 2.0 * half(p), half(p), half(p + 1)});
+        lat_status s = gauge_kick_sums(c, GaugeUpdate{1, 0.0, half(p - 1), half(p), 2.0 * half(p), half(p), half(p + 1)},
+                                       p < M && gauge_defer_ok(c));
         if (s != LAT_OK) return s;
         if (p < M && (s = gauge_drift(c)) != LAT_OK) return s;
     }
@@ -3036,7 +3081,7 @@ SU2Args su2_args_dev(lat_ctx *c)
     SU2Args a = su2_args(c, 0.0, 0.0, false);
     for (int k = 0; k < 4; ++k) a.phi_out[k] = (double *)c->dbl[k][0];   // the drift in place
     for (int k = 0; k < 12; ++k) a.U_out[k] = (double *)c->lnk[k][0];
-    a.dw = c->sc->w;
+    a.dw = c->grec->w;
     return a;
 }
 
@@ -3068,9 +3113,14 @@ lat_status su2_launch(lat_ctx *c, int mode, const SU2Args &args, const GaugeUpda
     const bool nt = c->su2_nt != 0;
     switch (mode) {
     case kSU2Drift:
-        hipLaunchKernelGGL(su2_drift, dim3((unsigned)((c->vol + 255) / 256)), dim3(256), 0, c->stream, a,
-                           (unsigned)c->vol);
+    {
+        const unsigned vol = (unsigned)c->vol;
+        const lat_status st = gauge_drift_launch(
+            c, [&](dim3 g) { hipLaunchKernelGGL(su2_drift<false>, g, dim3(kGaugeFinishThreads), 0, c->stream, a, vol, c->gfin); },
+            [&](dim3 g) { hipLaunchKernelGGL(su2_drift<true>, g, dim3(kGaugeFinishThreads), 0, c->stream, a, vol, c->gfin); });
+        if (st != LAT_OK) return st;
         break;
+    }
     case kSU2Step:
         if (nt) hipLaunchKernelGGL((su2_stage<kSU2Step, true>), grid, blk, 0, c->stream, a);
         else hipLaunchKernelGGL((su2_stage<kSU2Step, false>), grid, blk, 0, c->stream, a);
@@ -3150,9 +3200,13 @@ static bool su2_alternate()
     return e ? std::atoi(e) != 0 : true;
 }
 
-lat_status gauge_kick_sums(lat_ctx *c, const GaugeUpdate &u)
+lat_status gauge_kick_sums(lat_ctx *c, const GaugeUpdate &u, bool defer)
 {
-    return c->su2 ? su2_launch(c, kSU2KickSums, su2_args_dev(c), u) : u1_launch(c, kU1KickSums, u1_args_dev(c), u);
+    c->gfin_defer = defer;
+    const lat_status s = c->su2 ? su2_launch(c, kSU2KickSums, su2_args_dev(c), u)
+                                : u1_launch(c, kU1KickSums, u1_args_dev(c), u);
+    c->gfin_defer = false;
+    return s;
 }
 
 lat_status gauge_drift(lat_ctx *c)

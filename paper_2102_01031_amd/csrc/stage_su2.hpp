@@ -428,11 +428,18 @@ __device__ __forceinline__ void su2_site(const SU2Args &g, const SU2W &wt, const
 // arrays, one site per thread and in place (a site's drift reads nothing else): the
 // doublet phi + hd pi and the links exp(-i hdU g dx E.T) U, the step pass's drift
 // formed by the same expressions.  Reads 29 arrays and writes 16, with no forces.
-__global__ void __launch_bounds__(256) su2_drift(const SU2Args g, unsigned vol)
+template <bool FIN>
+__global__ void __launch_bounds__(kGaugeFinishThreads) su2_drift(const SU2Args g, unsigned vol, const GaugeFin F)
 {
-    const unsigned n = blockIdx.x * 256u + threadIdx.x;
+    const unsigned n = blockIdx.x * (unsigned)kGaugeFinishThreads + threadIdx.x;
+    double hd, hdU;
+    if constexpr (FIN) {
+        gauge_fin_prologue(F, hd, hdU);
+    } else {
+        hd = g.dw[4];
+        hdU = g.dw[5];
+    }
     if (n >= vol) return;
-    const double hd = g.dw[4], hdU = g.dw[5];
 #pragma unroll
     for (int k = 0; k < 4; ++k) g.phi_out[k][n] = g.phi_in[k][n] + hd * g.pi[k][n];
     const double hgdx = hdU * g.g * g.dx;

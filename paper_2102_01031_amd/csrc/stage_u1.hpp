@@ -250,20 +250,6 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
     }
 }
 
-// Drift only, with the record's weights hd = dw[4], hdA = dw[5]: phi' = phi + hd pi,
-// A_i' = A_i + hdA piA_i, one site per thread.  A site's drift reads nothing else, so
-// it runs in place (15 arrays of traffic, no forces, no copy back after the call).
-__global__ void __launch_bounds__(256) u1_drift(const U1Args g, size_t vol)
-{
-    const size_t n = (size_t)blockIdx.x * 256u + threadIdx.x;
-    if (n >= vol) return;
-    const double hd = g.dw[4], hdA = g.dw[5];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) g.phi_out[c][n] = g.phi_in[c][n] + hd * g.pi[c][n];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) g.A_out[i][n] = g.A_in[i][n] + hdA * g.piA[i][n];
-}
-
 // ---------------------------------------------------------------------------
 // Self-consistent expansion of the U(1) model (sec. 5.5.2, the b' equation with
 // the gauge energies): one-thread kernels between the lattice passes.  An
@@ -309,13 +295,33 @@ struct GaugeUpdate {
     double cB, cA, cA2, h, c1, c2;
 };
 
+// That update by the lanes of one wave, from the sums tot (valid in every lane): a' and
+// b, and in lanes 0 .. 6 the weights of the passes to come.
+struct GaugeNew {
+    double a, b, w;
+};
+__device__ inline GaugeNew gauge_update(const double *tot, double a, double b, const GaugeUpdate &u,
+                                        const U1SelfConst &k, int lane)
+{
+    const double after[5] = {tot[0], tot[1], tot[2], tot[3], tot[4]};
+    const double before[5] = {tot[8], tot[1], tot[2], tot[9], tot[4]};
+    if (u.cB != 0.0) b += u.cB * u1_kernel_b(a, before, k);
+    if (u.cA != 0.0) b += u.cA * u1_kernel_b(a, after, k);
+    if (u.cA2 != 0.0) b += u.cA2 * u1_kernel_b(a, after, k);
+    const double a1 = a + u.h * b, am = 0.5 * (a + a1);
+    const double ex = lane == 1 ? 1.0 + k.alpha : (lane == 2 ? 3.0 + k.alpha : (lane == 4 ? k.alpha - 3.0 : k.alpha - 1.0));
+    const double p = pow(lane < 4 ? a1 : am, ex);
+    return GaugeNew{a1, b, lane == 0 ? u.c1 : (lane == 6 ? u.c2 : (lane < 4 ? p : u.h * p))};
+}
+
 // The block partials of a summing pass of the gauge models (kU1Sums sums, then
 // kU1Maxes maxima per block), combined by one block in a fixed order into the record;
 // then the update above, its five powers side by side in the lanes of one wave, and,
 // with `host`, a copy of the record in pinned host memory.  One launch of one block
 // behind each pass instead of four one-thread kernels (5 us each at any size).
 constexpr int kGaugeFinishThreads = 256;
-__global__ void __launch_bounds__(kGaugeFinishThreads) gauge_finish(const double *partials, int nb, ScaleRecord *S,
+__global__ void __launch_bounds__(kGaugeFinishThreads) gauge_finish(const double *partials, int nb,
+                                                                    const ScaleRecord *Sin, ScaleRecord *S,
                                                                     const GaugeUpdate u, const U1SelfConst k,
                                                                     ScaleRecord *host)
 {
@@ -339,20 +345,11 @@ __global__ void __launch_bounds__(kGaugeFinishThreads) gauge_finish(const double
     else if (tid < NQ) S->maxes[tid - kU1Sums] = tot[tid];
     if (tid >= 64) return;
     if (u.on) {
-        const double a = S->a;
-        double b = S->b;
-        const double after[5] = {tot[0], tot[1], tot[2], tot[3], tot[4]};
-        const double before[5] = {tot[8], tot[1], tot[2], tot[9], tot[4]};
-        if (u.cB != 0.0) b += u.cB * u1_kernel_b(a, before, k);
-        if (u.cA != 0.0) b += u.cA * u1_kernel_b(a, after, k);
-        if (u.cA2 != 0.0) b += u.cA2 * u1_kernel_b(a, after, k);
-        const double a1 = a + u.h * b, am = 0.5 * (a + a1);
-        const double ex = tid == 1 ? 1.0 + k.alpha : (tid == 2 ? 3.0 + k.alpha : (tid == 4 ? k.alpha - 3.0 : k.alpha - 1.0));
-        const double p = pow(tid < 4 ? a1 : am, ex);
-        if (tid < 7) S->w[tid] = tid == 0 ? u.c1 : (tid == 6 ? u.c2 : (tid < 4 ? p : u.h * p));
+        const GaugeNew n = gauge_update(tot, Sin->a, Sin->b, u, k, tid);
+        if (tid < 7) S->w[tid] = n.w;
         if (tid == 0) {
-            S->a = a1;
-            S->b = b;
+            S->a = n.a;
+            S->b = n.b;
         }
     }
     if (host) {
@@ -360,6 +357,84 @@ __global__ void __launch_bounds__(kGaugeFinishThreads) gauge_finish(const double
         static_assert(sizeof(ScaleRecord) == 32 * sizeof(double), "record size");
         if (tid < 32) ((double *)host)[tid] = load_agent((const double *)S + tid);
     }
+}
+
+// A drift that begins with the finish of the summing pass before it, on small lattices:
+// every block adds the nb partials itself (in gauge_finish's order), its first wave
+// applies the update to the record `in`, and block 0 writes the new record to `out`,
+// so a sub-step takes two launches instead of three (U(1) 16^3, ten leapfrog steps with
+// their energies 180 -> 160 us; SU(2) 32^3 273 -> 257).
+struct GaugeFin {
+    const double *partials;
+    int nb;
+    const ScaleRecord *in;
+    ScaleRecord *out;
+    GaugeUpdate u;
+    U1SelfConst k;
+};
+
+// the drift weights h abar^{alpha-3} and h abar^{alpha-1} (blocks of kGaugeFinishThreads)
+__device__ inline void gauge_fin_prologue(const GaugeFin &F, double &hd, double &hdA)
+{
+    constexpr int NQ = kU1Sums, NT = kGaugeFinishThreads;
+    __shared__ double lds_red[(NT / 64) * NQ];
+    __shared__ double w[7];
+    const int tid = threadIdx.x;
+    double part[NQ], tot[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) part[q] = 0.0;
+    for (int i = tid; i < F.nb; i += NT) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) part[q] += F.partials[(size_t)i * (kU1Sums + kU1Maxes) + q];
+    }
+    block_sums<NT, NQ>(part, lds_red, tot);
+    if (tid < 64) {
+        const GaugeNew n = gauge_update(tot, F.in->a, F.in->b, F.u, F.k, tid);
+        if (tid < 7) w[tid] = n.w;
+        if (blockIdx.x == 0) {
+            if (tid < 7) F.out->w[tid] = n.w;
+            if (tid == 0) {
+                F.out->a = n.a;
+                F.out->b = n.b;
+            }
+        }
+    }
+    __syncthreads();
+    hd = w[4];
+    hdA = w[5];
+}
+
+// Drift only, with the record's weights hd = dw[4], hdA = dw[5]: phi' = phi + hd pi,
+// A_i' = A_i + hdA piA_i, one site per thread.  A site's drift reads nothing else, so
+// it runs in place (15 arrays of traffic, no forces, no copy back after the call).
+template <bool FIN>
+__global__ void __launch_bounds__(kGaugeFinishThreads) u1_drift(const U1Args g, size_t vol, const GaugeFin F)
+{
+    const size_t n = (size_t)blockIdx.x * kGaugeFinishThreads + threadIdx.x;
+    const bool on = n < vol;
+    double f[2], p[2], A[3], q[3];   // loaded ahead of the prologue's sums
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        f[c] = on ? g.phi_in[c][n] : 0.0;
+        p[c] = on ? g.pi[c][n] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        A[i] = on ? g.A_in[i][n] : 0.0;
+        q[i] = on ? g.piA[i][n] : 0.0;
+    }
+    double hd, hdA;
+    if constexpr (FIN) {
+        gauge_fin_prologue(F, hd, hdA);
+    } else {
+        hd = g.dw[4];
+        hdA = g.dw[5];
+    }
+    if (!on) return;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) g.phi_out[c][n] = f[c] + hd * p[c];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) g.A_out[i][n] = A[i] + hdA * q[i];
 }
 
 // The passes of u1_stage for lattices whose block rows fit LDS (N up to 440), with
