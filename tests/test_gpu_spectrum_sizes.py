@@ -1,6 +1,6 @@
 """Spectra and occupation numbers of random fields over the transform sizes:
 every radix (8, 4, 2, 3, 5, 7) alone and mixed, odd sizes (an odd number of rows
-to pair), the smallest, sizes left to the library transform (primes above 7), and
+to pair), the smallest, primes above 7, a size left to the library transform, and
 a number of bins below the mode range.  Reference: numpy's transform of the same
 values in float64.  A length-n transform's error is a few ulp times log2 n, so
 shell sums are held to 1e-13 of the largest shell."""
@@ -59,3 +59,22 @@ def test_sizes(N, prec):
             if nb > 1:
                 assert np.max(np.abs(o["n"][1:] - n)) <= 1e-12 * n.max()
     lat.close()
+
+
+def test_library_size():
+    """257 times its largest prime, itself, lies beyond the line transforms' rule."""
+    import torch
+
+    from paper_2102_01031_amd.lattice import Lattice
+    N, nb = 257, 40
+    rng = np.random.default_rng(N)
+    phi = rng.standard_normal((N, N, N))
+    dev = [torch.tensor(a.reshape(-1)).cuda() for a in (phi, np.zeros_like(phi))]
+    say(f"N={N} library transform")
+    lat = Lattice(dev[:1], dev[1:], N=N, dx=0.3, dt=0.005, potential="phi4")
+    s = lat.spectrum(0, "phi", nbins=nb)
+    lat.close()
+    shell, w = _shells(N), (np.abs(np.fft.fftn(phi)) ** 2).reshape(-1)
+    assert np.array_equal(s["count"], np.bincount(shell, minlength=nb)[:nb])
+    ref = np.bincount(shell, weights=w, minlength=nb)[:nb]
+    assert np.max(np.abs(s["sum"] - ref)) <= 1e-13 * ref.max()
