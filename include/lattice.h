@@ -39,6 +39,7 @@
 #ifndef LATTICE_H
 #define LATTICE_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
