@@ -3494,9 +3494,15 @@ lat_status adj_site_pass(lat_ctx *c, const double *const (&phi)[2], double cc, d
 
 }  // namespace
 
+// the contexts lattice_grad takes
+static bool grad_takes(const lat_ctx *c)
+{
+    return !c->batch && c->p.potential == LAT_PHI4_CHI2 && c->p.integrator == LAT_VV2 && !c->f32;
+}
+
 extern "C" size_t lattice_grad_work(const lat_ctx *c, const lat_grad_spec *spec)
 {
-    if (!c || !spec || c->batch || c->u1 || c->su2 || c->nf != 2 || c->f32 || spec->checkpoint_stride > 0) return 0;
+    if (!c || !spec || !grad_takes(c) || spec->checkpoint_stride > 0) return 0;
     return trajectory_doubles(c, spec->nsteps) * sizeof(double);
 }
 
@@ -3513,7 +3519,7 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
     const bool spec_obs = spec->observable == LAT_OBS_SPECTRUM_BIN;
     if (spec->observable != LAT_OBS_ENERGY_FRACTION && !spec_obs)
         return fail(c, LAT_EINVAL, "unknown observable");
-    if (c->batch || c->u1 || c->p.potential != LAT_PHI4_CHI2 || c->p.integrator != LAT_VV2 || c->f32)
+    if (!grad_takes(c))
         return fail(c, LAT_EUNSUPPORTED, "lattice_grad needs two fields, VV2 and float64");
     const bool self = c->p.expansion == LAT_EXP_SELF;
     if (spec->reserved != 0) return fail(c, LAT_EINVAL, "reserved field of lat_grad_spec must be 0");
