@@ -3669,6 +3669,7 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
     auto at = [&](int64_t p, int w, int f) {
         return p == 0 ? start[w][f] : hist + ((size_t)(p - 1) * slot_arrays + (size_t)(2 * w + f)) * c->vol;
     };
+    int64_t base = 0;   // point at which the running step_vv call starts
     if (keep) {
         for (auto &l : c->cur_lam) l[0] = l[1] = 0;
         // momenta between the passes in the second buffers of lphi and lpi, which the
@@ -3679,12 +3680,12 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
                 if (variant == kEnergy) {
                     x.phi_in[f] = at(T, 0, f);
                     x.pi_in[f] = self ? (void *)at(T, 1, f) : mom(0, f);
-                } else if (self) {   // point `pass`: drift from the point before, both kicks
-                    x.phi_in[f] = at(pass > 0 ? pass - 1 : 0, 0, f);
-                    x.pi_in[f] = pass > 0 ? mom(pass - 1, f) : (void *)start[1][f];
-                    x.phi_out[f] = pass > 0 ? at(pass, 0, f) : nullptr;
+                } else if (self) {   // point base + `pass`: drift from the point before, both kicks
+                    x.phi_in[f] = at(base + (pass > 0 ? pass - 1 : 0), 0, f);
+                    x.pi_in[f] = pass > 0 ? mom(pass - 1, f) : (void *)at(base, 1, f);
+                    x.phi_out[f] = pass > 0 ? at(base + pass, 0, f) : nullptr;
                     x.pi_out[f] = mom(pass, f);
-                    x.pi_mid[f] = pass > 0 ? at(pass, 1, f) : nullptr;
+                    x.pi_mid[f] = pass > 0 ? at(base + pass, 1, f) : nullptr;
                 } else {             // point `pass`: both kicks, drift to the next point
                     x.phi_in[f] = at(pass, 0, f);
                     x.pi_in[f] = pass > 0 ? mom(0, f) : (void *)start[1][f];
@@ -3697,8 +3698,9 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
         GCHK(checkpoint_io(c, 0, true));
     }
     // self-consistent expansion: the library's own VV2 steps, one call per
-    // segment between checkpoints, each pass storing (a, a') of its point on
-    // the device; the scale factors come back to the host once, at the end
+    // segment between checkpoints (kept trajectory: kChunkPasses steps, which bound
+    // the coefficient tables as lattice_step's calls do), each pass storing (a, a')
+    // of its point on the device; the scale factors come back to the host once, at the end
     // device layout of self_traj: (a, a') per step, then the initial scale record
     std::vector<double> traj_a;
     const int64_t step_save = c->step;
@@ -3706,9 +3708,10 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
     ScaleRecord *rec_dev = self ? (ScaleRecord *)(c->self_traj + 2 * ((size_t)T + 1)) : nullptr;
     if (self) {
         HIPCHK(c, hipMemcpyAsync(rec_dev, c->sc, sizeof(ScaleRecord), hipMemcpyDeviceToDevice, c->stream));
-        const int64_t span = keep ? T : k;
+        const int64_t span = keep ? kChunkPasses : k;
         for (int64_t s0 = 0; s0 < T; s0 += span) {
             const int64_t len = std::min<int64_t>(span, T - s0);
+            base = s0;
             c->traj_rec = traj_dev + 2 * (size_t)s0;
             const lat_status r = step_vv(c, len, 1);
             c->traj_rec = nullptr;
