@@ -67,10 +67,10 @@ lat_status su2_step_lf(lat_ctx *c, int64_t ns, int dir);
 lat_status gauge_step_vv(lat_ctx *c, int64_t ns, int dir);
 lat_status su2_sync(lat_ctx *c);
 lat_status su2_energy(lat_ctx *c, lat_energies *out);
-size_t su2_partial_capacity(int N);
+size_t su2_partial_capacity(const lat_ctx *c);
 int su2_zc(const lat_ctx *c, bool sums);
 void su2_geometry(lat_ctx *c);
-size_t u1_partial_capacity(int N);
+size_t u1_partial_capacity(const lat_ctx *c);
 void u1_geometry(lat_ctx *c);
 lat_status batch_step(lat_ctx *c, int64_t nsteps);
 
@@ -409,6 +409,15 @@ bool plane_geometry(lat_ctx *c, const char *spec)
 // (float32 72^3: 9.4 us in 512, 10.5 in 768; 110^3 18.1 and 16.9).
 // LATTICE_TILE="site[,kick[,red[,blocks]]]" overrides (kick, red: 0 or 1).
 constexpr int kSiteMaxSumBlocks = 768;
+
+// that kernel's blocks over vol sites in at most `most` of them, and their sites per thread
+int site_runs(size_t vol, int most, int *sites)
+{
+    const size_t nb = (vol + kSiteThreads - 1) / kSiteThreads;
+    *sites = (int)((nb + most - 1) / most);
+    return (int)((nb + *sites - 1) / *sites);
+}
+
 void site_geometry(lat_ctx *c, const char *spec)
 {
     const size_t size = c->f32 ? 4 : 8;
@@ -423,11 +432,9 @@ void site_geometry(lat_ctx *c, const char *spec)
     if (red < 0) red = !rows_ok(c->N) && c->N <= (c->f32 ? 127 : 72);
     if (kick) c->site_nblocks = (int)nb;
     if (red) {
-        cap = std::max(cap, 1);
         c->site_red = true;
         c->rows = c->plane = false;
-        c->zc = (int)((nb + cap - 1) / cap);
-        c->nblocks = (int)((nb + c->zc - 1) / c->zc);
+        c->nblocks = site_runs(c->vol, std::max(cap, 1), &c->zc);
         c->tiles_x = c->nblocks;
         c->tiles_y = c->chunks_z = 1;
     }
@@ -846,10 +853,7 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
             a.by_value = 1;
         }
         nb = red ? c->nblocks : c->site_nblocks;
-        if (en_site) {
-            a.zc = (c->site_nblocks + kSiteMaxSumBlocks - 1) / kSiteMaxSumBlocks;
-            nb = (c->site_nblocks + a.zc - 1) / a.zc;
-        }
+        if (en_site) nb = site_runs(c->vol, kSiteMaxSumBlocks, &a.zc);
         e = c->nf == 1 ? launch_site<T, 1>(variant, a, nb, stream) : launch_site<T, 2>(variant, a, nb, stream);
     } else if (c->rows)
         e = c->nf == 1 ? launch_rows<T, 1>(c->N, ty, pf, c->rows_vw, variant, a, nb, stream, lp)
@@ -1862,12 +1866,16 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
                 if (hipMalloc(&q, 4 * c->vol * sizeof(double4)) != hipSuccess) return bail(LAT_ENOMEM, "record allocation failed");
         su2_geometry(c);
     }
-    // (768: the one-site-per-thread kernel's, which a gradient's forward sweep may take)
-    c->partial_cap = (size_t)std::max(std::max(c->nblocks, kSiteMaxSumBlocks), c->en_nblocks) * kMaxQ + 64;
-    if (c->su2) c->partial_cap = su2_partial_capacity(c->N) + 64;
+    // the passes' blocks, or the one-site-per-thread kernel's where the energy pass or a
+    // gradient's forward sweep takes it
+    int sites;
+    const bool on_site = (double)bytes < 4294967296.0;
+    c->partial_cap = (size_t)std::max(std::max(c->nblocks, on_site ? site_runs(c->vol, kSiteMaxSumBlocks, &sites) : 0),
+                                      c->en_nblocks) * kMaxQ + 64;
+    if (c->su2) c->partial_cap = su2_partial_capacity(c) + 64;
     if (c->u1) {
         u1_geometry(c);
-        c->partial_cap = u1_partial_capacity(c->N) + 64;
+        c->partial_cap = u1_partial_capacity(c) + 64;
     }
     if (hipMalloc(&c->partials, c->partial_cap * sizeof(double)) != hipSuccess) return bail(LAT_ENOMEM, "scratch allocation failed");
     if (hipMalloc(&c->ticket, 64) != hipSuccess) return bail(LAT_ENOMEM, "scratch allocation failed");
@@ -2554,13 +2562,6 @@ namespace {
 
 constexpr int kU1TX = 64, kU1TY = 4;
 
-size_t u1_partial_capacity(int N)
-{
-    // one block per plane and four rows or fewer sites of the span kernel's shapes
-    const size_t tiles = (size_t)((N + kU1TX - 1) / kU1TX) * ((N + kU1TY - 1) / kU1TY) * (size_t)N;
-    return std::max(tiles, (size_t)N * N) * (kU1Sums + kU1Maxes);
-}
-
 U1Args u1_args(lat_ctx *c, double ck, double hd, bool write_fields)
 {
     U1Args a{};
@@ -2673,6 +2674,18 @@ int u1_span_blocks(const lat_ctx *c)
     return ((c->N + c->u1_ty - 1) / c->u1_ty) * ((c->N + c->u1_zc - 1) / c->u1_zc);
 }
 
+// blocks of u1_stage's energy pass
+int u1_energy_blocks(const lat_ctx *c)
+{
+    return ((c->N + kU1TX - 1) / kU1TX) * ((c->N + kU1TY - 1) / kU1TY) * ((c->N + c->u1_ezc - 1) / c->u1_ezc);
+}
+
+// partials of a summing pass
+size_t u1_partial_capacity(const lat_ctx *c)
+{
+    return (size_t)(c->u1_ty > 0 ? u1_span_blocks(c) : u1_energy_blocks(c)) * (kU1Sums + kU1Maxes);
+}
+
 template <int MODE>
 hipError_t launch_u1_span(const lat_ctx *c, const U1Args &a, int nb)
 {
@@ -2762,7 +2775,7 @@ lat_status u1_launch(lat_ctx *c, int mode, const U1Args &a, const GaugeUpdate &u
             // kick and sums: the energy pass forms the sums of the kicked state
             // without writing it, then a pass applies both kicks
             e.zc = c->u1_ezc;
-            nb = a.tiles_x * a.tiles_y * ((c->N + e.zc - 1) / e.zc);
+            nb = u1_energy_blocks(c);
             hipLaunchKernelGGL((u1_stage<kU1TX, kU1TY, kU1Energy>), dim3(nb), tb, 0, c->stream, e);
             if (mode == kU1KickSums) {
                 HIPCHK(c, hipGetLastError());
@@ -2952,18 +2965,14 @@ lat_status u1_energy(lat_ctx *c, lat_energies *out)
 // ===========================================================================
 namespace {
 
-size_t su2_partial_capacity(int N)
-{
-    // largest grids: one z plane per block, tiles of 128 sites or more with one
-    // partly filled tile per row and column, XCD bands rounded up
-    const size_t tiles = (size_t)N * N / 64 + 2 * (size_t)N + 16;
-    return tiles * (size_t)N * (kSU2Sums + kSU2Maxes);
-}
-
 int su2_tiles(const lat_ctx *c)
 {
     return ((c->N + c->su2_tx - 1) / c->su2_tx) * ((c->N + c->su2_ty - 1) / c->su2_ty);
 }
+
+// partials of a summing pass at one z plane per block, the most that its overrides allow
+// (such passes run plane-wide)
+size_t su2_partial_capacity(const lat_ctx *c) { return (size_t)su2_tiles(c) * c->N * (kSU2Sums + kSU2Maxes); }
 
 // SU(2) tiles, block order, z planes per block and cache policy.  A tile row is a
 // k-th of a lattice row, a tile as many rows as 256 threads hold; of k = 1 .. 8 the one
