@@ -243,6 +243,7 @@ namespace {
 
 lat_status fail(lat_ctx *c, lat_status s, const std::string &msg)
 {
+    if (s == LAT_ENOMEM) (void)hipGetLastError();   // must not be taken for a later launch's error
     if (c) c->err = msg;
     else g_init_error = msg;
     return s;
@@ -1045,9 +1046,10 @@ lat_status reserve_coef(lat_ctx *c, size_t n)
         // captured graphs hold the table's address: drop them with it
         drop_step_graphs(c);
         c->graph_n = 0;
+        const size_t cap = std::max(n, std::max(kCoefInitial, 2 * c->coef_cap));
         if (c->coef) HIPCHK(c, hipFree(c->coef));
         c->coef = nullptr;
-        const size_t cap = std::max(n, std::max(kCoefInitial, 2 * c->coef_cap));
+        c->coef_cap = 0;
         if (hipMalloc(&c->coef, cap * sizeof(PassCoef)) != hipSuccess)
             return fail(c, LAT_ENOMEM, "coefficient table allocation failed");
         c->coef_cap = cap;
@@ -1057,9 +1059,10 @@ lat_status reserve_coef(lat_ctx *c, size_t n)
             if (c->ring_pending[i]) HIPCHK(c, hipEventSynchronize(c->ring_ev[i]));
             c->ring_pending[i] = false;
         }
+        const size_t cap = std::max(n, std::max(kCoefInitial, 2 * c->ring_cap));
         if (c->ring_base) HIPCHK(c, hipHostFree(c->ring_base));
         c->ring_base = nullptr;
-        const size_t cap = std::max(n, std::max(kCoefInitial, 2 * c->ring_cap));
+        c->ring_cap = 0;
         if (hipHostMalloc((void **)&c->ring_base, lat_ctx::kRing * cap * sizeof(PassCoef), hipHostMallocDefault) !=
             hipSuccess)
             return fail(c, LAT_ENOMEM, "pinned coefficient staging allocation failed");
@@ -1823,7 +1826,7 @@ lat_status lattice_init(lat_ctx **out, const lat_params *p, const lat_fields *f,
     const size_t bytes = c->vol * c->esize;
 
     auto bail = [&](lat_status st, const std::string &m) {
-        g_init_error = m;
+        (void)fail(nullptr, st, m);   // (m may be the context's)
         free_ctx(c);
         return st;
     };
@@ -3632,6 +3635,12 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
             c->self_part_cap = pneed;
         }
     }
+    // (all of it before the first pass: a call that finds no memory leaves the state as it was)
+    if (spec_obs) {
+        if ((s = ensure_lines(c, 1)) != LAT_OK) return s;
+        if (c->spec_own == 0 && ((s = ensure_fft(c, false)) != LAT_OK || (s = ensure_fft(c, true)) != LAT_OK)) return s;
+    }
+    if ((s = reserve_coef(c, (size_t)(self ? std::min(T, keep ? kChunkPasses : k) : T) + 3)) != LAT_OK) return s;
     // with a kept trajectory the self-consistent passes run on the one-site-per-thread
     // kernel, which also stores the momenta at the kick points
     struct Guard {
@@ -3733,7 +3742,6 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
         traj_a.resize((size_t)T + 1);
         for (size_t i = 0; i <= (size_t)T; ++i) traj_a[i] = tr[2 * i];
     } else {
-        GCHK(reserve_coef(c, (size_t)T + 3));
         for (int64_t p = 0; p <= T; ++p) {
             PassCoef &P = c->coef_host[p];
             P.ka1 = kick_l(p);
@@ -3767,15 +3775,12 @@ extern "C" lat_status lattice_grad_in(lat_ctx *c, const lat_grad_spec *spec, lat
         cb = shell_weight(N, c->p.dx, spec->bin);
         hipLaunchKernelGGL(zero_doubles, dim3(1), dim3(64), 0, c->stream, &c->sc->sums[kMaxQ - 2], 2);
         HIPCHK(c, hipGetLastError());
-        GCHK(ensure_lines(c, 1));
         double *seed = (double *)c->lam[0][s][c->cur_lam[0][s]];
         if (c->spec_own > 0) {
             // (a library plan costs milliseconds, more than the whole run of a small lattice)
             HIPCHK(c, fft_shell_seed(c->spec_plan, phi_T[s], (int)spec->bin, 2.0 * cb,
                                      c->spec_g[0], c->adj_partials, &c->sc->sums[kMaxQ - 2], seed, c->stream));
         } else {
-            GCHK(ensure_fft(c, false));
-            GCHK(ensure_fft(c, true));
             HIPCHK(c, hipMemcpyAsync(c->fft_in, phi_T[s], bytes, hipMemcpyDeviceToDevice, c->stream));
             if (hipfftExecD2Z(c->fft_plan, c->fft_in, (hipfftDoubleComplex *)c->fft_out) != HIPFFT_SUCCESS) {
                 cleanup();
@@ -4425,8 +4430,8 @@ extern "C" lat_status lattice_init_batch(lat_ctx **out, const lat_params *p, int
     c->t = p->t0;
     c->lf_stag = p->lf_staggered;
     auto bail = [&](lat_status st, const std::string &m) {
+        (void)fail(nullptr, st, m);   // (m may be the context's)
         free_ctx(c);
-        g_init_error = m;
         return st;
     };
     for (int r = 0; r < n_real; ++r) {

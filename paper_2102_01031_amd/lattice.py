@@ -148,6 +148,18 @@ def _check(code, ctx=None):
         raise LatticeError(code, msg)
 
 
+def _call(fn, *args):
+    """A library call that may allocate device memory.  Where there is none left, what
+    torch's allocator holds unused (after a gradient up to 8 GiB, its trajectory) goes
+    back to the driver and the call is made once more."""
+    rc = fn(*args)
+    if rc == LAT_ENOMEM:
+        import torch
+        torch.cuda.empty_cache()
+        rc = fn(*args)
+    return rc
+
+
 def make_params(N, dx, dt, integrator="lf", expansion="none", potential="phi4", precision="f64", t0=0.0,
                 alpha=1.0, lam=1.0, q=0.0, v=1.0, e=0.5, kappa_g=1.0, kappa2=0.25, w_eos=1.0 / 3.0, H0=0.0,
                 t_ref=0.0, a0=1.0, b0=math.nan, lf_staggered=0, g=None) -> LatParams:
@@ -198,8 +210,8 @@ class Lattice:
             stream = torch.cuda.current_stream()
         self.stream = stream
         self._ctx = C.c_void_p()
-        rc = lib().lattice_init(C.byref(self._ctx), C.byref(self.params), C.byref(f),
-                                C.c_void_p(stream.cuda_stream))
+        rc = _call(lib().lattice_init, C.byref(self._ctx), C.byref(self.params), C.byref(f),
+                   C.c_void_p(stream.cuda_stream))
         _check(rc, None)
 
     def step(self, n: int):
@@ -232,9 +244,8 @@ class Lattice:
         s, d = np.zeros(nb), np.zeros(nb)
         c = np.zeros(nb, dtype=np.int64)
         dp = C.POINTER(C.c_double)
-        _check(lib().lattice_spectrum(self._ctx, int(field), {"phi": 0, "pi": 1}[array], nb,
-                                      s.ctypes.data_as(dp), d.ctypes.data_as(dp),
-                                      c.ctypes.data_as(C.POINTER(C.c_int64))), self._ctx)
+        _check(_call(lib().lattice_spectrum, self._ctx, int(field), {"phi": 0, "pi": 1}[array], nb,
+                     s.ctypes.data_as(dp), d.ctypes.data_as(dp), c.ctypes.data_as(C.POINTER(C.c_int64))), self._ctx)
         kir = 2 * math.pi / (N * self.params.dx)
         return dict(sum=s, delta=d, count=c, k=kir * np.arange(nb))
 
@@ -248,9 +259,8 @@ class Lattice:
         N = self.params.N
         nb = int(math.isqrt(3 * (N // 2) ** 2)) + 1 if nbins is None else int(nbins)
         n, c = np.zeros(nb), np.zeros(nb, dtype=np.int64)
-        _check(lib().lattice_occupation(self._ctx, int(field), nb, float(fstar2),
-                                        n.ctypes.data_as(C.POINTER(C.c_double)),
-                                        c.ctypes.data_as(C.POINTER(C.c_int64))), self._ctx)
+        _check(_call(lib().lattice_occupation, self._ctx, int(field), nb, float(fstar2),
+                     n.ctypes.data_as(C.POINTER(C.c_double)), c.ctypes.data_as(C.POINTER(C.c_int64))), self._ctx)
         kir = 2 * math.pi / (N * self.params.dx)
         return dict(n=n, count=c, k=kir * np.arange(nb))
 
@@ -260,7 +270,7 @@ class Lattice:
         returns the homogeneous charge <rho^a> per colour (one value for U(1))."""
         import numpy as np
         mean = np.zeros(3)
-        _check(lib().lattice_gauss_init(self._ctx, mean.ctypes.data_as(C.POINTER(C.c_double))), self._ctx)
+        _check(_call(lib().lattice_gauss_init, self._ctx, mean.ctypes.data_as(C.POINTER(C.c_double))), self._ctx)
         return mean if self.params.potential == POTENTIALS["su2_higgs"] else mean[:1]
 
     def grad(self, nsteps: int, stride: int = 0, want_phi: bool = True, want_pi: bool = True,
@@ -294,8 +304,13 @@ class Lattice:
                     work = torch.empty(need, dtype=torch.uint8, device="cuda")
             except torch.OutOfMemoryError:
                 need = 0
-        _check(lib().lattice_grad_in(self._ctx, C.byref(spec), C.byref(out), work.data_ptr() if need else None, need),
-               self._ctx)
+        rc = LAT_ENOMEM
+        if need:
+            rc = lib().lattice_grad_in(self._ctx, C.byref(spec), C.byref(out), work.data_ptr(), need)
+            work = None
+        if rc == LAT_ENOMEM:   # no trajectory, or no room beside it for the context's own arrays
+            rc = _call(lib().lattice_grad_in, self._ctx, C.byref(spec), C.byref(out), None, 0)
+        _check(rc, self._ctx)
         return dict(value=out.value, dO_dq=out.dO_dq, dO_dphi=gphi, dO_dpi=gpi, forward_ms=out.forward_ms,
                     reverse_ms=out.reverse_ms, dO_da0=out.dO_da0, dO_db0=out.dO_db0)
 
@@ -355,8 +370,8 @@ class LatticeBatch:
             stream = torch.cuda.current_stream()
         self.stream = stream
         self._ctx = C.c_void_p()
-        _check(lib().lattice_init_batch(C.byref(self._ctx), C.byref(self.params), n, Ns, fa,
-                                        1 if autotune else 0, C.c_void_p(stream.cuda_stream)), None)
+        _check(_call(lib().lattice_init_batch, C.byref(self._ctx), C.byref(self.params), n, Ns, fa,
+                     1 if autotune else 0, C.c_void_p(stream.cuda_stream)), None)
 
     def step(self, n: int):
         _check(lib().lattice_step(self._ctx, int(n)), self._ctx)
