@@ -5,9 +5,8 @@
 // Unnormalised forward DFT, sign e^{-i}, as a half spectrum F[(z N + y) HP + kx],
 // kx in [0, N/2], rows padded to HP (a multiple of 8) so that eight neighbouring
 // columns are one aligned 128-byte piece.
-//   x pass   two real rows per complex line of length N (rows y, y + 1 of one
-//            field, or the same row of two fields), separated by the symmetry of
-//            real transforms: A(k) = (Z(k) + Z*(N-k))/2, B(k) = (Z(k) - Z*(N-k))/(2i)
+//   x pass   two real rows of one field per complex line of length N, separated by
+//            the symmetry of real transforms: A(k) = (Z(k) + Z*(N-k))/2, B(k) = (Z(k) - Z*(N-k))/(2i)
 //   y pass   eight columns of a plane per block, in place
 //   z pass   eight columns per block; |F|^2 and mode counts go to the block's bins
 // A pass reads and writes the spectrum once, and the last one only reads it:
@@ -275,36 +274,32 @@ __device__ __forceinline__ void fft_lines(const FftPlan &P, unsigned lines, cons
     fft_any<COLS>(P.rad[P.nst - 1], P, Ns, lines, tw, rd, out);
 }
 
-// x pass.  pairs == 0: rows 2 l and 2 l + 1 of f0 to G0.  pairs != 0: row l of f0
-// and of the combination c0 f0 + c1 f1, to G0 and G1.  P.lines lines per block.
-template <typename T>
-__global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) fft_x(const T *__restrict__ f0, const T *__restrict__ f1, double c0,
-                                                        double c1, int pairs, double2 *__restrict__ G0,
-                                                        double2 *__restrict__ G1, const FftPlan P)
+// x pass: rows 2 l and 2 l + 1 of f0 (MIX: of c0 f0 + c1 f1) make line l, P.lines lines
+// per block.  A complex line's rounding follows its larger row, so both rows are one
+// array's: with a row of phi and one of its momentum in a line, a momentum of 1e-8 phi
+// kept nine digits.
+template <typename T, bool MIX>
+__global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
+fft_x(const T *__restrict__ f0, const T *__restrict__ f1, double c0, double c1, double2 *__restrict__ G, const FftPlan P)
 {
     extern __shared__ double2 fft_lds[];
     double2 *tw = fft_lds, *a = tw + P.N;
     double2 *b = a + (P.inplace ? 0 : P.lines * P.xpitch);
     double2 *z = P.nst % 2 == 0 ? a : b;                  // the last stage's result
-    const unsigned N = (unsigned)P.N, rows = N * N;
-    const unsigned nl = pairs ? rows : (rows + 1) / 2;    // complex lines in all
+    const unsigned N = (unsigned)P.N, rows = N * N, nl = (rows + 1) / 2;
     const unsigned l0 = blockIdx.x * (unsigned)P.lines;
     const unsigned mine = min((unsigned)P.lines, nl - l0);
     for (unsigned i = threadIdx.x; i < N; i += blockDim.x) tw[i] = P.tw[i];
+    auto value = [&](size_t o) {
+        double v = (double)f0[o];
+        if constexpr (MIX) v = c0 * v + c1 * (double)f1[o];
+        return v;
+    };
     fft_lines<false>(
         P, mine, tw, a, b,
         [&](unsigned l, unsigned x) {
-            double2 v;
-            if (pairs) {
-                const size_t o = (size_t)(l0 + l) * N + x;
-                v.x = (double)f0[o];
-                v.y = c0 * v.x + c1 * (double)f1[o];
-            } else {
-                const size_t r = 2 * (size_t)(l0 + l);
-                v.x = (double)f0[r * N + x];
-                v.y = r + 1 < rows ? (double)f0[(r + 1) * N + x] : 0.0;
-            }
-            return v;
+            const size_t r = 2 * (size_t)(l0 + l), o = r * N + x;
+            return double2{value(o), r + 1 < rows ? value(o + N) : 0.0};
         },
         [&](unsigned l, unsigned i, double2 v) { z[l * P.xpitch + fft_slot<false>(i)] = v; });
     // whole padded rows (zeros past N / 2): no partly written pieces of memory
@@ -317,15 +312,9 @@ __global__ void __launch_bounds__(kFftMaxThreads) __attribute__((amdgpu_waves_pe
             A = double2{0.5 * (p.x + m.x), 0.5 * (p.y - m.y)};
             B = double2{0.5 * (p.y + m.y), 0.5 * (m.x - p.x)};
         }
-        if (pairs) {
-            const size_t o = (size_t)(l0 + l) * HP + k;
-            G0[o] = A;
-            G1[o] = B;
-        } else {
-            const size_t r = 2 * (size_t)(l0 + l);
-            G0[r * HP + k] = A;
-            if (r + 1 < rows) G0[(r + 1) * HP + k] = B;
-        }
+        const size_t r = 2 * (size_t)(l0 + l);
+        G[r * HP + k] = A;
+        if (r + 1 < rows) G[(r + 1) * HP + k] = B;
     }
 }
 

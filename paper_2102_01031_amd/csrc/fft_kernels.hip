@@ -75,16 +75,26 @@ static size_t lines_lds(const FftPlan &p, int pitch)
     return ((size_t)p.N + (size_t)(p.inplace ? 1 : 2) * kFftCols * pitch) * sizeof(double2);
 }
 
+template <typename T, bool MIX>
+static hipError_t x_pass_of(const FftPlan &p, const void *f0, const void *f1, double c0, double c1, double2 *G,
+                            hipStream_t st)
+{
+    const long nl = ((long)p.N * p.N + 1) / 2;
+    const auto fn = fft_x<T, MIX>;
+    const hipError_t e = allow_lds(fn);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((nl + p.lines - 1) / p.lines)), dim3(p.threads), lines_lds(p, p.xpitch), st,
+                       (const T *)f0, (const T *)f1, c0, c1, G, p);
+    return hipGetLastError();
+}
+
+// f0 to G0, and for nq = 2 the combination to G1
 template <typename T>
 static hipError_t x_pass(const FftPlan &p, const void *f0, const void *f1, double c0, double c1, int nq, double2 *G0,
                          double2 *G1, hipStream_t st)
 {
-    const long rows = (long)p.N * p.N, nl = nq == 2 ? rows : (rows + 1) / 2;
-    hipError_t e = allow_lds(fft_x<T>);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fft_x<T>, dim3((unsigned)((nl + p.lines - 1) / p.lines)), dim3(p.threads), lines_lds(p, p.xpitch), st,
-                       (const T *)f0, (const T *)f1, c0, c1, nq == 2 ? 1 : 0, G0, G1, p);
-    return hipGetLastError();
+    const hipError_t e = x_pass_of<T, false>(p, f0, nullptr, 1.0, 0.0, G0, st);
+    return e != hipSuccess || nq == 1 ? e : x_pass_of<T, true>(p, f0, f1, c0, c1, G1, st);
 }
 
 hipError_t fft_spectra(const FftPlan &p, bool f32, const void *f0, const void *f1, double c0, double c1, int nq,
