@@ -2620,8 +2620,8 @@ U1Args u1_args_dev(lat_ctx *c)
     return a;
 }
 
-// U(1) launch geometry.  u1_span where a block's rows fit: 17 TY + 24 doubles of LDS
-// per x position, at most 512 sites per block.  Of all row counts and z chunks the one
+// U(1) launch geometry.  u1_span where a block's rows fit: at most 512 sites per block
+// (u1_span_lds, 14 TY + 21 doubles per x position, then fits too).  Of all row counts and z chunks the one
 // with the least rounds * (planes + 2 of a block's start-up) * (threads resident per
 // CU, a halo row counted as 0.6 of a row for its loads and half of its sines, and not
 // below 512: fewer wait for latency all the same).  96^3: 30.4 us per pass in five

@@ -99,8 +99,8 @@ __global__ void __launch_bounds__(TX *TY) u1_stage(const U1Args g)
     const int N = g.N;
     const int x = bx * TX + tx, y = by * TY + ty;
     const bool valid = x < N && y < N;
-    // the energy pass takes a column of zc planes per block (fewer blocks, so
-    // fewer ticket releases); the other passes one plane
+    // the energy pass takes a column of zc planes per block (fewer partials for the
+    // kernel that adds them up); the other passes one plane
     const int zb = MODE == kU1Energy ? (rest / g.tiles_y) * g.zc : rest / g.tiles_y;
     const int ze = MODE == kU1Energy ? min(zb + g.zc, N) : zb + 1;
 
@@ -437,7 +437,7 @@ __global__ void __launch_bounds__(kGaugeFinishThreads) u1_drift(const U1Args g, 
     for (int i = 0; i < 3; ++i) g.A_out[i][n] = A[i] + hdA * q[i];
 }
 
-// The passes of u1_stage for lattices whose block rows fit LDS (N up to 440), with
+// The passes of u1_stage for lattices whose rows fit a block (N up to 512), with
 // the transcendental work shared between neighbouring sites.  A block owns TY whole
 // x rows, one thread per site (threads rounded up to whole wavefronts), and marches
 // z over [z0, z1).  Per plane every site evaluates its own three plaquette sines
@@ -446,13 +446,22 @@ __global__ void __launch_bounds__(kGaugeFinishThreads) u1_drift(const U1Args g, 
 // the previous plane, and the row y0 - 1 below the block is evaluated by the block's
 // threads, one operation each.  Every angle is formed by the same expression, in the
 // same order, as in u1_stage, which evaluates 9 sines and 6 phases per site and reads
-// 44 values.  Bound by memory at 128^3 (58 us per step pass, 5.8 TB/s; 102 us while
-// the phases came back from a call through pointers, that is, through scratch), by
-// the sines and the halo row below it: 96^3 step pass 30 us, the kick pass of
-// u1_stage 47, its energy pass 110 against 45.
+// 44 values.  Bound by instruction issue as much as by memory, one block of at most 512
+// threads per CU: 128^3 step pass 62 us on average over lattices in turn, 5.4 TB/s (66
+// with an LDS array per value, whose addresses took 150 more instructions per plane, and
+// in a kernel with the row length known at compile time), energy pass 63 (67); 96^3 step
+// pass 30.5 us (32.1; u1_stage 57), energy pass 31 (33; u1_stage 115), kick-and-sums
+// 32.2 (33.4).
 constexpr int kU1SpanThreads = 512;
-// LDS of a block of TY rows (doubles)
-inline size_t u1_span_lds(int N, int TY) { return (size_t)N * (17 * (size_t)TY + 24); }
+// LDS (doubles): two records of seven values per x position and row, the fields' on the
+// rows y0 - 1 .. y0 + TY, the sines' and phases' on y0 - 1 .. y0 + TY - 1.  A site reads its
+// neighbours' records at constant offsets from the addresses of five places, formed once
+// (an array per value took an address each, a third of the loop's integer instructions);
+// seven, an odd number, spreads neighbouring records over the banks.
+constexpr int kU1Rec = 7;
+enum U1Field : int { kU1Psi = 0, kU1Ax = 4, kU1Az = 5, kU1Ay = 6 };   // psi: two parities of (psi0, psi1)
+enum U1Trig : int { kU1Sxy = 0, kU1Syz = 1, kU1Cy = 2, kU1Sy = 3, kU1Sxz = 4, kU1Cx = 5, kU1Sx = 6 };
+inline size_t u1_span_lds(int N, int TY) { return (size_t)kU1Rec * N * (2 * (size_t)TY + 3); }
 
 template <int HPT, int MODE>
 __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY)
@@ -476,26 +485,24 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
     const int r = own ? tid / N + 1 : 1;      // LDS row of this thread's site (rows 0 .. nr + 1 stand for y0 - 1 .. y0 + nr)
     const int x = own ? tid - (r - 1) * N : 0;
     const int xm = x == 0 ? N - 1 : x - 1, xp = x == N - 1 ? 0 : x + 1;
-    const int ro = r * N + x;                 // this site in rows 0 .. nr + 1 arrays
-    const int wo = (r - 1) * N + x;           // this site in own-row arrays
 
-    // LDS: psi and A of the current plane, double-buffered by plane parity so that
-    // storing plane z + 1 cannot race with the last reads of plane z; then the
-    // sines and phases
-    const int RN = (TY + 2) * N, RM = (TY + 1) * N, RO = TY * N;
-    double *const s_p0_ = u1_lds, *const s_p1_ = s_p0_ + 2 * RN, *const s_ax_ = s_p1_ + 2 * RN,
-                 *const s_az_ = s_ax_ + 2 * RN;                        // rows 0 .. TY + 1
-    double *const s_ay_ = s_az_ + 2 * RN, *const s_ayn_ = s_ay_ + 2 * RM;   // A_y rows 0 .. TY; A_y(row 0, z + 1)
-    double *const s_sxy = s_ayn_ + 2 * N, *const s_syz = s_sxy + RM;   // rows 0 .. TY
-    double *const s_cy = s_syz + RM, *const s_sy = s_cy + RM;          // phase of A_y, rows 0 .. TY
-    double *const s_sxz = s_sy + RM;                                   // own rows (index row - 1)
-    double *const s_cx = s_sxz + RO, *const s_sx = s_cx + RO;          // phase of A_x, own rows
+    // LDS places: this site and its neighbours in the field records (f_*) and the sines'
+    // (t_*), whose rows 0 .. nr + 1 stand for y0 - 1 .. y0 + nr.  psi is double-buffered by
+    // plane parity, so that storing plane z + 1 cannot race with the last reads of plane z;
+    // the other values are read before the barrier that the next plane's stores follow.
+    double *const F = u1_lds, *const S = F + kU1Rec * (TY + 2) * N;
+    const int ro = kU1Rec * (r * N + x), rxm = kU1Rec * (r * N + xm), rdn = ro - kU1Rec * N;
+    double *const f_o = F + ro, *const f_dn = F + rdn, *const f_up = F + ro + kU1Rec * N;
+    double *const f_xm = F + rxm, *const f_xp = F + kU1Rec * (r * N + xp);
+    double *const t_o = S + ro, *const t_dn = S + rdn, *const t_xm = S + rxm;
+    double *const top = F + kU1Rec * (nr + 1) * N;   // row nr + 1; its A_y holds A_y(row 0, z + 1)
 
     const unsigned NN = (unsigned)N * (unsigned)N;   // 8 N^3 < 2^32
     const unsigned so = (unsigned)((y0 + r - 1) * N + x);   // site offset within a plane
     const int yb = (y0 == 0 ? N - 1 : y0 - 1) * N;
     const int yt = ((y0 + nr) % N) * N;
     const int NH = 2 * N, NOP = 3 * N;        // halo cells and halo-row operations per plane
+    const int op0 = tid / N, hx0 = tid - op0 * N, dop = NT / N, dhx = NT - dop * N;   // this thread's first, and the step
 
     const double edx = g.e * g.dx;
     const double inv_dx2 = 1.0 / (g.dx * g.dx);
@@ -512,17 +519,18 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
     }
 
     // halo cells: c < N is row 0 (y0 - 1), else row nr + 1 (y0 + nr)
-    int hrow[HPT], hx[HPT];
+    double *hc[HPT];   // the cell's record
+    int hx[HPT];
     unsigned hoff[HPT];
-    bool hval[HPT];
+    bool hval[HPT], hbot[HPT];
 #pragma unroll
     for (int j = 0; j < HPT; ++j) {
         const int c = tid + j * NT;
         hval[j] = c < NH;
-        const bool bot = c < N;
-        hx[j] = bot ? c : c - N;
-        hrow[j] = bot ? 0 : nr + 1;
-        hoff[j] = hval[j] ? (unsigned)((bot ? yb : yt) + hx[j]) : 0u;
+        hbot[j] = c < N;
+        hx[j] = hbot[j] ? c : (hval[j] ? c - N : 0);
+        hc[j] = (hbot[j] ? F : top) + kU1Rec * hx[j];
+        hoff[j] = hval[j] ? (unsigned)((hbot[j] ? yb : yt) + hx[j]) : 0u;
     }
 
     double wm[2], w0[2], wp[2];   // psi at z - 1, z, z + 1
@@ -539,7 +547,6 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
         const unsigned o0 = (unsigned)z0 * NN;
         const unsigned o1 = (unsigned)((z0 + 1) % N) * NN;
         double am[3];
-        double *const s_az1 = s_az_ + RN;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             wm[c] = ld32(g.phi_in[c], om + so);
@@ -552,7 +559,7 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
             a0[i] = ld32(g.A_in[i], o0 + so);
             a1[i] = ld32(g.A_in[i], o1 + so);
         }
-        if (own) s_az1[ro] = am[2];
+        if (own) f_o[kU1Az] = am[2];
 #pragma unroll
         for (int j = 0; j < HPT; ++j) {
             hp0[j] = hp1[j] = hax[j] = hay[j] = haz[j] = hayn[j] = 0.0;
@@ -561,17 +568,17 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
                 hp1[j] = ld32(g.phi_in[1], o0 + hoff[j]);
                 hax[j] = ld32(g.A_in[0], o0 + hoff[j]);
                 haz[j] = ld32(g.A_in[2], o0 + hoff[j]);
-                if (hrow[j] == 0) {
+                if (hbot[j]) {
                     hay[j] = ld32(g.A_in[1], o0 + hoff[j]);
                     hayn[j] = ld32(g.A_in[1], o1 + hoff[j]);
                 } else {
-                    s_az1[(nr + 1) * N + hx[j]] = ld32(g.A_in[2], om + hoff[j]);
+                    hc[j][kU1Az] = ld32(g.A_in[2], om + hoff[j]);
                 }
             }
         }
         __syncthreads();
-        const double txz = edx * ((s_az1[r * N + xp] - am[2]) - a0[0] + am[0]);
-        const double tyz = edx * ((s_az1[(r + 1) * N + x] - am[2]) - a0[1] + am[1]);
+        const double txz = edx * ((f_xp[kU1Az] - am[2]) - a0[0] + am[0]);
+        const double tyz = edx * ((f_up[kU1Az] - am[2]) - a0[1] + am[1]);
         sxzm = lat_sin(txz);
         syzm = lat_sin(tyz);
         lat_sincos(edx * am[2], &szm, &czm);
@@ -580,28 +587,25 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
 
     for (int z = z0; z < z1; ++z) {
         const unsigned oz = (unsigned)z * NN;
-        const int b = (z - z0) & 1;
-        double *const s_p0 = s_p0_ + b * RN, *const s_p1 = s_p1_ + b * RN, *const s_ax = s_ax_ + b * RN,
-                     *const s_az = s_az_ + b * RN, *const s_ay = s_ay_ + b * RM, *const s_ayn = s_ayn_ + b * N;
+        const int q = kU1Psi + 2 * ((z - z0) & 1);   // this plane's psi
         // (A) plane z into LDS
         if (own) {
-            s_p0[ro] = w0[0];
-            s_p1[ro] = w0[1];
-            s_ax[ro] = a0[0];
-            s_ay[ro] = a0[1];
-            s_az[ro] = a0[2];
+            f_o[q] = w0[0];
+            f_o[q + 1] = w0[1];
+            f_o[kU1Ax] = a0[0];
+            f_o[kU1Ay] = a0[1];
+            f_o[kU1Az] = a0[2];
         }
 #pragma unroll
         for (int j = 0; j < HPT; ++j) {
             if (hval[j]) {
-                const int hs = hrow[j] * N + hx[j];
-                s_p0[hs] = hp0[j];
-                s_p1[hs] = hp1[j];
-                s_ax[hs] = hax[j];
-                s_az[hs] = haz[j];
-                if (hrow[j] == 0) {
-                    s_ay[hx[j]] = hay[j];
-                    s_ayn[hx[j]] = hayn[j];
+                hc[j][q] = hp0[j];
+                hc[j][q + 1] = hp1[j];
+                hc[j][kU1Ax] = hax[j];
+                hc[j][kU1Az] = haz[j];
+                if (hbot[j]) {
+                    hc[j][kU1Ay] = hay[j];
+                    top[kU1Rec * hx[j] + kU1Ay] = hayn[j];
                 }
             }
         }
@@ -628,7 +632,7 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
                 hp1[j] = ld32(g.phi_in[1], oh + hoff[j]);
                 hax[j] = ld32(g.A_in[0], oh + hoff[j]);
                 haz[j] = ld32(g.A_in[2], oh + hoff[j]);
-                if (hrow[j] == 0) {
+                if (hbot[j]) {
                     hay[j] = ld32(g.A_in[1], oh + hoff[j]);
                     hayn[j] = ld32(g.A_in[1], ohn + hoff[j]);
                 }
@@ -640,9 +644,9 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
         double th[3];   // own plaquette angles (the energy mode's magnetic term)
         double ss[3], ps[3], pc[3];   // their sines; sine and cosine of the link phases
         {
-            const double txy = edx * ((s_ay[r * N + xp] - a0[1]) - s_ax[(r + 1) * N + x] + a0[0]);
-            const double txz = edx * ((s_az[r * N + xp] - a0[2]) - a1[0] + a0[0]);
-            const double tyz = edx * ((s_az[(r + 1) * N + x] - a0[2]) - a1[1] + a0[1]);
+            const double txy = edx * ((f_xp[kU1Ay] - a0[1]) - f_up[kU1Ax] + a0[0]);
+            const double txz = edx * ((f_xp[kU1Az] - a0[2]) - a1[0] + a0[0]);
+            const double tyz = edx * ((f_up[kU1Az] - a0[2]) - a1[1] + a0[1]);
             th[0] = txy;
             th[1] = txz;
             th[2] = tyz;
@@ -654,27 +658,33 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
 #pragma unroll
             for (int j = 0; j < 3; ++j) lat_sincos(edx * a0[j], &ps[j], &pc[j]);
             if (own) {
-                s_sxy[ro] = ss[0];
-                s_sxz[wo] = ss[1];
-                s_syz[ro] = ss[2];
-                s_sx[wo] = ps[0];
-                s_cx[wo] = pc[0];
-                s_sy[ro] = ps[1];
-                s_cy[ro] = pc[1];
+                t_o[kU1Sxy] = ss[0];
+                t_o[kU1Sxz] = ss[1];
+                t_o[kU1Syz] = ss[2];
+                t_o[kU1Sx] = ps[0];
+                t_o[kU1Cx] = pc[0];
+                t_o[kU1Sy] = ps[1];
+                t_o[kU1Cy] = pc[1];
             }
         }
-        for (int id = tid; id < NOP; id += NT) {
-            const int op = id / N, hxo = id - op * N;
-            const int hxp = hxo == N - 1 ? 0 : hxo + 1;
+        for (int id = tid, op = op0, hxo = hx0; id < NOP; id += NT) {
+            double *const f = F + kU1Rec * hxo, *const t = S + kU1Rec * hxo;
             if (op == 0) {
                 double sv, cv;
-                lat_sincos(edx * s_ay[hxo], &sv, &cv);
-                s_sy[hxo] = sv;
-                s_cy[hxo] = cv;
+                lat_sincos(edx * f[kU1Ay], &sv, &cv);
+                t[kU1Sy] = sv;
+                t[kU1Cy] = cv;
             } else if (op == 1) {
-                s_sxy[hxo] = lat_sin(edx * ((s_ay[hxp] - s_ay[hxo]) - s_ax[N + hxo] + s_ax[hxo]));
+                const double ayp = hxo == N - 1 ? F[kU1Ay] : f[kU1Rec + kU1Ay];
+                t[kU1Sxy] = lat_sin(edx * ((ayp - f[kU1Ay]) - f[kU1Rec * N + kU1Ax] + f[kU1Ax]));
             } else {
-                s_syz[hxo] = lat_sin(edx * ((s_az[N + hxo] - s_az[hxo]) - s_ayn[hxo] + s_ay[hxo]));
+                t[kU1Syz] = lat_sin(edx * ((f[kU1Rec * N + kU1Az] - f[kU1Az]) - top[kU1Rec * hxo + kU1Ay] + f[kU1Ay]));
+            }
+            op += dop;
+            hxo += dhx;
+            if (hxo >= N) {
+                hxo -= N;
+                ++op;
             }
         }
         __syncthreads();
@@ -688,22 +698,22 @@ __global__ void __launch_bounds__(kU1SpanThreads) u1_span(const U1Args g, int TY
 #pragma unroll
             for (int i = 0; i < 3; ++i) pa[i] = ld32(g.piA[i], o);
             const double sxy = ss[0], sxz = ss[1], syz = ss[2];
-            const double mag[3] = {(sxy - s_sxy[ro - N]) + (sxz - sxzm),
-                                   (-sxy + s_sxy[r * N + xm]) + (syz - syzm),
-                                   (-sxz + s_sxz[(r - 1) * N + xm]) + (-syz + s_syz[ro - N])};
+            const double mag[3] = {(sxy - t_dn[kU1Sxy]) + (sxz - sxzm),
+                                   (-sxy + t_xm[kU1Sxy]) + (syz - syzm),
+                                   (-sxz + t_xm[kU1Sxz]) + (-syz + t_dn[kU1Syz])};
             const double pr = w0[0], pim = w0[1];
             double d2r = 0.0, d2i = 0.0, J[3], grad2 = 0.0;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 double qr, qi, rr, ri, sm, cm;
                 if (i == 0) {
-                    qr = s_p0[r * N + xp]; qi = s_p1[r * N + xp];
-                    rr = s_p0[r * N + xm]; ri = s_p1[r * N + xm];
-                    sm = s_sx[(r - 1) * N + xm]; cm = s_cx[(r - 1) * N + xm];
+                    qr = f_xp[q]; qi = f_xp[q + 1];
+                    rr = f_xm[q]; ri = f_xm[q + 1];
+                    sm = t_xm[kU1Sx]; cm = t_xm[kU1Cx];
                 } else if (i == 1) {
-                    qr = s_p0[ro + N]; qi = s_p1[ro + N];
-                    rr = s_p0[ro - N]; ri = s_p1[ro - N];
-                    sm = s_sy[ro - N]; cm = s_cy[ro - N];
+                    qr = f_up[q]; qi = f_up[q + 1];
+                    rr = f_dn[q]; ri = f_dn[q + 1];
+                    sm = t_dn[kU1Sy]; cm = t_dn[kU1Cy];
                 } else {
                     qr = wp[0]; qi = wp[1];
                     rr = wm[0]; ri = wm[1];
