@@ -848,6 +848,7 @@ lat_status run_pass_t(lat_ctx *c, int variant, int pass_index, int last_mode, hi
     }
     const bool red = variant == kKickOnlyRed || variant == kDriftKickRed || variant == kKickCopyRed || variant == kEnergy;
     const bool en_site = variant == kEnergy && energy_on_site(c);
+    if (a.fin && !red) return fail(c, LAT_EHIP, "a pass without sums does not finish another's");
     if (en_site || (red ? c->site_red : c->site_nblocks > 0)) {
         if (c->by_value) {
             a.imm = c->coef_host[pass_index];

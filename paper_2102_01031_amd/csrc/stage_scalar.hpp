@@ -436,9 +436,11 @@ __global__ void __launch_bounds__(TX *TY) scalar_stage(const ScalarArgs<T> g)
     }
 
     PassCoef C = *g.coef;
-    if (g.fin) {
-        __shared__ double lds_coef[4];
-        finalise_prologue<NT, NF>(g, lds_red, lds_coef, C);
+    if constexpr (RED) {   // the other passes follow no deferring pass
+        if (g.fin) {
+            __shared__ double lds_coef[4];
+            finalise_prologue<NT, NF>(g, lds_red, lds_coef, C);
+        }
     }
     const T dl = (T)C.dload, c1 = (T)C.c1, c2 = (T)C.c2, de = (T)C.dend;
     const T ka1 = (T)C.ka1, ka3 = (T)C.ka3, idx2 = (T)g.inv_dx2;
