@@ -2981,7 +2981,10 @@ size_t su2_partial_capacity(const lat_ctx *c) { return (size_t)su2_tiles(c) * c-
 // SU(2) tiles, block order, z planes per block and cache policy.  A tile row is a
 // k-th of a lattice row, a tile as many rows as 256 threads hold; of k = 1 .. 8 the one
 // that leaves the fewest threads idle, each cut counted as 8 % (a wavefront's accesses
-// break at a row's end): whole rows at 24, 40, 48, 64, 72, 128, halves at 96 and 100.
+// break at a row's end): whole rows at 24, 40, 48, 64, 72, 128, halves at 100.  On known
+// backgrounds 11 % where a tile of whole rows holds five of them: step passes at 44^3 16.6 us
+// in 44 x 5 tiles, 20.4 in 22 x 11, one of which then fell to each XCD; the summing
+// passes, bound by their arithmetic, take the same time in both.
 // 64 x 4 on every size left up to half of the threads without a site: eight leapfrog
 // steps at 72^3 70.6 us each in 64 x 4, 58.8 in 36 x 7, 52.3 in 72 x 3 tiles.
 // The blocks of a plane are dealt to the XCDs in bands (su2_stage) unless that would
@@ -2998,14 +3001,15 @@ void su2_geometry(lat_ctx *c)
     const int N = c->N, most = std::min(N, kSU2Threads);
     const char *te = std::getenv("LATTICE_SU2_TILE");
     const int want = te ? std::atoi(te) : 0;
+    const double cut = c->p.expansion != LAT_EXP_SELF && 5 * N <= kSU2Threads ? 0.11 : 0.08;
     double best = -1.0e9;
     for (int k = 1; k <= 8; ++k) {
         const int tx = (N + k - 1) / k;
         if (tx > kSU2Threads) continue;
         const int ty = std::min(N, kSU2Threads / tx);
         const double used = (double)N * N / ((double)k * ((N + ty - 1) / ty) * kSU2Threads);
-        if (used - 0.08 * (k - 1) > best) {
-            best = used - 0.08 * (k - 1);
+        if (used - cut * (k - 1) > best) {
+            best = used - cut * (k - 1);
             c->su2_tx = tx;
             c->su2_ty = ty;
         }
