@@ -388,7 +388,7 @@ def main():
     c0 = time.perf_counter()
     sp = lat.spectrum(0, "phi")
     spectrum = {"ms": 1e3 * (time.perf_counter() - c0), "bins": len(sp["sum"]), "field": "phi",
-                "includes": "copy to the transform buffer, float64 real-to-complex FFT, binning, host copy"}
+                "includes": "float64 line transforms with fused binning, sums to the host"}
     # occupation number of chi (two transforms, binning, <phi^2> reduction, host copy)
     lat.occupation(1)                 # second half-spectrum buffer on the first call
     torch.cuda.synchronize()

@@ -288,7 +288,9 @@ lat_status lattice_batch_tile(const lat_ctx *ctx, int32_t N, int32_t *tile_x, in
  * LF steps of real scalar fields with N <= 32 and no self-consistent
  * expansion run up to four steps per kernel launch (each block recomputes the
  * edge of its window, so the state agrees with one pass per step to
- * rounding); the number of launches is visible in lattice_stats.
+ * rounding); on a known background (no expansion or a fixed one) lattices whose passes
+ * stream from memory run two passes per launch.  The number of launches is visible in
+ * lattice_stats.
  * Asynchronous on the context stream. */
 lat_status lattice_step(lat_ctx *ctx, int64_t nsteps);
 
@@ -391,7 +393,8 @@ typedef struct lat_grad_out {
  * unnormalised inverse transform of phi_s's spectrum kept on shell b, scaled
  * by 2 c_b (the transforms of lattice_spectrum; their buffers and plans are kept
  * like its).  A bad observable, field, bin or a nonzero reserved
- * member gives LAT_EINVAL.  Synchronises the stream. */
+ * member gives LAT_EINVAL.  A call that finds no memory (LAT_ENOMEM) has changed
+ * nothing.  Synchronises the stream. */
 lat_status lattice_grad(lat_ctx *ctx, const lat_grad_spec *spec, lat_grad_out *out);
 
 /* lattice_grad with a device work array of the caller's (16-byte aligned, used until
@@ -408,7 +411,9 @@ lat_status lattice_grad_in(lat_ctx *ctx, const lat_grad_spec *spec, lat_grad_out
 /* Launch statistics of the stencil kernels, per kernel kind:
  *   0 kick only, 1 kick only + reductions, 2 drift only (the end of a
  *   self-consistent leapfrog call), 3 drift on load + kick + reductions,
- *   4 kick + drift at end (leapfrog; velocity-Verlet without self-consistent expansion),
+ *   4 kick + drift at end (leapfrog; velocity-Verlet without self-consistent expansion;
+ *     one launch may hold up to five leapfrog steps of a small lattice, or two passes of
+ *     one whose passes stream from memory),
  *   5 energy (read only), 6 U(1) or SU(2) leapfrog (and their energy passes), 7 adjoint reverse pass.
  * kernel_ms is accumulated from HIP events recorded on the context stream around
  * each launch while profiling is on (lattice_profile); it stays 0 otherwise. */

@@ -14,9 +14,10 @@ expansion with ``kappa2``, from ``a0`` and ``b0`` = a' at the start; b0 must be
 given, and both may be tensors that require a gradient).  ``alpha`` is the
 alpha-time exponent.
 
-When a gradient is wanted the forward call runs ``lattice_grad`` (reverse
-integration with checkpoints) and keeps dO/d(phi, chi, pi_phi, pi_chi) at the
-initial time, dO/dq and, with self-consistent expansion, dO/da0 and dO/db0 for
+When a gradient is wanted the forward call runs ``Lattice.grad`` (with ``stride=0``
+over a kept trajectory of up to 8 GiB, which torch's allocator holds between
+calls; else, and where there is no room for one, by reverse integration with
+checkpoints) and keeps dO/d(phi, chi, pi_phi, pi_chi) at the initial time, dO/dq and, with self-consistent expansion, dO/da0 and dO/db0 for
 the backward.  Under ``torch.no_grad()``, or when no input requires a gradient,
 only the forward steps and the observable run.  The inputs are copied; they
 are not modified.

@@ -9,17 +9,20 @@
 //            the symmetry of real transforms: A(k) = (Z(k) + Z*(N-k))/2, B(k) = (Z(k) - Z*(N-k))/(2i)
 //   y pass   eight columns of a plane per block, in place
 //   z pass   eight columns per block; |F|^2 and mode counts go to the block's bins
-// A pass reads and writes the spectrum once, and the last one only reads it:
-// bound by memory.  At 256^3 in float64 one spectrum moves 0.70 GB.
+// A pass reads and writes the spectrum once, and the last one only reads it: at 256^3 in
+// float64 one spectrum moves 0.70 GB.  The y pass runs at memory's rate (6.0 TB/s); the x
+// passes (3.9, with the combination 3.7) share their time with LDS, four conflict cycles to
+// each of its instructions; the z pass (1.9) is bound by binning, one shell index and
+// one LDS atomic per mode.
 // Lines are transformed by Stockham's self-sorting algorithm with radices 8, 4, 2,
 // 3, 5 and 7 (a plain sum per output for larger primes, between two buffers after a
 // copy into LDS), one butterfly per thread and stage where a block has the threads, so
 // that a stage can write over the LDS buffer it read (half the LDS of two buffers,
 // twice the blocks per CU); the first stage reads its points from memory and the
 // last stage of the y pass writes them without another trip through LDS.  At 256^3
-// in float64: x pass 68 us (99 with two buffers and every stage through LDS), y pass
-// 49 (92), z pass 76 (101), 0.70 GB in all; the library transform, its input copy
-// and a binning pass took 270 us.  The roots of unity come from a
+// in float64: x pass 72 us (99 with two buffers and every stage through LDS; of the
+// combination of two arrays 112), y pass 48 (92), z pass 77 (101), 0.70 GB in all; the
+// library transform, its input copy and a binning pass took 270 us.  The roots of unity come from a
 // table computed on the host in extended precision.
 #pragma once
 #include "common.hpp"

@@ -1083,8 +1083,6 @@ lat_status reserve_coef(lat_ctx *c, size_t n)
 lat_status upload_coef(lat_ctx *c, size_t n)
 {
     const int k = c->ring_slot;
-    if (!c->traj_rec)
-        for (size_t i = 0; i < n; ++i) c->coef_host[i].traj = nullptr;
     HIPCHK(c, hipMemcpyAsync(c->coef, c->coef_host, n * sizeof(PassCoef), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipEventRecord(c->ring_ev[k], c->stream));
     c->ring_pending[k] = true;

@@ -8,11 +8,12 @@
 // sites.  Per plane p of the march: the first pass at p (its in-plane neighbours from
 // LDS, its z neighbours from registers), its phi to a second LDS plane, then the second
 // pass at p - 1, one barrier in all.  The widened sites are advanced redundantly, by
-// the same expressions as their owners, so the result is that of two passes, bit for
-// bit.  Every array is read and written once for two passes (the widened part from
+// the same expressions as their owners, so the result is that of two passes, to the
+// rounding of products that the compiler fuses in one kernel and not in the other.  Every array is read and written once for two passes (the widened part from
 // L2); momenta are read beyond the own sites and so go to the other buffer too.
-// Bound by LDS and the vector unit about as much as by memory: 98 to 140 KB of LDS, so
-// one block of 512 threads per CU.  Leapfrog step, single passes and pairs: one float64
+// Bound by LDS and the vector unit about as much as by memory: 63 KB (float32, one field,
+// N = 203) to 156 KB (float64, two fields, N = 506) of LDS, and as a rule a grid of one
+// block of 512 threads per CU.  384^3, one float64 field: 1.86 GB at 5.1 TB/s.  Leapfrog step, single passes and pairs: one float64
 // field 384^3 347 -> 175 us, 256^3 110 -> 62, 128^3 16.7 -> 15.1; two 256^3 187 -> 113,
 // 320^3 403 -> 238, 110^3 19.6 -> 17.4; float32, two fields 384^3 366 -> 187, one 256^3
 // 44 -> 36.

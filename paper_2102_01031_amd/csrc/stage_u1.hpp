@@ -446,12 +446,13 @@ __global__ void __launch_bounds__(kGaugeFinishThreads) u1_drift(const U1Args g, 
 // the previous plane, and the row y0 - 1 below the block is evaluated by the block's
 // threads, one operation each.  Every angle is formed by the same expression, in the
 // same order, as in u1_stage, which evaluates 9 sines and 6 phases per site and reads
-// 44 values.  Bound by instruction issue as much as by memory, one block of at most 512
-// threads per CU: 128^3 step pass 62 us on average over lattices in turn, 5.4 TB/s (66
+// 44 values.  Bound at 128^3 by memory and by what one block of eight wavefronts per CU
+// keeps in flight: step pass 62 us over lattices in turn, 357 MB through the L2 misses at
+// 5.7 TB/s, waves issuing vector work in 17% of their cycles and waiting in 21% (66 us
 // with an LDS array per value, whose addresses took 150 more instructions per plane, and
-// in a kernel with the row length known at compile time), energy pass 63 (67); 96^3 step
-// pass 30.5 us (32.1; u1_stage 57), energy pass 31 (33; u1_stage 115), kick-and-sums
-// 32.2 (33.4).
+// in a kernel with the row length known at compile time), energy pass 63 (67).  96^3 step
+// pass 30.5 us (32.1; u1_stage 57), energy pass 31 (33; u1_stage 115), kick-and-sums 32.2
+// (33.4): the sines, whose vector work takes a quarter of the wave cycles.
 constexpr int kU1SpanThreads = 512;
 // LDS (doubles): two records of seven values per x position and row, the fields' on the
 // rows y0 - 1 .. y0 + TY, the sines' and phases' on y0 - 1 .. y0 + TY - 1.  A site reads its
