@@ -151,12 +151,14 @@ def _check(code, ctx=None):
 def _call(fn, *args):
     """A library call that may allocate device memory.  Where there is none left, what
     torch's allocator holds unused (after a gradient up to 8 GiB, its trajectory) goes
-    back to the driver and the call is made once more."""
+    back to the driver and the call is made once more.  Not while the caller's stream is
+    captured, where nothing may be given back: the call's own error stands."""
     rc = fn(*args)
     if rc == LAT_ENOMEM:
         import torch
-        torch.cuda.empty_cache()
-        rc = fn(*args)
+        if not torch.cuda.is_current_stream_capturing():
+            torch.cuda.empty_cache()
+            rc = fn(*args)
     return rc
 
 
